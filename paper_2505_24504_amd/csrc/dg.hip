@@ -1,170 +1,212 @@
 // DG space operator of the well-balanced perturbation system (paper eqs.
 // convDiscr, elementint, surfaceint and perturbed-euler) on gfx950.
 //
-// One work-group holds EPB whole elements, one thread per GL node (k = 3: 8
-// elements x 16 nodes = 128 threads).  Element values are staged in LDS; each
-// thread then
-//   B  evaluates the volume flux at its node (total state U' + Ubar minus the
-//      background flux, minus the viscous flux) into LDS,
-//   C  loads the neighbour element's trace and normal derivative at one face
-//      point from global memory into registers (faces are evaluated from both
-//      sides; this costs flops, not HBM bytes) and evaluates HLLC minus the
-//      background HLLC, the interior-penalty terms and the symmetric term there,
-//   D  contracts the volume fluxes with the GL derivative matrix, lifts the
-//      face terms to its node and writes the requested output.
+// On Cartesian elements the operator splits by direction: the x-fluxes need only
+// x-derivatives and the z-fluxes only z-derivatives, and each is contracted along its
+// own direction.  A thread therefore takes one line of k + 1 GL nodes of an element
+// along x or along z, holds it in registers and does everything along it there with
+// wave-uniform weights: 128 threads of a work-group take the x-lines of a tile of
+// elements, 128 the z-lines.  Per tile:
+//   T  every line's trace and trace derivative at both ends; those at the high end, and
+//      the facing ends of the neighbour elements' lines outside the tile, go to LDS;
+//      the background of the tile's rows is staged with them;
+//   F  every line's face point at its low end (each face point of the grid once, at a
+//      tile's high end once more by the tile): HLLC minus the background HLLC, the
+//      interior-penalty terms and both sides' symmetric terms;
+//   V  the volume fluxes along the line (total state U' + Ubar minus the background
+//      flux, minus the viscous flux), contracted with the GL derivative matrix, and the
+//      face terms of both ends lifted to the line's nodes;
+//   D  the x-lines add the z-lines' result (through LDS) and write the output.
 // In JVP mode the kernel evaluates the fluxes of U' + eps y and differences them
 // point by point with those of U' before contracting.  The fluxes of U' are the
 // same for every product with one linearization state: mode 5 writes them (volume
 // fluxes per node, face terms per face point) once per linearization, and each
 // product reads them back instead of evaluating a second state.
+//
+// What bounds it: FP64 issue and LDS reads on large grids, on the density current
+// (256 x 64 elements, k = 3, one round of work-groups) the chain of its phases.  With a
+// thread per node, every face point evaluated from both sides and the background's HLLC
+// at each of them, M^-1 L_h took 705 us at 1024 x 1024 elements (viscous, k = 3) and an
+// explicit stage 15.3 us at 256 x 64 and 11.1 us at 197 x 45 (k = 2); this form takes
+// 449, 12.5 and 8.2 us with half the VALU and a third of the LDS work per node.  A
+// node-per-thread form with each tile face evaluated once reached 636, 13.3 and 7.9 us.
 #include "jfmg_internal.h"
 
 namespace jfmg {
 
+// Tiles of TEX x TEZ elements with HALF lines per direction: 32 elements (k = 3),
+// 42 (k = 2), 64 (k = 1).  The lines of neighbours (NHX + NHZ of them) and the face
+// points at the tile's high ends (NXF + NZF) each fit one wave per direction.
 template <int N1> struct DgShape {
-    static constexpr int NP = N1 * N1;
-    static constexpr int NTH = (N1 == 2) ? 64 : 128;
-    static constexpr int EPB = NTH / NP;
-    static constexpr int FPE = 4 * N1;   // face points per element
+    static constexpr int TEX = N1 == 3 ? 7 : 8, TEZ = N1 == 4 ? 4 : N1 == 3 ? 6 : 8;
+    static constexpr int NP = N1 * N1, HALF = 128, NTH = 2 * HALF, EPB = TEX * TEZ;
+    static constexpr int NXF = TEZ * N1, NZF = TEX * N1;     // high-end face points of x- and z-lines
+    static constexpr int NSLOT = NTH + 2 * (NXF + NZF);      // own lines, then left, right, bottom, top
+    static constexpr int ROWS = TEZ * N1, NROW = ROWS + TEZ + 1;   // background rows: nodes, then z-faces
+    static_assert(EPB * N1 <= HALF && 2 * NXF <= 64 && 2 * NZF <= 64 && NXF + NZF <= 64 && 3 * ROWS + TEZ + 1 <= 64,
+                  "tile shape");
 };
 
-__device__ __forceinline__ int face_nb(int f, int ex, int ez, int nx, int nz, int bc)
+// work-groups of a grid of nx x nz elements
+template <int N1> __host__ __device__ inline int dg_tiles(int nx, int nz)
 {
-    // returns neighbour element index, or -1 for a slip wall
-    if (f == 0) { if (ex > 0) return ez * nx + ex - 1; return bc == 1 ? ez * nx + nx - 1 : -1; }
-    if (f == 1) { if (ex < nx - 1) return ez * nx + ex + 1; return bc == 1 ? ez * nx : -1; }
-    if (f == 2) return ez > 0 ? (ez - 1) * nx + ex : -1;
-    return ez < nz - 1 ? (ez + 1) * nx + ex : -1;
+    return ((nx + DgShape<N1>::TEX - 1) / DgShape<N1>::TEX) * ((nz + DgShape<N1>::TEZ - 1) / DgShape<N1>::TEZ);
 }
 
-// Face terms of one state at face point r of an x-face (xf) or z-face of element
-// row ez with outward normal +e_D (pos) or -e_D, before the quadrature weight:
-//   fl = -H(U_in, U_out; n) (minus the background's H when BGSUB) plus, for
-//        viscous flow, the average of both sides' F_v . n minus the interior
-//        penalty on the jump of the velocity-like variables,
-//   sy = the symmetric term's jump mu (U_c,in - U_c,out - (U_c/rho)_in (rho_in - rho_out)).
-// The element's own values come from its LDS block sv; the neighbour nb (-1: a
-// slip wall, mirrored state) is read from U, plus eps Y when PLUSY.  When pos is
-// uniform over the wave the trace weights are scalar loads.
-template <int N1, bool NS, bool BGSUB, bool PLUSY>
-__device__ __forceinline__ void dg_face(const DgArgs& A, const double (&sv)[4][N1 * N1], const double* __restrict__ U,
-                                        const double* __restrict__ Y, double eps, long N, int nb, bool xf, bool pos,
-                                        int r, int ez, double (&fl)[4], double (&sy)[4])
+// LDS record of a background row (node row or z-face): rho, rho u, rho theta (the
+// background has no vertical wind), pressure, 1/(rho theta), d/dz of the three; with the
+// background subtracted also the HLLC flux of the background in the frame of the row's
+// faces (normal momentum at 1, tangential at 2) through a face inside the grid (or the
+// wall of the bottom or top row), for node rows through a wall on the low and on the
+// high side, and the x-momentum and rho theta components of the convective x-flux.
+enum { BR_RHO = 0, BR_MX = 1, BR_RT = 2, BR_P = 3, BR_IRT = 4, BR_DRHO = 5, BR_DMX = 6, BR_DRT = 7, BR_H = 8,
+       BR_HLO = 12, BR_HHI = 16, BR_F1 = 20, BR_F3 = 21 };
+static_assert(DG_REC == 22, "record length");
+
+// Record of node row (zr false) or z-face row i in rec; with bgsub the flux entries of
+// case v (0: inside the grid, 1 and 2: a wall on the low or high side), else and for
+// v = 0 the state entries.
+__device__ __forceinline__ void dg_record(const DgArgs& A, bool zr, int i, int v, bool bgsub, double* __restrict__ rec)
 {
-    constexpr int NP = N1 * N1;
-    const RefTab& R = A.R;
-    const double sg = pos ? 1.0 : -1.0;
-    const bool wall = nb < 0;
-    // trace and normal-derivative weights of the own and the other side
-    const double* es = pos ? R.ep : R.em;
-    const double* ds = pos ? R.dp : R.dm;
-    const double* eo = pos ? R.em : R.ep;
-    const double* dso = pos ? R.dm : R.dp;
-    double Ub[4], dUb[4];
-    const int zrow = xf ? (ez * N1 + r) : (ez + (pos ? 1 : 0));
-    const double* bgp = xf ? A.bg_node : A.bg_face;
-    const double* dbgp = xf ? A.dbg_node : A.dbg_face;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) { Ub[c] = bgp[zrow * 4 + c]; dUb[c] = dbgp[zrow * 4 + c]; }
-    const double pbz = xf ? A.pb_node[zrow] : A.pb_face[zrow];
-    const double irz = xf ? A.irt_node[zrow] : A.irt_face[zrow];
-    double trx[4], dnx[4];   // the neighbour's trace and normal derivative (d/d xi)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) trx[c] = dnx[c] = 0.0;
-    if (!wall) {
-        // every load of the neighbour's nodes first (one block: one memory round trip
-        // instead of one per component), then the sums in the same order
-        double vu[4][N1], vy[PLUSY ? 4 : 1][PLUSY ? N1 : 1];
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int j = 0; j < N1; ++j) {
-                const unsigned o = (unsigned)nb * NP + (xf ? r * N1 + j : j * N1 + r);
-                vu[c][j] = ld(U + c * N, o);
-                if constexpr (PLUSY) vy[c][j] = ld(Y + c * N, o);
-            }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int j = 0; j < N1; ++j) {
-                double v = vu[c][j];
-                if constexpr (PLUSY) v = v + eps * vy[c][j];
-                trx[c] += eo[j] * v;
-                if constexpr (NS) dnx[c] += dso[j] * v;
-            }
+    const double* bg = (zr ? A.bg_face : A.bg_node) + 4 * i;
+    const double* db = (zr ? A.dbg_face : A.dbg_node) + 4 * i;
+    const double pb = zr ? A.pb_face[i] : A.pb_node[i], irt = zr ? A.irt_face[i] : A.irt_node[i];
+    const double rho = bg[0], mx = bg[1], rt = bg[3];
+    if (v == 0) {
+        rec[BR_RHO] = rho;
+        rec[BR_MX] = mx;
+        rec[BR_RT] = rt;
+        rec[BR_P] = pb;
+        rec[BR_IRT] = irt;
+        rec[BR_DRHO] = db[0];
+        rec[BR_DMX] = db[1];
+        rec[BR_DRT] = db[3];
     }
-    double tro[4], Uo[4], Ux[4], H[4];
+    if (bgsub) {
+        double UL[4] = {rho, zr ? 0.0 : mx, zr ? mx : 0.0, rt}, UR[4], H[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) UR[c] = UL[c];
+        if (v == 1 || (zr && i == 0)) UL[1] = -UL[1];
+        if (v == 2 || (zr && i == A.nz)) UR[1] = -UR[1];
+        const double ir = frcp(rho);
+        hllc_ax<double, 1>(A.gas, UL, UR, pb, pb, ir, ir, H);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) rec[(v == 0 ? BR_H : v == 1 ? BR_HLO : BR_HHI) + c] = H[c];
+        if (v == 0) {
+            const double q1 = mx * ir;
+            rec[BR_F1] = mx * q1 + pb;
+            rec[BR_F3] = rt * q1;
+        }
+    }
+}
+
+// The records of every row of a grid, once per problem: node rows, then z-faces.
+__global__ void __launch_bounds__(256) dg_records_kernel(DgArgs A, int rows, double* __restrict__ rec)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= rows + A.nz + 1) return;
+    const bool zr = i >= rows;
+    for (int v = 0; v < 3; ++v) dg_record(A, zr, zr ? i - rows : i, v, true, rec + (long)DG_REC * i);
+}
+
+void launch_dg_records(int k, const DgArgs& A, double* rec, hipStream_t st)
+{
+    const int rows = (k + 1) * A.nz;
+    dg_records_kernel<<<dim3((unsigned)((rows + A.nz + 1 + 255) / 256)), dim3(256), 0, st>>>(A, rows, rec);
+}
+
+// Terms at one face point along +e_D, in the face frame (component 1 the normal
+// momentum, 2 the tangential one), from both sides' traces tl, th and trace derivatives
+// nl, nh (d/d xi):
+//   Phi = H(U_lo, U_hi) (minus the background's H when BGSUB) minus, for viscous flow,
+//         the average of both sides' F_v . n plus the interior penalty on the jump of
+//         the velocity-like variables,
+//   slo, shi = the symmetric term's jump of either side, mu/2 (+-[U_c] - (U_c/rho)_side (+-[rho])),
+//         [U] = U_lo - U_hi (components 1..3).
+// At a slip wall (wlo, whi) the missing side is the inside trace mirrored.
+template <bool NS, bool BGSUB>
+__device__ __forceinline__ void dg_face(const DgArgs& A, double (&tl)[4], const double (&nl)[4], double (&th)[4],
+                                        const double (&nh)[4], const double* __restrict__ row, bool xf, bool wlo,
+                                        bool whi, double (&Phi)[4], double (&slo)[3], double (&shi)[3])
+{
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {   // slip walls: the inside trace on both sides
+        const double a = wlo ? th[c] : tl[c];
+        th[c] = whi ? tl[c] : th[c];
+        tl[c] = a;
+    }
+    const double pb = row[BR_P], irt = row[BR_IRT], mx = row[BR_MX];
+    const double Ub[4] = {row[BR_RHO], xf ? mx : 0.0, xf ? 0.0 : mx, row[BR_RT]};
+    double UL[4], UR[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        double v = 0.0;
-#pragma unroll
-        for (int j = 0; j < N1; ++j) v += es[j] * sv[c][xf ? r * N1 + j : j * N1 + r];
-        tro[c] = v;
-        Uo[c] = v + Ub[c];
+        UL[c] = tl[c] + Ub[c];
+        UR[c] = th[c] + Ub[c];
     }
-    const double po = pert_pressure(A.gas, tro[3], irz, pbz);
-    double px = po;
-    if (wall) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) Ux[c] = Uo[c];
-        if (xf) Ux[1] = -Uo[1]; else Ux[2] = -Uo[2];
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) Ux[c] = trx[c] + Ub[c];
-        px = pert_pressure(A.gas, trx[3], irz, pbz);
-    }
-    const double iro = frcp(Uo[0]), irx = frcp(Ux[0]);
-    hllc_face(A.gas, Uo, Ux, po, px, iro, irx, xf, sg, H);
+    if (wlo) UL[1] = -UL[1];
+    if (whi) UR[1] = -UR[1];
+    const double rt[2] = {tl[3], th[3]}, ir2[2] = {irt, irt}, pb2[2] = {pb, pb};
+    double pp[2];
+    pert_pressures<double, 2, false>(A.gas, rt, ir2, pb2, pp);
+    const double pL = pp[0], pR = pp[1];
+    const double irL = frcp(UL[0]), irR = frcp(UR[0]);
+    hllc_ax<double, 1>(A.gas, UL, UR, pL, pR, irL, irR, Phi);
     if constexpr (BGSUB) {
-        double Um[4], Hb[4];
+        const double* hb = row + (wlo && xf ? BR_HLO : whi && xf ? BR_HHI : BR_H);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) Um[c] = Ub[c];
-        if (wall) { if (xf) Um[1] = -Ub[1]; else Um[2] = -Ub[2]; }
-        const double irb = frcp(Ub[0]);
-        hllc_face(A.gas, Ub, Um, pbz, pbz, irb, irb, xf, sg, Hb);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) H[c] -= Hb[c];
+        for (int c = 0; c < 4; ++c) Phi[c] -= hb[c];
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) { fl[c] = -H[c]; sy[c] = 0.0; }
+    for (int c = 0; c < 3; ++c) slo[c] = shi[c] = 0.0;
     if constexpr (NS) {
-        if (!wall) {
-            // F_v(U, G) . n of a Cartesian face involves only the normal derivative
-            // G_n (the tangential part enters multiplied by 0): own side from the
-            // element's values, other side from the neighbour's trace derivative,
+        if (!(wlo || whi)) {
+            // F_v(U, G) . n of a Cartesian face involves only the normal derivative (the
+            // tangential part enters multiplied by 0): both sides' trace derivatives,
             // plus the background's z-derivative on z-faces
             const double gs = xf ? A.rdx2 : A.rdz2;
-            double Gno[4], Gnx[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double sn = 0.0;
-#pragma unroll
-                for (int j = 0; j < N1; ++j) sn += ds[j] * sv[c][xf ? r * N1 + j : j * N1 + r];
-                const double db = xf ? 0.0 : dUb[c];
-                Gno[c] = gs * sn + db;
-                Gnx[c] = gs * dnx[c] + db;
-            }
             const double eta = xf ? A.eta_x : A.eta_z;
-            const double Dl0 = tro[0] - trx[0];
-            const double irm = frcp(0.5 * (Uo[0] + Ux[0]));
+            const double gb[4] = {xf ? 0.0 : row[BR_DRHO], 0.0, xf ? 0.0 : row[BR_DMX], xf ? 0.0 : row[BR_DRT]};
+            const double GL0 = gs * nl[0] + gb[0], GR0 = gs * nh[0] + gb[0];
+            const double D0 = tl[0] - th[0];
+            const double irm = frcp(0.5 * (UL[0] + UR[0]));
 #pragma unroll
             for (int c = 1; c < 4; ++c) {
-                const double ro = Uo[c] * iro;
-                const double Fo = sg * A.mu * (Gno[c] - ro * Gno[0]);
-                const double Fxx = sg * A.mu * (Gnx[c] - Ux[c] * irx * Gnx[0]);
-                const double Dlc = tro[c] - trx[c];
-                const double pen = eta * A.mu * (Dlc - (0.5 * (Uo[c] + Ux[c]) * irm) * Dl0);
-                fl[c] += 0.5 * (Fo + Fxx) - pen;
-                sy[c] = 0.5 * A.mu * (Dlc - ro * Dl0);
+                const double rl = UL[c] * irL, rr = UR[c] * irR;
+                const double fo = (gs * nl[c] + gb[c]) - rl * GL0;
+                const double fx = (gs * nh[c] + gb[c]) - rr * GR0;
+                const double Dc = tl[c] - th[c];
+                const double pen = eta * (Dc - (0.5 * (UL[c] + UR[c]) * irm) * D0);
+                Phi[c] -= A.mu * (0.5 * (fo + fx) - pen);
+                slo[c - 1] = 0.5 * A.mu * (Dc - rl * D0);
+                shi[c - 1] = -0.5 * A.mu * (Dc - rr * D0);
             }
         }
     }
 }
 
-// k = 3: at most 128 VGPRs (four waves per SIMD) and 20 KB of LDS per 128-thread
-// work-group, so that eight work-groups fit per CU; lower degrees at most 168.
-template <int N1, bool NS, int MODE, bool RG>
-__global__ void __launch_bounds__(DgShape<N1>::NTH, N1 == 4 ? 4 : 3)
+// The line of nodes n0, n0 + 1, ... (x) or n0, n0 + N1, ... (z) of the four components,
+// in the line's frame (component 1 the momentum along it).  xd is wave-uniform.
+template <int N1>
+__device__ __forceinline__ void dg_line(const double* __restrict__ U, long N, unsigned n0, bool xd, bool ok,
+                                        double (&v)[4][N1])
+{
+    if (xd) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < N1; ++j) v[c][j] = ok ? ld(U + c * N, n0 + j) : 0.0;
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < N1; ++j) v[c][j] = ok ? ld(U + (c == 1 ? 2 : c == 2 ? 1 : c) * N, n0 + j * N1) : 0.0;
+    }
+}
+
+// REC: the background records are read from the problem's table (A.rec); without one
+// (the allocation-free residual) wave 0 evaluates the tile's.
+template <int N1, bool NS, int MODE, bool RG, bool REC>
+__global__ void __launch_bounds__(DgShape<N1>::NTH, MODE == 3 ? 2 : 3)
 dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict__ U, const double* __restrict__ Y,
           const double* __restrict__ Ubar, double* __restrict__ out, const double* __restrict__ yn2p,
           const double* __restrict__ ut2p, int eps_mode, double adt, Red red, long ms, ExStage rk, int ycount)
@@ -181,254 +223,346 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         red = mbr(red, ms);
         if (!RG) lin0 = mbr(lin0, ms);   // a ragged member's pointer is its own
     }
-    constexpr int NP = DgShape<N1>::NP, NTH = DgShape<N1>::NTH, EPB = DgShape<N1>::EPB, FPE = DgShape<N1>::FPE;
-    const int nbm = (int)((A.ne + EPB - 1) / EPB);   // this member's work-groups
-    if ((int)blockIdx.x >= nbm || (RG && sits_out(mt))) {   // beyond a smaller member, or one that sits out
-        if (MODE == 2 && threadIdx.x == 0) red.partials[block_linear()] = 0.0;
+    using S = DgShape<N1>;
+    constexpr int NP = S::NP, NTH = S::NTH, HALF = S::HALF, EPB = S::EPB, TEX = S::TEX, TEZ = S::TEZ;
+    constexpr int NXF = S::NXF, NZF = S::NZF, NSLOT = S::NSLOT, ROWS = S::ROWS;
+    constexpr bool BGSUB = MODE != 3 && MODE != 5;
+    constexpr int BRN = BGSUB ? 22 : 8;               // doubles of a background record
+    constexpr int TRN = NS ? 8 : 4;                   // trace (and its derivative)
+    constexpr int FLN = NS ? 7 : 4;                   // face terms the low side's element needs
+    constexpr int FCN = NS ? 10 : 4;                  // stored face terms of the linearization state
+    const int nx = A.nx, nz = A.nz;
+    const int ntx = (nx + TEX - 1) / TEX, ntiles = dg_tiles<N1>(nx, nz);   // this member's work-groups
+    if ((int)blockIdx.x >= ntiles || (RG && sits_out(mt))) {   // beyond a smaller member, or one that sits out
+        if (MODE == 2 && red.partials && threadIdx.x == 0) red.partials[block_linear()] = 0.0;
         return;
     }
-    constexpr bool OUTL = MODE != 5;   // the fluxes stay in LDS for the contraction
-    __shared__ double sS[EPB][4][NP];
-    __shared__ double sFx[OUTL ? EPB : 1][4][NP], sFz[OUTL ? EPB : 1][4][NP];
-    __shared__ double sFc[OUTL ? EPB : 1][4][N1][4];
-    __shared__ double sSy[OUTL && NS ? EPB : 1][4][N1][4];
+    // traces [component][slot] of the low sides, later the z-lines' result [component][node]
+    constexpr int NTR = TRN * NSLOT, NLZ = MODE == 5 ? 1 : 4 * EPB * NP;
+    __shared__ double sT[NTR > NLZ ? NTR : NLZ];
+    __shared__ double sF[FLN * (NTH + NXF + NZF)];   // face terms [term][own low face, then the tile's high faces]
+    __shared__ double sB[S::NROW][BRN];
+    constexpr int NFS = NTH + NXF + NZF;
 
     const int t = threadIdx.x;
-    const int le = t / NP, nd = t - le * NP;
-    const bool act = le < EPB;
-    const long eb = (long)xcd_tile(blockIdx.x, nbm) * EPB;   // XCD-contiguous element ranges
-    const long e = eb + le;
-    const bool valid = act && e < A.ne;
-    const int ez = valid ? (int)(e / A.nx) : 0;
-    const long N = A.ne * NP, NF = A.ne * FPE;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool xd = wv < HALF / 64;                       // x- or z-line (wave-uniform)
+    const int tile = (int)xcd_tile(blockIdx.x, ntiles);   // XCD-contiguous ranges of tiles
+    const int ex0 = (tile % ntx) * TEX, ez0 = (tile / ntx) * TEZ;
+    const int wx = min(TEX, nx - ex0), wz = min(TEZ, nz - ez0);   // elements of this tile
+    const bool per = A.bc == 1;
+    const int lt = xd ? t : t - HALF;
+    const int le = lt / N1, ln = lt - le * N1;            // element of the tile, line
+    const int lz = le / TEX, lx = le - lz * TEX;
+    const bool valid = le < EPB && lx < wx && lz < wz;
+    const long N = A.ne * NP;
+    double* const vol0 = lin0;              // [8][N]
+    double* const face0 = lin0 + 8 * N;     // [FCN][NF]
+    const unsigned NF = (unsigned)(N1 * ((nx + 1) * (long)nz + nx * (long)(nz + 1)));
+    const unsigned e0 = (unsigned)(((ez0 + lz) * (long)nx + ex0 + lx) * NP);
+    const unsigned n0 = e0 + (xd ? ln * N1 : ln);         // first node of the line
     const RefTab& R = A.R;
-    double* vol0 = lin0;              // [8][N]
-    double* face0 = lin0 + 8 * N;     // [8][NF]
 
-    const unsigned no = (unsigned)(e * NP + nd);   // the thread's node in component arrays
-    // ---- A: stage the element values (JVP: of U' + eps y).  The loads are issued
-    // before the step size is known (it depends on a device scalar). ----
-    double u0[4], y0[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        u0[c] = valid ? ld(U + c * N, no) : 0.0;
-        y0[c] = (MODE == 3 && valid) ? ld(Y + c * N, no) : 0.0;
+    // ---- every global load first ----
+    double s[4][N1], y[4][N1];
+    dg_line<N1>(U, N, n0, xd, valid, s);
+    if constexpr (MODE == 3) dg_line<N1>(Y, N, n0, xd, valid, y);
+    // the neighbour elements' lines outside the tile: of bottom and top (z) in wave 2, of
+    // left and right (x) in wave 3; at a wall none
+    double h[4][N1], hy[4][N1];
+    int hslot = -1;
+    bool hhigh = false;
+    if (wv >= 2) {
+        const int l = t & 63, n = wv == 2 ? NZF : NXF;
+        const bool up = l >= n;                           // top or right neighbours: their low end
+        const int q = up ? l - n : l, g = q / N1, r = q - g * N1;
+        int ex = wv == 2 ? ex0 + g : (up ? ex0 + wx : ex0 - 1);
+        const int ez = wv == 2 ? (up ? ez0 + wz : ez0 - 1) : ez0 + g;
+        bool ok = l < 2 * n && g < (wv == 2 ? wx : wz);
+        if (wv == 2) ok = ok && ez >= 0 && ez < nz;
+        else if (ex < 0 || ex >= nx) { ex = up ? 0 : nx - 1; ok = ok && per; }
+        if (ok) hslot = NTH + (wv == 2 ? 2 * NXF : 0) + l;
+        hhigh = !up;
+        const unsigned o = (unsigned)((ez * (long)nx + ex) * NP) + (wv == 2 ? r : r * N1);
+        dg_line<N1>(U, N, o, wv != 2, ok, h);
+        if constexpr (MODE == 3) dg_line<N1>(Y, N, o, wv != 2, ok, hy);
     }
-    // the node row's background and (JVP) the stored volume fluxes of U', with the loads above
-    const int a = nd % N1, b = nd / N1;
-    double Ub[4], dUb[4], v0x[4], v0z[4];
-    double pbz = 0.0, irz = 0.0;
-    {
-        const int zi = ez * N1 + b;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) { Ub[c] = act ? A.bg_node[zi * 4 + c] : 0.0; dUb[c] = act ? A.dbg_node[zi * 4 + c] : 0.0; }
-        pbz = act ? A.pb_node[zi] : 0.0;
-        irz = act ? A.irt_node[zi] : 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            v0x[c] = (MODE == 3 && valid) ? ld(vol0 + c * N, no) : 0.0;
-            v0z[c] = (MODE == 3 && valid) ? ld(vol0 + (4 + c) * N, no) : 0.0;
-        }
+    if constexpr (REC) {
+        const double* rn = A.rec + (long)DG_REC * ez0 * N1;                  // node rows
+        const double* rf = A.rec + (long)DG_REC * ((long)nz * N1 + ez0);     // z-faces
+        for (int i = t; i < BRN * wz * N1; i += NTH) sB[i / BRN][i % BRN] = rn[(i / BRN) * DG_REC + i % BRN];
+        for (int i = t; i < BRN * (wz + 1); i += NTH) sB[ROWS + i / BRN][i % BRN] = rf[(i / BRN) * DG_REC + i % BRN];
+    } else if (t < (BGSUB ? 3 * ROWS : ROWS) + TEZ + 1) {
+        // one lane per row; a node row's three flux cases on three lanes
+        const bool zr = t < TEZ + 1;   // a z-face row
+        const int q = t - (TEZ + 1), v = zr ? 0 : q / ROWS, r = zr ? t : q - v * ROWS;
+        if (zr ? r <= wz : r < wz * N1)
+            dg_record(A, zr, zr ? ez0 + r : ez0 * N1 + r, v, BGSUB, sB[zr ? ROWS + r : r]);
     }
     double eps = 0.0;
     if constexpr (MODE == 3) {
         const double ut2 = eps_mode == 0 ? 0.0 : ut2p[0];
         // ||y||^2: yn2p[0], or with ycount > 0 the sum of the ycount block partials at yn2p
-        // (fixed order; sFx serves as scratch until phase B writes it)
         double yn2;
-        if (ycount > 0) {
-            double a = 0.0;
-            for (int i = t; i < ycount; i += NTH) a += yn2p[i];
-            a = wave_sum(a);
-            double* scr = &sFx[0][0][0];
-            if ((t & 63) == 0) scr[t >> 6] = a;
-            __syncthreads();
-            yn2 = scr[0];
-#pragma unroll
-            for (int w = 1; w < NTH / 64; ++w) yn2 += scr[w];
-        } else {
-            yn2 = yn2p[0];
-        }
+        if (ycount > 0) yn2 = sum_partials<NTH>(yn2p, ycount);
+        else yn2 = yn2p[0];
         if (!(yn2 > 0.0)) {   // y = 0: the product is 0 (uniform over the grid)
-            if (valid)
-                for (int c = 0; c < 4; ++c) st(out + c * N, no, 0.0);
+            if (valid && xd)
+                for (int c = 0; c < 4; ++c)
+                    for (int j = 0; j < N1; ++j) st(out + c * N, n0 + j, 0.0);
             return;
         }
         eps = uniform(eps_mode == 0 ? FdEps<double>::sqrt_eps / sqrt(yn2)
                                     : FdEps<double>::sqrt_eps * sqrt(ut2) / sqrt(yn2));
-    }
-    if (act) {
+        // the line of U' + eps y
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sS[le][c][nd] = MODE == 3 ? u0[c] + eps * y0[c] : u0[c];
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < N1; ++j) {
+                s[c][j] = s[c][j] + eps * y[c][j];
+                if (wv >= 2) h[c][j] = h[c][j] + eps * hy[c][j];
+            }
+    }
+
+    // ---- T: traces ----
+    double tlo[4], dlo[4];   // at the line's low end
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        double a = 0.0, b = 0.0, da = 0.0, db = 0.0;
+#pragma unroll
+        for (int j = 0; j < N1; ++j) {
+            a += R.em[j] * s[c][j];
+            b += R.ep[j] * s[c][j];
+            if constexpr (NS) {
+                da += R.dm[j] * s[c][j];
+                db += R.dp[j] * s[c][j];
+            }
+        }
+        tlo[c] = a;
+        dlo[c] = da;
+        sT[c * NSLOT + t] = b;
+        if constexpr (NS) sT[(4 + c) * NSLOT + t] = db;
+    }
+    if (hslot >= 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            double a = 0.0, da = 0.0;
+#pragma unroll
+            for (int j = 0; j < N1; ++j) {
+                a += (hhigh ? R.ep[j] : R.em[j]) * h[c][j];
+                if constexpr (NS) da += (hhigh ? R.dp[j] : R.dm[j]) * h[c][j];
+            }
+            sT[c * NSLOT + hslot] = a;
+            if constexpr (NS) sT[(4 + c) * NSLOT + hslot] = da;
+        }
     }
     __syncthreads();
 
-    // ---- B: volume fluxes (JVP: minus those of U') ----
-    if (act) {
-        double Ut[4], Fx[4], Fz[4];
+    // ---- F: the face point at the line's low end, and wave 1 the tile's high faces ----
+    auto traces = [&](int slot, double (&tr)[4], double (&dn)[4]) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) Ut[c] = sS[le][c][nd] + Ub[c];
-        const double pt = pert_pressure(A.gas, sS[le][3][nd], irz, pbz);
-        conv_flux_xz(Ut, pt, Fx, Fz);
-        if constexpr (MODE != 3 && MODE != 5) {
-            double Bx[4], Bz[4];
-            conv_flux_xz(Ub, pbz, Bx, Bz);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { Fx[c] -= Bx[c]; Fz[c] -= Bz[c]; }
+        for (int c = 0; c < 4; ++c) {
+            tr[c] = sT[c * NSLOT + slot];
+            if constexpr (NS) dn[c] = sT[(4 + c) * NSLOT + slot];
         }
-        if constexpr (NS) {
-            // F_v^x and F_v^z: mu (G_c - (U_c/rho) G_rho) with the x- and z-derivatives
-            double Gx[4], Gz[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double sx = 0.0, sz = 0.0;
-#pragma unroll
-                for (int j = 0; j < N1; ++j) {
-                    sx += R.D[a][j] * sS[le][c][b * N1 + j];
-                    sz += R.D[b][j] * sS[le][c][j * N1 + a];
-                }
-                Gx[c] = A.rdx2 * sx;
-                Gz[c] = A.rdz2 * sz + dUb[c];
-            }
-            const double ir = frcp(Ut[0]);
-#pragma unroll
-            for (int c = 1; c < 4; ++c) {
-                const double rc = Ut[c] * ir;
-                Fx[c] -= A.mu * (Gx[c] - rc * Gx[0]);
-                Fz[c] -= A.mu * (Gz[c] - rc * Gz[0]);
-            }
-        }
+    };
+    // face point of the grid, gx / gz: the face's low-side element is the one before it
+    auto stored_at = [&](bool xf, int gx, int gz, int r) {
+        return xf ? (unsigned)(((long)gz * (nx + 1) + gx) * N1 + r)
+                  : (unsigned)(((long)(nx + 1) * nz + (long)gz * nx + gx) * N1 + r);
+    };
+    auto finish = [&](double (&Phi)[4], double (&slo)[3], double (&shi)[3], unsigned fo, int slot) {
         if constexpr (MODE == 5) {
-            if (valid) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) { st(vol0 + c * N, no, Fx[c]); st(vol0 + (4 + c) * N, no, Fz[c]); }
+            for (int c = 0; c < 4; ++c) st(face0 + (long)c * NF, fo, Phi[c]);
+            if constexpr (NS) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    st(face0 + (long)(4 + c) * NF, fo, slo[c]);
+                    st(face0 + (long)(7 + c) * NF, fo, shi[c]);
+                }
             }
         } else {
             if constexpr (MODE == 3) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    Fx[c] = Fx[c] - v0x[c];
-                    Fz[c] = Fz[c] - v0z[c];
+                for (int c = 0; c < 4; ++c) Phi[c] -= ld(face0 + (long)c * NF, fo);
+                if constexpr (NS) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        slo[c] -= ld(face0 + (long)(4 + c) * NF, fo);
+                        shi[c] -= ld(face0 + (long)(7 + c) * NF, fo);
+                    }
                 }
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) { sFx[le][c][nd] = Fx[c]; sFz[le][c][nd] = Fz[c]; }
+            for (int c = 0; c < 4; ++c) sF[c * NFS + slot] = Phi[c];
+            if constexpr (NS) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sF[(4 + c) * NFS + slot] = slo[c];
+            }
+        }
+    };
+    double Phi[4], shi[3];   // of the line's low face
+    if (valid) {
+        const bool first = xd ? lx == 0 : lz == 0;   // the low neighbour is outside the tile
+        const int slot = first ? NTH + (xd ? lz * N1 + ln : 2 * NXF + lx * N1 + ln) : t - (xd ? N1 : TEX * N1);
+        double tl[4], nl[4], slo[3];
+        traces(slot, tl, nl);
+        const bool wlo = first && (xd ? ex0 == 0 && !per : ez0 == 0);
+        dg_face<NS, BGSUB>(A, tl, nl, tlo, dlo, sB[xd ? lz * N1 + ln : ROWS + lz], xd, wlo, false, Phi, slo, shi);
+        finish(Phi, slo, shi, stored_at(xd, ex0 + lx, ez0 + lz, ln), t);
+    }
+    if (wv == 1) {
+        const int l = t & 63;
+        const bool xf = l < NXF;
+        const int q = xf ? l : l - NXF, g = q / N1, r = q - g * N1;
+        if (l < NXF + NZF && g < (xf ? wz : wx)) {
+            double tl[4], nl[4], th[4], nh[4], Ph[4], sl[3], sh[3];
+            traces(xf ? (g * TEX + wx - 1) * N1 + r : HALF + ((wz - 1) * TEX + g) * N1 + r, tl, nl);
+            traces(NTH + (xf ? NXF : 2 * NXF + NZF) + q, th, nh);
+            const bool end = xf ? ex0 + wx == nx : ez0 + wz == nz;
+            dg_face<NS, BGSUB>(A, tl, nl, th, nh, sB[xf ? g * N1 + r : ROWS + wz], xf, false, end && !(xf && per), Ph, sl,
+                               sh);
+            // (mode 5: a face between tiles is stored by the tile of its high side)
+            if (MODE != 5 || end)
+                finish(Ph, sl, sh, xf ? stored_at(true, ex0 + wx, ez0 + g, r) : stored_at(false, ex0 + g, ez0 + wz, r),
+                       NTH + l);
         }
     }
 
-    // ---- C: face terms (JVP: minus those of U'); the neighbour element's trace
-    // and normal derivative at the face point come straight from global memory
-    // into registers.  With k = 3 (16 face points and 16 threads per element)
-    // wave 0 takes the faces with outward normal -e_x / -e_z of all eight
-    // elements and wave 1 those with +e_x / +e_z, so that the side, and with it
-    // every trace weight, is uniform per wave. ----
-    auto face_point = [&](int fle, int f, int r, bool pos) {
-        const int fe = (int)eb + fle;
-        const bool fvalid = fe < A.ne;
-        const int fez = fvalid ? fe / A.nx : 0;
-        const int fex = fvalid ? fe - fez * A.nx : 0;
-        const int nb = fvalid ? face_nb(f, fex, fez, A.nx, A.nz, A.bc) : -1;
-        const bool xf = f < 2;
-        const unsigned q = (unsigned)fe * FPE + f * N1 + r;
-        double fl[4], sy[4];
-        dg_face<N1, NS, MODE != 3 && MODE != 5, MODE == 3>(A, sS[fle], U, Y, eps, N, nb, xf, pos, r, fez, fl, sy);
-        if constexpr (MODE == 5) {
-            if (fvalid) {
+    // ---- V: volume fluxes along the line and their contraction, over the line's scale
+    // 2/dx or 2/dz and the node's mass: M^-1 L_h along this direction ----
+    double L[4][N1];
+    const double r2 = xd ? A.rdx2 : A.rdz2;
+    if (valid) {
+        const long vo = xd ? 0 : 4 * N;   // this direction's stored volume fluxes
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < N1; ++j) L[c][j] = 0.0;
+        double pt[N1], ir1[N1], pb1[N1];
+#pragma unroll
+        for (int q = 0; q < N1; ++q) {
+            const double* row = sB[lz * N1 + (xd ? ln : q)];
+            ir1[q] = row[BR_IRT];
+            pb1[q] = row[BR_P];
+        }
+        pert_pressures<double, N1, false>(A.gas, s[3], ir1, pb1, pt);
+#pragma unroll
+        for (int q = 0; q < N1; ++q) {
+            const double* row = sB[lz * N1 + (xd ? ln : q)];
+            const double mx = row[BR_MX], pb = pb1[q];
+            const double Ut[4] = {s[0][q] + row[BR_RHO], s[1][q] + (xd ? mx : 0.0), s[2][q] + (xd ? 0.0 : mx),
+                                  s[3][q] + row[BR_RT]};
+            const double ir = frcp(Ut[0]);
+            const double qn = Ut[1] * ir;
+            double F[4] = {Ut[1], Ut[1] * qn + pt[q], Ut[2] * qn, Ut[3] * qn};
+            if constexpr (BGSUB) {
+                // the background's flux: along z only its pressure
+                F[0] -= xd ? mx : 0.0;
+                F[1] -= xd ? row[BR_F1] : pb;
+                F[3] -= xd ? row[BR_F3] : 0.0;
+            }
+            if constexpr (NS) {
+                // mu (G_c - (U_c/rho) G_rho) with the derivative along the line
+                double G[4];
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    st(face0 + c * NF, q, fl[c]);
-                    if constexpr (NS) st(face0 + (4 + c) * NF, q, sy[c]);
+                    double a = 0.0;
+#pragma unroll
+                    for (int j = 0; j < N1; ++j) a += R.D[q][j] * s[c][j];
+                    G[c] = r2 * a;
                 }
-            }
-            return;
-        }
-        if constexpr (MODE == 3) {
+                if (!xd) {
+                    G[0] += row[BR_DRHO];
+                    G[2] += row[BR_DMX];
+                    G[3] += row[BR_DRT];
+                }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                fl[c] = fl[c] - (fvalid ? ld(face0 + c * NF, q) : 0.0);
-                if constexpr (NS) sy[c] = sy[c] - (fvalid ? ld(face0 + (4 + c) * NF, q) : 0.0);
+                for (int c = 1; c < 4; ++c) F[c] -= A.mu * (G[c] - (Ut[c] * ir) * G[0]);
             }
-        }
-        const double W = R.w[r] * (xf ? A.dz : A.dx) * 0.5;
+            const unsigned no = xd ? n0 + q : n0 + q * N1;
+            if constexpr (MODE == 5) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            sFc[fle][f][r][c] = W * fl[c];
-            if constexpr (NS) sSy[fle][f][r][c] = W * sy[c];
-        }
-    };
-    if constexpr (N1 == 4 && NTH == 128) {
-        const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // wave index, uniform
-        const int l = t & 63, qf = l & 7;
-        face_point(l >> 3, ((qf >> 2) << 1) | w, qf & 3, w != 0);
-    } else if (act) {
-        for (int fp = nd; fp < FPE; fp += NP) {
-            const int f = fp / N1;
-            face_point(le, f, fp - f * N1, (f & 1) != 0);
+                for (int c = 0; c < 4; ++c) st(vol0 + vo + c * N, no, F[c]);
+            }
+            if constexpr (MODE == 3) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) F[c] -= ld(vol0 + vo + c * N, no);
+            }
+            if constexpr (MODE != 5) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int a = 0; a < N1; ++a) L[c][a] += R.lt[a][q] * F[c];
+            }
         }
     }
     if constexpr (MODE == 5) return;
-    // U'_rho and y are read again for the output (not held through the face phase);
-    // the loads are issued before the barrier so that their latency overlaps it
-    double y_d[4] = {0.0, 0.0, 0.0, 0.0}, urho_d = 0.0;
-    if constexpr (MODE == 3) {
-        if (valid) {
-            const double* Ud = opaque(U);
-            const double* Yd = opaque(Y);
-            urho_d = ld(Ud, no);
+    __syncthreads();
+    if (valid) {
+        // face terms of the line's ends: the high face's from LDS
+        const bool last = xd ? lx == wx - 1 : lz == wz - 1;
+        const int slot = last ? NTH + (xd ? lz * N1 + ln : NXF + lx * N1 + ln) : t + (xd ? N1 : TEX * N1);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) y_d[c] = ld(Yd + c * N, no);
+        for (int c = 0; c < 4; ++c) {
+            const double ph = sF[c * NFS + slot];
+#pragma unroll
+            for (int a = 0; a < N1; ++a) L[c][a] += R.lt[a][4] * Phi[c] - R.lt[a][5] * ph;
+            if constexpr (NS) {
+                if (c > 0) {
+                    const double lo = r2 * shi[c - 1], hi = r2 * sF[(3 + c) * NFS + slot];
+#pragma unroll
+                    for (int a = 0; a < N1; ++a) L[c][a] += R.lt[a][7] * hi - R.lt[a][6] * lo;
+                }
+            }
+        }
+        if (!xd) {   // (the traces are read no more)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int a = 0; a < N1; ++a)
+                    sT[((c == 1 ? 2 : c == 2 ? 1 : c) * EPB + le) * NP + a * N1 + ln] = r2 * L[c][a];
         }
     }
     __syncthreads();
 
-    // ---- D: contraction, lifting and output ----
+    // ---- D: both directions, gravity and the output, by the x-lines ----
     double nrm = 0.0;
-    if (valid) {
-        const double m = R.w[a] * R.w[b] * A.J, im = frcp(m);
+    if (xd && valid) {
         const double sc = MODE == 3 ? adt / eps : 0.0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double sx = 0.0, sz = 0.0;
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int q = 0; q < N1; ++q) sx += R.w[q] * R.D[q][a] * sFx[le][c][b * N1 + q];
-#pragma unroll
-            for (int q = 0; q < N1; ++q) sz += R.w[q] * R.D[q][b] * sFz[le][c][q * N1 + a];
-            double L = A.J * (A.rdx2 * R.w[b] * sx + A.rdz2 * R.w[a] * sz);
-            L += sFc[le][0][b][c] * R.em[a] + sFc[le][1][b][c] * R.ep[a];
-            L += sFc[le][2][a][c] * R.em[b] + sFc[le][3][a][c] * R.ep[b];
-            if constexpr (NS) {
-                L += sSy[le][0][b][c] * (-A.rdx2 * R.dm[a]) + sSy[le][1][b][c] * (A.rdx2 * R.dp[a]);
-                L += sSy[le][2][a][c] * (-A.rdz2 * R.dm[b]) + sSy[le][3][a][c] * (A.rdz2 * R.dp[b]);
+            for (int a = 0; a < N1; ++a) {
+                const unsigned no = n0 + a;
+                double v = r2 * L[c][a] + sT[(c * EPB + le) * NP + ln * N1 + a];
+                if (c == 2) {
+                    // gravity; JVP: of (U' + eps y)_rho - U'_rho
+                    if constexpr (MODE == 3) v -= A.g * (s[0][a] - ld(U, no));
+                    else v -= A.g * s[0][a];
+                }
+                if constexpr (MODE == 0) st(out + c * N, no, v * (R.w[a] * R.w[ln] * A.J));
+                else if constexpr (MODE == 1) st(out + c * N, no, v);
+                else if constexpr (MODE == 2) {
+                    const double G = s[c][a] - adt * v - ld(Ubar + c * N, no);
+                    st(out + c * N, no, G);
+                    nrm += G * G;
+                } else if constexpr (MODE == 3) {
+                    st(out + c * N, no, y[c][a] - sc * v);
+                } else {   // explicit Runge-Kutta stage
+                    const double base = rk.a0 != 0.0 ? rk.a0 * ld(Ubar + c * N, no) : 0.0;
+                    st(out + c * N, no, base + rk.a1 * s[c][a] + rk.c * v);
+                }
             }
-            if (c == 2) {
-                // gravity; JVP: of (U' + eps y)_rho - U'_rho
-                if constexpr (MODE == 3) L += m * (-A.g * (sS[le][0][nd] - urho_d));
-                else L += m * (-A.g * sS[le][0][nd]);
-            }
-            if constexpr (MODE == 0) st(out + c * N, no, L);
-            else if constexpr (MODE == 1) st(out + c * N, no, L * im);
-            else if constexpr (MODE == 2) {
-                const double G = sS[le][c][nd] - adt * (L * im) - ld(Ubar + c * N, no);
-                st(out + c * N, no, G);
-                nrm += G * G;
-            } else if constexpr (MODE == 3) {
-                st(out + c * N, no, y_d[c] - sc * (L * im));
-            } else {   // explicit Runge-Kutta stage
-                const double base = rk.a0 != 0.0 ? rk.a0 * ld(Ubar + c * N, no) : 0.0;
-                st(out + c * N, no, base + rk.a1 * sS[le][c][nd] + rk.c * (L * im));
-            }
-            // one component at a time: keeps the LDS reads of the next component
-            // from being hoisted into this one (register pressure)
-            __builtin_amdgcn_sched_barrier(0);
-        }
     }
-    if constexpr (MODE == 2) put_partial<NTH>(red, nrm);
+    if constexpr (MODE == 2)
+        if (red.partials) put_partial<NTH>(red, nrm);
 }
 
-int dg_grid(int k, long ne)
+int dg_grid(int k, int nx, int nz)
 {
-    const int epb = k == 1 ? DgShape<2>::EPB : k == 2 ? DgShape<3>::EPB : DgShape<4>::EPB;
-    return (int)((ne + epb - 1) / epb);
+    return k == 1 ? dg_tiles<2>(nx, nz) : k == 2 ? dg_tiles<3>(nx, nz) : dg_tiles<4>(nx, nz);
 }
 
 template <int N1, bool NS, bool RG>
@@ -441,30 +575,26 @@ static void launch_dg_n(int mode, const DgArgs& A0, const double* U, const doubl
     A.rdz2 = 2.0 / A.dz;
     A.eta_x = A.c_ip * (double)(N1 * N1) / A.dx;
     A.eta_z = A.c_ip * (double)(N1 * N1) / A.dz;
-    const dim3 grid(dg_grid(N1 - 1, A.ne), 1, mb.n), block(DgShape<N1>::NTH);
-    if (mode == 2 && red.out) {
-        timed_launch(dg_kernel<N1, NS, 2, RG>, grid, block, st, A, mb.tab, U, Y, Ubar, out, yn2, ut2, eps_mode, adt,
-                     red, mb.ms, ex, 0);
-        launch_finalize(red.partials, (int)grid.x, 1, red.out, st, Gate{}, mb);
-        return;
-    }
-#define JFMG_DG_CASE(M)                                                                                            \
-    case M:                                                                                                        \
-        timed_launch(dg_kernel<N1, NS, M, RG>, grid, block, st, A, mb.tab, U, Y, Ubar, out, yn2, ut2, eps_mode, adt, \
-                     red, mb.ms, ex, 0);                                                                           \
-        break;
+    const dim3 grid(dg_tiles<N1>(A.nx, A.nz), 1, mb.n), block(DgShape<N1>::NTH);
+    auto launch = [&](auto kernel, int yc) {
+        timed_launch(kernel, grid, block, st, A, mb.tab, U, Y, Ubar, out, yn2, ut2, eps_mode, adt, red, mb.ms, ex, yc);
+    };
     switch (mode) {
-        JFMG_DG_CASE(0)
-        JFMG_DG_CASE(1)
-        JFMG_DG_CASE(2)
-        JFMG_DG_CASE(4)
-        JFMG_DG_CASE(5)
-    default:
-        timed_launch(dg_kernel<N1, NS, 3, RG>, grid, block, st, A, mb.tab, U, Y, Ubar, out, yn2, ut2, eps_mode, adt,
-                     red, mb.ms, ex, ycount);
+    case 0: launch(dg_kernel<N1, NS, 0, RG, true>, 0); break;
+    case 1: launch(dg_kernel<N1, NS, 1, RG, true>, 0); break;
+    case 2:
+        if constexpr (!RG) {
+            if (!A.rec) launch(dg_kernel<N1, NS, 2, false, false>, 0);
+            else launch(dg_kernel<N1, NS, 2, false, true>, 0);
+        } else {
+            launch(dg_kernel<N1, NS, 2, true, true>, 0);
+        }
+        if (red.out) launch_finalize(red.partials, (int)grid.x, 1, red.out, st, Gate{}, mb);
         break;
+    case 4: launch(dg_kernel<N1, NS, 4, RG, true>, 0); break;
+    case 5: launch(dg_kernel<N1, NS, 5, RG, true>, 0); break;
+    default: launch(dg_kernel<N1, NS, 3, RG, true>, ycount); break;
     }
-#undef JFMG_DG_CASE
 }
 
 template <int N1>

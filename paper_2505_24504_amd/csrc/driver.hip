@@ -166,6 +166,13 @@ bool reftab(int k, int transfer, RefTab& R)
     B.eval(1.0, R.ep);
     B.deriv(-1.0, R.dm);
     B.deriv(1.0, R.dp);
+    for (int a = 0; a < n; ++a) {
+        for (int q = 0; q < n; ++q) R.lt[a][q] = R.w[q] * R.D[q][a] / R.w[a];
+        R.lt[a][4] = R.em[a] / R.w[a];
+        R.lt[a][5] = R.ep[a] / R.w[a];
+        R.lt[a][6] = R.dm[a] / R.w[a];
+        R.lt[a][7] = R.dp[a] / R.w[a];
+    }
     if (transfer == 1) {
         const double h = 2.0 / n;
         for (int a = 0; a < n; ++a) {
@@ -315,6 +322,7 @@ struct jfmg_problem {
     size_t fvp;
     int xcnt[MAXLEV][3];
     double* bg_node; double* dbg_node; double* th_node; double* bg_face; double* dbg_face;
+    double* rec;                        // background records of the DG kernel
     double* pb_node; double* pb_face;   // [.][2]: background pressure, 1/(rho theta)
     double *Un, *Ubar, *Uk, *G, *delta, *tmp1, *tmp2, *Ulin, *lin0;
     double *V, *Z;
@@ -501,9 +509,10 @@ size_t layout(const jfmg_config& c, char* base, F&& bind)
     bind("dbg_face", cv.take((size_t)(c.nz + 1) * 4 * 8), 0);
     bind("pb_node", cv.take((size_t)c.nz * n1 * 2 * 8), 0);
     bind("pb_face", cv.take((size_t)(c.nz + 1) * 2 * 8), 0);
+    bind("rec", cv.take((size_t)((n1 + 1) * (size_t)c.nz + 1) * DG_REC * 8), 0);
     const char* dgn[] = {"Un", "Ubar", "Uk", "G", "delta", "tmp1", "tmp2", "Ulin"};
     for (const char* s : dgn) bind(s, cv.take((size_t)N * 8), 0);
-    bind("lin0", cv.take((size_t)lin_doubles(c.k, ne) * 8), 0);
+    bind("lin0", cv.take((size_t)lin_doubles(c.k, c.physics == 1, c.nx, c.nz) * 8), 0);
     bind("V", cv.take((size_t)N * 8 * (m + 1)), 0);
     bind("Z", cv.take((size_t)N * 8 * m), 0);
     int nxl = n1 * c.nx, nzl = n1 * c.nz;
@@ -638,7 +647,7 @@ template <typename T> jfmg_status linearize_t(jfmg_problem* p, const double* U, 
     launch_norm2_total(p->cfg.k, p->A, p->Ulin, red_at(p, S_UTOT), st, p->mb);
     {
         // the volume fluxes and face terms of U' that every product with this state differences against
-        ProfScope ps(p, JFMG_K_DG_LINEARIZE, (double)p->N * 8 + 8.0 * lin_doubles(p->cfg.k, p->ne));
+        ProfScope ps(p, JFMG_K_DG_LINEARIZE, (double)p->N * 8 + 8.0 * lin_doubles(p->cfg.k, p->cfg.physics == 1, p->cfg.nx, p->cfg.nz));
         launch_dg(p->cfg.k, p->cfg.physics == 1, 5, p->A, p->Ulin, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0.0,
                   no_red(), st, p->mb);
     }
@@ -902,7 +911,7 @@ jfmg_status mg_apply_t(jfmg_problem* p, double* r, double* z, int zslot, const N
 // block partials in p->partials
 void jvp_slot(jfmg_problem* p, const double* y, double* out, int yslot, int ycount = 0)
 {
-    ProfScope ps(p, JFMG_K_DG_JVP, 3.0 * p->N * 8 + 8.0 * lin_doubles(p->cfg.k, p->ne));
+    ProfScope ps(p, JFMG_K_DG_JVP, 3.0 * p->N * 8 + 8.0 * lin_doubles(p->cfg.k, p->cfg.physics == 1, p->cfg.nx, p->cfg.nz));
     launch_dg(p->cfg.k, p->cfg.physics == 1, 3, p->A, p->Ulin, y, nullptr, out,
               ycount > 0 ? p->partials : p->scal + yslot, p->scal + S_UTOT, p->cfg.fd_eps_mode, p->adt, no_red(),
               p->st, p->mb, ExStage{}, ycount);
@@ -1627,6 +1636,7 @@ DgArgs dg_args_of(const jfmg_problem* p, const jfmg_config& c, size_t off)
     A.bg_face = at(p->bg_face); A.dbg_face = at(p->dbg_face);
     A.pb_node = at(p->pb_node); A.irt_node = at(p->pb_node + (size_t)c.nz * p->n1);
     A.pb_face = at(p->pb_face); A.irt_face = at(p->pb_face + (c.nz + 1));
+    A.rec = at(p->rec);
     A.R = p->R;
     A.lin0 = (double*)((char*)p->lin0 + off);
     return A;
@@ -1709,6 +1719,7 @@ jfmg_status create_impl(const jfmg_config* cfgs, int n, bool ragged, void* works
         else if (nm == "dbg_face") p->dbg_face = (double*)ptr;
         else if (nm == "pb_node") p->pb_node = (double*)ptr;
         else if (nm == "pb_face") p->pb_face = (double*)ptr;
+        else if (nm == "rec") p->rec = (double*)ptr;
         else if (nm == "Un") p->Un = (double*)ptr;
         else if (nm == "Ubar") p->Ubar = (double*)ptr;
         else if (nm == "Uk") p->Uk = (double*)ptr;
@@ -1753,6 +1764,10 @@ jfmg_status create_impl(const jfmg_config* cfgs, int n, bool ragged, void* works
     if (!ragged) {
         // one set of tables (member 0's; the members of a lock-step batch share them)
         e = upload_tables(p, *cfg, 0, keep);
+        if (!e) {
+            launch_dg_records(cfg->k, dg_args_of(p, *cfg, 0), p->rec, st);
+            e = hipGetLastError();
+        }
     } else {
         tab.resize(members);
         long off = 0;
@@ -1763,6 +1778,10 @@ jfmg_status create_impl(const jfmg_config* cfgs, int n, bool ragged, void* works
             MemberArgs& M = tab[m];
             std::memset(&M, 0, sizeof(M));
             M.dg = dg_args_of(p, c, ob);
+            if (!e) {
+                launch_dg_records(c.k, M.dg, (double*)((char*)p->rec + ob), st);
+                e = hipGetLastError();
+            }
             M.N = 4L * c.nx * c.nz * p->np;
             M.live = 1;
             for (int l = 0; l < p->nlev; ++l) {

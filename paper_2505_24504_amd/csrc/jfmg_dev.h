@@ -173,6 +173,53 @@ template <typename T> __device__ __forceinline__ T pert_dpress(const Gas<T>& G, 
     return pb * f;
 }
 
+// pert_pressure (DEV false) or pert_dpress (DEV true) of n states at once: the same
+// values, with one copy of the general power for all of them (the unrolled callers
+// would each carry it several times, most of their code size, while states that far
+// from the background are rare).
+template <typename T, int n, bool DEV>
+__device__ __forceinline__ void pert_pressures(const Gas<T>& G, const T (&rt1)[n], const T (&irtb)[n], const T (&pb)[n],
+                                               T (&out)[n])
+{
+    constexpr bool F32 = std::is_same_v<T, float>;
+    constexpr int n0 = F32 ? 4 : 6, n1 = F32 ? 7 : GAS_NCOEF, last = DEV ? 1 : 0;
+    bool far = false;
+#pragma unroll
+    for (int q = 0; q < n; ++q) {
+        const T s = rt1[q] * irtb[q];
+        const T as = dabs<T>(s);
+        T f = G.cg[n0 - 1];
+#pragma unroll
+        for (int k = n0 - 2; k >= last; --k) f = f * s + G.cg[k];
+        if (!(as <= T(1.0 / 1024.0))) {
+            f = G.cg[n1 - 1];
+#pragma unroll
+            for (int k = n1 - 2; k >= last; --k) f = f * s + G.cg[k];
+        }
+        if constexpr (DEV) f = f * s;
+        far = far || !(as <= T(0.05));
+        out[q] = pb[q] * f;
+    }
+    if (far) {
+#pragma unroll 1
+        for (int q = 0; q < n; ++q) {
+            T s = rt1[0] * irtb[0], p = pb[0];
+#pragma unroll
+            for (int r = 1; r < n; ++r) {
+                s = q == r ? rt1[r] * irtb[r] : s;
+                p = q == r ? pb[r] : p;
+            }
+            if (!(dabs<T>(s) <= T(0.05))) {
+                T f = dpow<T>(T(1) + s, G.gamma);
+                if constexpr (DEV) f = f - T(1);
+                const T v = p * f;
+#pragma unroll
+                for (int r = 0; r < n; ++r) out[r] = q == r ? v : out[r];
+            }
+        }
+    }
+}
+
 // Convective flux F_c(U) . n for an axis-aligned unit normal (nx, nz), pressure p given.
 template <typename T>
 __device__ __forceinline__ void conv_flux(const T* U, T p, T nx, T nz, T* F)

@@ -40,6 +40,9 @@ constexpr int MAXLEV = 8;
 struct RefTab {
     double xi[MAXN1], w[MAXN1], D[MAXN1][MAXN1], em[MAXN1], ep[MAXN1], dm[MAXN1], dp[MAXN1];
     double V[MAXN1][MAXN1], Vinv[MAXN1][MAXN1], wnc[MAXN1];
+    // per node a, over its weight w_a: the derivative column w_q D_qa (q < 4), the traces
+    // l_a(-1), l_a(1) and the trace derivatives l_a'(-1), l_a'(1)
+    double lt[MAXN1][8];
 };
 
 // ---------------------------------------------------------------------------
@@ -102,6 +105,8 @@ Gas<double> gas_of(const jfmg_config& c);
 // message returned by jfmg_last_error(NULL) for calls without a problem
 void set_create_error(const std::string& msg);
 
+constexpr int DG_REC = 22;   // doubles of a background record (DgArgs::rec)
+
 // Everything a DG kernel needs about the grid, the gas and the background.
 struct DgArgs {
     long ne;
@@ -120,10 +125,15 @@ struct DgArgs {
     const double* irt_node;
     const double* pb_face;   // [nz+1]        the same at element z-faces
     const double* irt_face;
+    // records of the background rows of the DG kernel (DG_REC doubles each, node rows,
+    // then z-faces), written once per problem by launch_dg_records; null: evaluated in
+    // the kernel (the allocation-free residual)
+    const double* rec = nullptr;
     // fluxes of the linearization state U', written once per linearization (mode 5)
     // and read by every product with it (mode 3): the volume fluxes F^x, F^z per
-    // node, [8][ne (k+1)^2], then the face terms per face point of every element,
-    // [8][ne 4 (k+1)] (flux, then the symmetric term's jump); lin_doubles() long
+    // node, [8][ne (k+1)^2], then the terms of every face point of the grid (x-faces row
+    // by row, then z-faces), the flux [4] and in viscous flow the symmetric term's jumps
+    // of the low and the high side, [3] each; lin_doubles() long
     double* lin0 = nullptr;
     RefTab R;
 };
@@ -201,7 +211,8 @@ struct LiveBits {
 void launch_set_live(MemberArgs* tab, int n, const LiveBits& bits, hipStream_t st);
 
 // ---- DG kernels (dg.hip) ----
-// mode 0: <psi,L>  1: M^-1 L  2: G = U - adt M^-1 L - Ubar (+ ||G||^2 into red.out)
+// mode 0: <psi,L>  1: M^-1 L  2: G = U - adt M^-1 L - Ubar (+ ||G||^2 into red.out; no norm
+// without red.partials)
 // mode 3: JVP out = Y - adt/eps M^-1 (L(U+eps Y) - L(U)), eps from the device scalars
 //         yn2 = ||Y||^2 and ut2 = ||U + Ubar||^2 (eps_mode 1)
 // mode 4: explicit Runge-Kutta stage out = ex.a0 Ubar + ex.a1 U + ex.c M^-1 L(U)
@@ -215,10 +226,15 @@ void launch_dg(int k, bool ns, int mode, const DgArgs& A, const double* U, const
                const double* Ubar, double* out, const double* yn2, const double* ut2, int eps_mode,
                double adt, Red red, hipStream_t st, const Mb& mb = Mb{}, const ExStage& ex = ExStage{},
                int ycount = 0);
-// doubles of DgArgs::lin0 for degree k and ne elements
-inline long lin_doubles(int k, long ne) { return 8 * ne * (k + 1) * (k + 1) + 8 * ne * 4 * (k + 1); }
+// doubles of DgArgs::lin0 for degree k and nx x nz elements
+inline long lin_doubles(int k, bool ns, long nx, long nz)
+{
+    return 8 * nx * nz * (k + 1) * (k + 1) + (ns ? 10 : 4) * (k + 1) * ((nx + 1) * nz + nx * (nz + 1));
+}
+// the background records of the whole grid of A into rec, DG_REC ((k+1) nz + nz + 1) doubles
+void launch_dg_records(int k, const DgArgs& A, double* rec, hipStream_t st);
 int transfer_grid(int k, long ne);
-int dg_grid(int k, long ne);
+int dg_grid(int k, int nx, int nz);   // work-groups of a DG launch
 void launch_initial_state(int k, const DgArgs& A, int shape, double amp, double xc, double zc,
                           double xr, double zr, double a, double Z, double x0, double z0,
                           double u_mean, double* U, hipStream_t st, const Mb& mb = Mb{});

@@ -37,12 +37,13 @@ struct TableParams {
 
 // Byte layout of one call inside the array (256-byte aligned regions).
 struct Layout {
-    size_t bg_node, dbg_node, th_node, bg_face, dbg_face, pb_node, pb_face, partials, end;
+    size_t bg_node, dbg_node, bg_face, dbg_face, pb_node, pb_face, partials, end;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-Layout layout_of(const jfmg_config& c)
+// norm_pass: block partials of a separate norm kernel instead of the DG kernel's
+Layout layout_of(const jfmg_config& c, bool norm_pass)
 {
     const size_t rows = (size_t)c.nz * (c.k + 1), faces = (size_t)c.nz + 1;
     Layout L;
@@ -50,12 +51,11 @@ Layout layout_of(const jfmg_config& c)
     auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
     L.bg_node = take(rows * 4 * 8);
     L.dbg_node = take(rows * 4 * 8);
-    L.th_node = take(rows * 8);
     L.bg_face = take(faces * 4 * 8);
     L.dbg_face = take(faces * 4 * 8);
     L.pb_node = take(rows * 2 * 8);
     L.pb_face = take(faces * 2 * 8);
-    L.partials = take((size_t)jfmg::dg_grid(c.k, (long)c.nx * c.nz) * 8);
+    L.partials = take((norm_pass ? 1024 : (size_t)jfmg::dg_grid(c.k, c.nx, c.nz)) * 8);
     L.end = o;
     return L;
 }
@@ -66,8 +66,8 @@ Layout layout_of(const jfmg_config& c)
 // all rows' pressures first, then all reciprocals.
 __global__ void __launch_bounds__(256)
 bg_tables_kernel(TableParams P, double* __restrict__ bg_node, double* __restrict__ dbg_node,
-                 double* __restrict__ th_node, double* __restrict__ bg_face, double* __restrict__ dbg_face,
-                 double* __restrict__ pb_node, double* __restrict__ pb_face)
+                 double* __restrict__ bg_face, double* __restrict__ dbg_face, double* __restrict__ pb_node,
+                 double* __restrict__ pb_face)
 {
     const int rows = P.c.nz * P.n1, faces = P.c.nz + 1;
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -78,7 +78,6 @@ bg_tables_kernel(TableParams P, double* __restrict__ bg_node, double* __restrict
             bg_node[i * 4 + c] = bp.U[c];
             dbg_node[i * 4 + c] = bp.dU[c];
         }
-        th_node[i] = bp.theta;
         pb_node[i] = jfmg::bg_pressure(P.c, bp.U[3]);
         pb_node[rows + i] = 1.0 / bp.U[3];
     } else if (i < rows + faces) {
@@ -129,7 +128,10 @@ extern "C" jfmg_status jfmg_stage_residual_noalloc(const jfmg_config* cfg, const
     if (s) return report(s, msg ? msg : "invalid configuration");
     if (cfg->batch > 1) return report(JFMG_EINVAL, "the allocation-free residual takes a single problem (batch 0 or 1)");
     if (!std::isfinite(alpha_dt)) return report(JFMG_EINVAL, "alpha_dt must be finite");
-    const Layout L = layout_of(*cfg);
+    // the DG kernel's block partials, or (where they do not fit the array) a norm pass over G
+    Layout L = layout_of(*cfg, false);
+    const bool norm_pass = L.end > SCRATCH_BYTES;
+    if (norm_pass) L = layout_of(*cfg, true);
     if (L.end > SCRATCH_BYTES)
         return report(JFMG_ENOMEM, "problem needs " + std::to_string(L.end) + " bytes of the " +
                                        std::to_string(SCRATCH_BYTES) + "-byte static scratch");
@@ -149,28 +151,29 @@ extern "C" jfmg_status jfmg_stage_residual_noalloc(const jfmg_config* cfg, const
     P.dz = dz;
     double* bg_node = (double*)(base + L.bg_node);
     double* dbg_node = (double*)(base + L.dbg_node);
-    double* th_node = (double*)(base + L.th_node);
     double* bg_face = (double*)(base + L.bg_face);
     double* dbg_face = (double*)(base + L.dbg_face);
     double* pb_node = (double*)(base + L.pb_node);
     double* pb_face = (double*)(base + L.pb_face);
     const int entries = cfg->nz * n1 + cfg->nz + 1;
-    bg_tables_kernel<<<dim3((entries + 255) / 256), dim3(256), 0, st>>>(P, bg_node, dbg_node, th_node, bg_face,
-                                                                        dbg_face, pb_node, pb_face);
+    bg_tables_kernel<<<dim3((entries + 255) / 256), dim3(256), 0, st>>>(P, bg_node, dbg_node, bg_face, dbg_face,
+                                                                        pb_node, pb_face);
 
     jfmg::DgArgs A;
     A.ne = (long)cfg->nx * cfg->nz;
     A.nx = cfg->nx; A.nz = cfg->nz; A.bc = cfg->bc; A.physics = cfg->physics;
     A.dx = dx; A.dz = dz; A.J = dx * dz / 4.0; A.g = cfg->g; A.mu = cfg->mu; A.c_ip = cfg->c_ip;
     A.gas = jfmg::gas_of(*cfg);
-    A.bg_node = bg_node; A.dbg_node = dbg_node; A.th_node = th_node;
+    A.bg_node = bg_node; A.dbg_node = dbg_node; A.th_node = nullptr;   // read for initial states only
     A.bg_face = bg_face; A.dbg_face = dbg_face;
     A.pb_node = pb_node; A.irt_node = pb_node + (size_t)cfg->nz * n1;
     A.pb_face = pb_face; A.irt_face = pb_face + (cfg->nz + 1);
     A.R = R;
     // G and its block partials; with norm2 the one-block finalize sums them into norm2[0]
+    const jfmg::Red red{(double*)(base + L.partials), norm2};
     jfmg::launch_dg(cfg->k, cfg->physics == 1, 2, A, U, nullptr, Ubar, G, nullptr, nullptr, 0, alpha_dt,
-                    jfmg::Red{(double*)(base + L.partials), norm2}, st);
+                    norm_pass ? jfmg::Red{nullptr, nullptr} : red, st);
+    if (norm_pass && norm2) jfmg::launch_norm2(G, 4 * A.ne * n1 * n1, red, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return report(JFMG_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
     return JFMG_OK;
