@@ -23,13 +23,16 @@
 // fluxes per node, face terms per face point) once per linearization, and each
 // product reads them back instead of evaluating a second state.
 //
-// What bounds it: FP64 issue and LDS reads on large grids, on the density current
+// What bounds it: memory latency and FP64 issue on large grids, on the density current
 // (256 x 64 elements, k = 3, one round of work-groups) the chain of its phases.  With a
 // thread per node, every face point evaluated from both sides and the background's HLLC
 // at each of them, M^-1 L_h took 705 us at 1024 x 1024 elements (viscous, k = 3) and an
 // explicit stage 15.3 us at 256 x 64 and 11.1 us at 197 x 45 (k = 2); this form takes
-// 449, 12.5 and 8.2 us with half the VALU and a third of the LDS work per node.  A
+// 438, 12.0 and 7.7 us with half the VALU and a third of the LDS work per node.  A
 // node-per-thread form with each tile face evaluated once reached 636, 13.3 and 7.9 us.
+// Six waves per work-group (the neighbours' lines and the high faces on two of their
+// own) were slower at k = 3, 18.7 against 15.2 us under counters: two such groups do
+// not fit the three wave slots per SIMD that 168 registers leave.
 #include "jfmg_internal.h"
 
 namespace jfmg {
@@ -89,7 +92,7 @@ __device__ __forceinline__ void dg_record(const DgArgs& A, bool zr, int i, int v
         if (v == 1 || (zr && i == 0)) UL[1] = -UL[1];
         if (v == 2 || (zr && i == A.nz)) UR[1] = -UR[1];
         const double ir = frcp(rho);
-        hllc_ax<double, 1>(A.gas, UL, UR, pb, pb, ir, ir, H);
+        hllc_ax<double, 1>(A.gas, UL, UR, pb, pb, pb, pb, ir, ir, H);
 #pragma unroll
         for (int c = 0; c < 4; ++c) rec[(v == 0 ? BR_H : v == 1 ? BR_HLO : BR_HHI) + c] = H[c];
         if (v == 0) {
@@ -150,36 +153,34 @@ __device__ __forceinline__ void dg_face(const DgArgs& A, double (&tl)[4], const 
     pert_pressures<double, 2, false>(A.gas, rt, ir2, pb2, pp);
     const double pL = pp[0], pR = pp[1];
     const double irL = frcp(UL[0]), irR = frcp(UR[0]);
-    hllc_ax<double, 1>(A.gas, UL, UR, pL, pR, irL, irR, Phi);
+    hllc_ax<double, 1>(A.gas, UL, UR, pL, pR, pL, pR, irL, irR, Phi);
     if constexpr (BGSUB) {
         const double* hb = row + (wlo && xf ? BR_HLO : whi && xf ? BR_HHI : BR_H);
 #pragma unroll
         for (int c = 0; c < 4; ++c) Phi[c] -= hb[c];
     }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) slo[c] = shi[c] = 0.0;
     if constexpr (NS) {
-        if (!(wlo || whi)) {
-            // F_v(U, G) . n of a Cartesian face involves only the normal derivative (the
-            // tangential part enters multiplied by 0): both sides' trace derivatives,
-            // plus the background's z-derivative on z-faces
-            const double gs = xf ? A.rdx2 : A.rdz2;
-            const double eta = xf ? A.eta_x : A.eta_z;
-            const double gb[4] = {xf ? 0.0 : row[BR_DRHO], 0.0, xf ? 0.0 : row[BR_DMX], xf ? 0.0 : row[BR_DRT]};
-            const double GL0 = gs * nl[0] + gb[0], GR0 = gs * nh[0] + gb[0];
-            const double D0 = tl[0] - th[0];
-            const double irm = frcp(0.5 * (UL[0] + UR[0]));
+        // F_v(U, G) . n of a Cartesian face involves only the normal derivative (the
+        // tangential part enters multiplied by 0): both sides' trace derivatives,
+        // plus the background's z-derivative on z-faces; none of it at walls
+        const bool wall = wlo | whi;
+        const double gs = xf ? A.rdx2 : A.rdz2;
+        const double eta = xf ? A.eta_x : A.eta_z;
+        const double gb[4] = {xf ? 0.0 : row[BR_DRHO], 0.0, xf ? 0.0 : row[BR_DMX], xf ? 0.0 : row[BR_DRT]};
+        const double GL0 = gs * nl[0] + gb[0], GR0 = gs * nh[0] + gb[0];
+        const double D0 = tl[0] - th[0];
+        const double irm = frcp(0.5 * (UL[0] + UR[0]));
 #pragma unroll
-            for (int c = 1; c < 4; ++c) {
-                const double rl = UL[c] * irL, rr = UR[c] * irR;
-                const double fo = (gs * nl[c] + gb[c]) - rl * GL0;
-                const double fx = (gs * nh[c] + gb[c]) - rr * GR0;
-                const double Dc = tl[c] - th[c];
-                const double pen = eta * (Dc - (0.5 * (UL[c] + UR[c]) * irm) * D0);
-                Phi[c] -= A.mu * (0.5 * (fo + fx) - pen);
-                slo[c - 1] = 0.5 * A.mu * (Dc - rl * D0);
-                shi[c - 1] = -0.5 * A.mu * (Dc - rr * D0);
-            }
+        for (int c = 1; c < 4; ++c) {
+            const double rl = UL[c] * irL, rr = UR[c] * irR;
+            const double fo = (gs * nl[c] + gb[c]) - rl * GL0;
+            const double fx = (gs * nh[c] + gb[c]) - rr * GR0;
+            const double Dc = tl[c] - th[c];
+            const double pen = eta * (Dc - (0.5 * (UL[c] + UR[c]) * irm) * D0);
+            const double pv = A.mu * (0.5 * (fo + fx) - pen);
+            Phi[c] -= wall ? 0.0 : pv;
+            slo[c - 1] = wall ? 0.0 : 0.5 * A.mu * (Dc - rl * D0);
+            shi[c - 1] = wall ? 0.0 : -0.5 * A.mu * (Dc - rr * D0);
         }
     }
 }

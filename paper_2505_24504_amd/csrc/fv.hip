@@ -92,10 +92,12 @@ __device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ]
         if (wallR) UR[D] = -UR[D];
         const T pb = pr[0], irb = pr[1];
         // the face's background pressure is left out of the flux (see the file comment)
-        const T dpL = pert_dpress(A.gas, wL[3], irb, pb), dpR = pert_dpress(A.gas, wR[3], irb, pb);
-        const T pL = pb + dpL, pR = pb + dpR;
+        const T rt[2] = {wL[3], wR[3]}, ir2[2] = {irb, irb}, pb2[2] = {pb, pb};
+        T dp[2];
+        pert_pressures<T, 2, true>(A.gas, rt, ir2, pb2, dp);
+        const T pL = pb + dp[0], pR = pb + dp[1];
         const T irL = frcp<T>(UL[0]), irR = frcp<T>(UR[0]);
-        hllc_ax_dp<T, D>(A.gas, UL, UR, pL, pR, dpL, dpR, irL, irR, Phi);
+        hllc_ax<T, D>(A.gas, UL, UR, pL, pR, dp[0], dp[1], irL, irR, Phi);
         if (A.physics == 1 && !wall) {
             // k = 0 diffusion: mean of mu (G_c - (U_c/rho) G_rho) over both sides, where the
             // only gradient is the background's (z-faces), minus the interior penalty

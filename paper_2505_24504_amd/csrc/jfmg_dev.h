@@ -116,89 +116,44 @@ template <typename T> __device__ __forceinline__ T frcp(T a)
 }
 
 // Equation of state of the potential-temperature form, p = p0 (R rho theta / p0)^gamma,
-// evaluated at the total state rho theta = rtb (1 + s), s = (rho theta)' / rtb, as
-// p = pb (1 + s)^gamma with the background pressure pb = p0 (R rtb / p0)^gamma.
-// (1 + s)^gamma is the binomial series in Horner form, truncated below the unit
-// roundoff for 1 < gamma <= 5/3: 6 terms for |s| <= 2^-10 (atmospheric pressure
-// perturbations; truncation <= 6e-21) and 12 for |s| <= 1/20 (<= 3e-19) in FP64,
-// 4 and 7 terms in FP32; pow beyond.  s = 0 returns pb exactly, so background and
-// perturbed evaluations agree bitwise.
-template <typename T> __device__ __forceinline__ T pert_pressure(const Gas<T>& G, T rt1, T irtb, T pb)
-{
-    constexpr bool F32 = std::is_same_v<T, float>;
-    const T s = rt1 * irtb;
-    const T as = dabs<T>(s);
-    T f;
-    if (as <= T(1.0 / 1024.0)) {
-        constexpr int n = F32 ? 4 : 6;
-        f = G.cg[n - 1];
-#pragma unroll
-        for (int k = n - 2; k >= 0; --k) f = f * s + G.cg[k];
-    } else if (as <= T(0.05)) {
-        constexpr int n = F32 ? 7 : GAS_NCOEF;
-        f = G.cg[n - 1];
-#pragma unroll
-        for (int k = n - 2; k >= 0; --k) f = f * s + G.cg[k];
-    } else {
-        f = dpow<T>(T(1) + s, G.gamma);
-    }
-    return pb * f;
-}
-
-// The pressure's deviation from the background, p - pb = pb ((1 + s)^gamma - 1): the
-// series of pert_pressure without its constant term, so that it is accurate to the
-// unit roundoff of p - pb rather than of p (FP32 FV operators, whose values enter only
+// evaluated at the total states rho theta = rtb (1 + s), s = (rho theta)' / rtb, as
+// p = pb (1 + s)^gamma with the background pressure pb = p0 (R rtb / p0)^gamma, for n
+// states at once: p (DEV false) or the deviation p - pb (DEV true: accurate to the unit
+// roundoff of p - pb rather than of p; FP32 FV operators, whose values enter only
 // differences of two evaluations, carry p - pb where the pressure enters additively).
-template <typename T> __device__ __forceinline__ T pert_dpress(const Gas<T>& G, T rt1, T irtb, T pb)
-{
-    constexpr bool F32 = std::is_same_v<T, float>;
-    const T s = rt1 * irtb;
-    const T as = dabs<T>(s);
-    T f;
-    if (as <= T(1.0 / 1024.0)) {
-        constexpr int n = F32 ? 4 : 6;
-        f = G.cg[n - 1];
-#pragma unroll
-        for (int k = n - 2; k >= 1; --k) f = f * s + G.cg[k];
-        f = f * s;
-    } else if (as <= T(0.05)) {
-        constexpr int n = F32 ? 7 : GAS_NCOEF;
-        f = G.cg[n - 1];
-#pragma unroll
-        for (int k = n - 2; k >= 1; --k) f = f * s + G.cg[k];
-        f = f * s;
-    } else {
-        f = dpow<T>(T(1) + s, G.gamma) - T(1);
-    }
-    return pb * f;
-}
-
-// pert_pressure (DEV false) or pert_dpress (DEV true) of n states at once: the same
-// values, with one copy of the general power for all of them (the unrolled callers
-// would each carry it several times, most of their code size, while states that far
-// from the background are rare).
+// (1 + s)^gamma is the binomial series, 12 terms in FP64 and 7 in FP32, truncated below
+// the unit roundoff for |s| <= 1/20 and 1 < gamma <= 5/3 (<= 3e-19 in FP64), pow
+// beyond.  It is summed as 1 + s g(s) with g in pairs (Estrin): the last step alone
+// rounds at the scale of the result, as in Horner's form, but four operations deep
+// instead of eleven, and without a branch on |s| that would cut the flux evaluations
+// around it in pieces (a face point of the DG kernel spent 1100 of its 4000 cycles in
+// the branched Horner form).  s = 0 returns pb (0) exactly, so background and perturbed
+// evaluations agree bitwise.  The general power is one copy for all n states, as a rare
+// branch after them.
 template <typename T, int n, bool DEV>
 __device__ __forceinline__ void pert_pressures(const Gas<T>& G, const T (&rt1)[n], const T (&irtb)[n], const T (&pb)[n],
                                                T (&out)[n])
 {
-    constexpr bool F32 = std::is_same_v<T, float>;
-    constexpr int n0 = F32 ? 4 : 6, n1 = F32 ? 7 : GAS_NCOEF, last = DEV ? 1 : 0;
     bool far = false;
 #pragma unroll
     for (int q = 0; q < n; ++q) {
         const T s = rt1[q] * irtb[q];
-        const T as = dabs<T>(s);
-        T f = G.cg[n0 - 1];
-#pragma unroll
-        for (int k = n0 - 2; k >= last; --k) f = f * s + G.cg[k];
-        if (!(as <= T(1.0 / 1024.0))) {
-            f = G.cg[n1 - 1];
-#pragma unroll
-            for (int k = n1 - 2; k >= last; --k) f = f * s + G.cg[k];
+        const T* c = G.cg;
+        const T s2 = s * s;
+        const T s4 = s2 * s2;
+        T g;
+        if constexpr (std::is_same_v<T, float>) {
+            g = (c[1] + c[2] * s) + (c[3] + c[4] * s) * s2 + (c[5] + c[6] * s) * s4;
+        } else {
+            static_assert(GAS_NCOEF == 12, "series length");
+            const T lo = (c[1] + c[2] * s) + (c[3] + c[4] * s) * s2;
+            const T mi = (c[5] + c[6] * s) + (c[7] + c[8] * s) * s2;
+            const T hi = (c[9] + c[10] * s) + c[11] * s2;
+            g = lo + (mi + hi * s4) * s4;
         }
-        if constexpr (DEV) f = f * s;
-        far = far || !(as <= T(0.05));
-        out[q] = pb[q] * f;
+        if constexpr (DEV) out[q] = pb[q] * (g * s);
+        else out[q] = pb[q] * (T(1) + g * s);
+        far = far || !(dabs<T>(s) <= T(0.05));
     }
     if (far) {
 #pragma unroll 1
@@ -220,85 +175,22 @@ __device__ __forceinline__ void pert_pressures(const Gas<T>& G, const T (&rt1)[n
     }
 }
 
-// Convective flux F_c(U) . n for an axis-aligned unit normal (nx, nz), pressure p given.
-template <typename T>
-__device__ __forceinline__ void conv_flux(const T* U, T p, T nx, T nz, T* F)
-{
-    const T ir = frcp<T>(U[0]);
-    const T q = (U[1] * nx + U[2] * nz) * ir;
-    F[0] = U[1] * nx + U[2] * nz;
-    F[1] = U[1] * q + p * nx;
-    F[2] = U[2] * q + p * nz;
-    F[3] = U[3] * q;
-}
-
-// Both Cartesian convective fluxes F_c^x(U) and F_c^z(U) (pressure given) with one
-// reciprocal of rho; the same numbers as conv_flux with (1, 0) and (0, 1).
-template <typename T>
-__device__ __forceinline__ void conv_flux_xz(const T* U, T p, T* Fx, T* Fz)
-{
-    const T ir = frcp<T>(U[0]);
-    const T u = U[1] * ir, w = U[2] * ir;
-    Fx[0] = U[1];
-    Fx[1] = U[1] * u + p;
-    Fx[2] = U[2] * u;
-    Fx[3] = U[3] * u;
-    Fz[0] = U[2];
-    Fz[1] = U[1] * w;
-    Fz[2] = U[2] * w + p;
-    Fz[3] = U[3] * w;
-}
-
-// HLLC flux (Toro) with Davis wave speeds S_L = min(q_L - c_L, q_R - c_R),
-// S_R = max(q_L + c_L, q_R + c_R); star flux in the S*-factored form
-// (S*(S_K U_K - F_K) + S_K p*_K D*) / (S_K - S*), p*_K = p_K + rho_K (S_K - q_K)(S* - q_K).
-// Pressures of both states are given.
-template <typename T>
-__device__ __forceinline__ void hllc(const Gas<T>& G, const T* UL, const T* UR, T pL, T pR, T nx, T nz, T* F)
-{
-    const T rL = UL[0], rR = UR[0];
-    const T irL = frcp<T>(rL), irR = frcp<T>(rR);
-    const T qL = (UL[1] * nx + UL[2] * nz) * irL, qR = (UR[1] * nx + UR[2] * nz) * irR;
-    const T cL = dsqrt<T>(G.gamma * pL * irL), cR = dsqrt<T>(G.gamma * pR * irR);
-    const T SL = fmin(qL - cL, qR - cR);
-    const T SR = fmax(qL + cL, qR + cR);
-    if (SL >= T(0)) {
-        F[0] = UL[1] * nx + UL[2] * nz;
-        F[1] = UL[1] * qL + pL * nx;
-        F[2] = UL[2] * qL + pL * nz;
-        F[3] = UL[3] * qL;
-        return;
-    }
-    const T Ss = (pR - pL + rL * qL * (SL - qL) - rR * qR * (SR - qR)) * frcp<T>(rL * (SL - qL) - rR * (SR - qR));
-    const T* UK;
-    T SK, rK, qK, pK;
-    if (Ss >= T(0)) { UK = UL; SK = SL; rK = rL; qK = qL; pK = pL; }
-    else if (SR > T(0)) { UK = UR; SK = SR; rK = rR; qK = qR; pK = pR; }
-    else {
-        F[0] = UR[1] * nx + UR[2] * nz;
-        F[1] = UR[1] * qR + pR * nx;
-        F[2] = UR[2] * qR + pR * nz;
-        F[3] = UR[3] * qR;
-        return;
-    }
-    const T FK0 = UK[1] * nx + UK[2] * nz;
-    const T FK1 = UK[1] * qK + pK * nx;
-    const T FK2 = UK[2] * qK + pK * nz;
-    const T FK3 = UK[3] * qK;
-    const T pst = pK + rK * (SK - qK) * (Ss - qK);
-    const T iden = frcp<T>(SK - Ss);
-    F[0] = (Ss * (SK * UK[0] - FK0)) * iden;
-    F[1] = (Ss * (SK * UK[1] - FK1) + SK * pst * nx) * iden;
-    F[2] = (Ss * (SK * UK[2] - FK2) + SK * pst * nz) * iden;
-    F[3] = (Ss * (SK * UK[3] - FK3)) * iden;
-}
-
-// The same HLLC flux for the normal +e_D of a Cartesian face (D = 1: x, D = 2: z),
-// with 1/rho of both states given (the callers reuse them).  A face with normal
-// -e_D is the mirror case, H(a, b; -e) = -H(b, a; +e), so every Cartesian face
-// (slip walls included, via a mirrored ghost state) needs only this form.
+// HLLC flux (Toro) for the normal +e_D of a Cartesian face (D = 1: x, D = 2: z), Davis
+// wave speeds S_L = min(q_L - c_L, q_R - c_R), S_R = max(q_L + c_L, q_R + c_R); star flux
+// in the S*-factored form (S*(S_K U_K - F_K) + S_K p*_K e_D) / (S_K - S*),
+// p*_K = p_K + rho_K (S_K - q_K)(S* - q_K).  1/rho of both states is given (the callers
+// reuse it).  pL, pR set the sound speeds; dpL, dpR enter wherever the pressure is added
+// (the physical fluxes, the star pressure, p_R - p_L): the full pressures for the flux
+// F, or p - pb with a background pressure pb shared by both sides for F - pb e_D (the
+// star flux is affine in the pressure with weight one).
+// A face with normal -e_D is the mirror case, H(a, b; -e) = -H(b, a; +e), so every
+// Cartesian face (slip walls included, via a mirrored ghost state) needs only this form.
+// Without branches: the supersonic cases take the physical flux of the side that the
+// star flux is built on, so that one basic block holds the face and its long dependency
+// chain overlaps the work around it.
 template <typename T, int D>
-__device__ __forceinline__ void hllc_ax(const Gas<T>& G, const T* UL, const T* UR, T pL, T pR, T irL, T irR, T* F)
+__device__ __forceinline__ void hllc_ax(const Gas<T>& G, const T* UL, const T* UR, T pL, T pR, T dpL, T dpR, T irL,
+                                        T irR, T* F)
 {
     constexpr int E = 3 - D;   // tangential momentum
     const T rL = UL[0], rR = UR[0];
@@ -306,106 +198,23 @@ __device__ __forceinline__ void hllc_ax(const Gas<T>& G, const T* UL, const T* U
     const T cL = psqrt<T>(G.gamma * pL * irL), cR = psqrt<T>(G.gamma * pR * irR);
     const T SL = fmin(qL - cL, qR - cR);
     const T SR = fmax(qL + cL, qR + cR);
-    if (SL >= T(0)) {
-        F[0] = UL[D];
-        F[D] = UL[D] * qL + pL;
-        F[E] = UL[E] * qL;
-        F[3] = UL[3] * qL;
-        return;
-    }
-    if (SR <= T(0)) {
-        F[0] = UR[D];
-        F[D] = UR[D] * qR + pR;
-        F[E] = UR[E] * qR;
-        F[3] = UR[3] * qR;
-        return;
-    }
-    const T Ss = (pR - pL + rL * qL * (SL - qL) - rR * qR * (SR - qR)) * frcp<T>(rL * (SL - qL) - rR * (SR - qR));
-    const bool lk = Ss >= T(0);
-    const T SK = lk ? SL : SR, rK = lk ? rL : rR, qK = lk ? qL : qR, pK = lk ? pL : pR;
-    const T uD = lk ? UL[D] : UR[D], uE = lk ? UL[E] : UR[E], u3 = lk ? UL[3] : UR[3];
-    const T pst = pK + rK * (SK - qK) * (Ss - qK);
-    const T iden = frcp<T>(SK - Ss);
-    F[0] = (Ss * (SK * rK - uD)) * iden;
-    F[D] = (Ss * (SK * uD - (uD * qK + pK)) + SK * pst) * iden;
-    F[E] = (Ss * (SK * uE - uE * qK)) * iden;
-    F[3] = (Ss * (SK * u3 - u3 * qK)) * iden;
-}
-
-// HLLC flux F . n on a Cartesian face whose normal n = side e_D (side = +-1) has
-// its axis chosen per thread (xf: D = 1, else D = 2), so that the lanes of a wave
-// working on x- and z-faces take one path: both states are rotated into the face
-// frame (normal momentum side U_D, tangential U_E), the one-dimensional form above
-// is evaluated there and its normal-momentum component rotated back (F_D = side
-// times it).  Multiplication by +-1 and the component swap are exact.
-template <typename T>
-__device__ __forceinline__ void hllc_face(const Gas<T>& G, const T* UL, const T* UR, T pL, T pR, T irL, T irR,
-                                          bool xf, T side, T* F)
-{
-    const T a[4] = {UL[0], side * (xf ? UL[1] : UL[2]), xf ? UL[2] : UL[1], UL[3]};
-    const T b[4] = {UR[0], side * (xf ? UR[1] : UR[2]), xf ? UR[2] : UR[1], UR[3]};
-    T Fn[4];
-    hllc_ax<T, 1>(G, a, b, pL, pR, irL, irR, Fn);
-    const T fd = side * Fn[1];
-    F[0] = Fn[0];
-    F[1] = xf ? fd : Fn[2];
-    F[2] = xf ? Fn[2] : fd;
-    F[3] = Fn[3];
-}
-
-// The same HLLC flux less pb e_D (pb: the background pressure of the face, the same on
-// both sides): p (full) sets the sound speeds, dp = p - pb enters wherever the pressure
-// is added (the physical fluxes, the star pressure, p_R - p_L).  Algebraically
-// F - pb e_D, since the star flux (S*(S_K U_K - F_K) + S_K p*_K e_D) / (S_K - S*) is
-// affine in the pressure with weight one.
-template <typename T, int D>
-__device__ __forceinline__ void hllc_ax_dp(const Gas<T>& G, const T* UL, const T* UR, T pL, T pR, T dpL, T dpR, T irL,
-                                           T irR, T* F)
-{
-    constexpr int E = 3 - D;   // tangential momentum
-    const T rL = UL[0], rR = UR[0];
-    const T qL = UL[D] * irL, qR = UR[D] * irR;
-    const T cL = psqrt<T>(G.gamma * pL * irL), cR = psqrt<T>(G.gamma * pR * irR);
-    const T SL = fmin(qL - cL, qR - cR);
-    const T SR = fmax(qL + cL, qR + cR);
-    if (SL >= T(0)) {
-        F[0] = UL[D];
-        F[D] = UL[D] * qL + dpL;
-        F[E] = UL[E] * qL;
-        F[3] = UL[3] * qL;
-        return;
-    }
-    if (SR <= T(0)) {
-        F[0] = UR[D];
-        F[D] = UR[D] * qR + dpR;
-        F[E] = UR[E] * qR;
-        F[3] = UR[3] * qR;
-        return;
-    }
     const T Ss = (dpR - dpL + rL * qL * (SL - qL) - rR * qR * (SR - qR)) * frcp<T>(rL * (SL - qL) - rR * (SR - qR));
-    const bool lk = Ss >= T(0);
+    const bool supL = SL >= T(0), supR = SR <= T(0);
+    const bool lk = supL | (!supR & (Ss >= T(0)));
     const T SK = lk ? SL : SR, rK = lk ? rL : rR, qK = lk ? qL : qR, dpK = lk ? dpL : dpR;
     const T uD = lk ? UL[D] : UR[D], uE = lk ? UL[E] : UR[E], u3 = lk ? UL[3] : UR[3];
+    const T FD = uD * qK + dpK, FE = uE * qK, F3 = u3 * qK;   // the physical flux (first component: uD)
     const T pst = dpK + rK * (SK - qK) * (Ss - qK);
     const T iden = frcp<T>(SK - Ss);
-    F[0] = (Ss * (SK * rK - uD)) * iden;
-    F[D] = (Ss * (SK * uD - (uD * qK + dpK)) + SK * pst) * iden;
-    F[E] = (Ss * (SK * uE - uE * qK)) * iden;
-    F[3] = (Ss * (SK * u3 - u3 * qK)) * iden;
-}
-
-// Viscous flux F_v(U, G) . n = mu rho grad(U_c / rho) . n written with the
-// conserved-variable gradient G = (Gx, Gz): mu (G_c - (U_c/rho) G_rho), c = 1..3.
-template <typename T>
-__device__ __forceinline__ void visc_flux(T mu, const T* U, const T* Gx, const T* Gz, T nx, T nz, T* F)
-{
-    F[0] = T(0);
-    const T ir = frcp<T>(U[0]);
-#pragma unroll
-    for (int c = 1; c < 4; ++c) {
-        T r = U[c] * ir;
-        F[c] = mu * ((Gx[c] - r * Gx[0]) * nx + (Gz[c] - r * Gz[0]) * nz);
-    }
+    const T G0 = (Ss * (SK * rK - uD)) * iden;
+    const T GD = (Ss * (SK * uD - FD) + SK * pst) * iden;
+    const T GE = (Ss * (SK * uE - FE)) * iden;
+    const T G3 = (Ss * (SK * u3 - F3)) * iden;
+    const bool sup = supL | supR;
+    F[0] = sup ? uD : G0;
+    F[D] = sup ? FD : GD;
+    F[E] = sup ? FE : GE;
+    F[3] = sup ? F3 : G3;
 }
 
 // ---------------------------------------------------------------------------
