@@ -218,14 +218,32 @@ __device__ __forceinline__ void hllc_ax(const Gas<T>& G, const T* UL, const T* U
 }
 
 // ---------------------------------------------------------------------------
-// Reductions.  Wave64 butterfly, then waves combined by thread 0 in wave order.
+// Reductions, in a fixed order everywhere: the wave, then the waves in their order.
 // ---------------------------------------------------------------------------
 
+// Value of another lane by data-parallel primitives (VALU moves; a shuffle goes through
+// LDS, 120 cycles a step): control CTRL over the rows of ROWS, 0 where no lane is read.
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_move(double v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0u, (unsigned)b, CTRL, ROWS, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(b >> 32), CTRL, ROWS, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// Sum over the wave's 64 lanes, in every lane (scalar registers).  All lanes must take
+// part.  Inclusive sums in each row of 16 lanes (shifts by 1, 2, 4, 8), then of the rows
+// (lane 15 of rows 0 and 2 to rows 1 and 3, lane 31 to rows 2 and 3): lane 63 has all.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_move<0x111, 0xf>(v);
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    v += dpp_move<0x142, 0xa>(v);
+    v += dpp_move<0x143, 0xc>(v);
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, 63), hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), 63);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 __device__ __forceinline__ double wave_max(double v)
 {
@@ -242,6 +260,7 @@ template <int NTH> __device__ __forceinline__ double block_sum(double v, double*
     __syncthreads();
     double s = 0.0;
     if (threadIdx.x == 0)
+#pragma unroll
         for (int i = 0; i < NTH / 64; ++i) s += sh[i];
     __syncthreads();
     return s;
@@ -285,8 +304,15 @@ __device__ __forceinline__ unsigned xcd_tile(unsigned w, unsigned nb)
 template <int NTH> __device__ __forceinline__ void put_partial(const Red& r, double v)
 {
     __shared__ double sh[NTH / 64];
-    const double s = block_sum<NTH>(v, sh);
-    if (threadIdx.x == 0) r.partials[block_linear()] = s;
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < NTH / 64; ++i) s += sh[i];
+        r.partials[block_linear()] = s;
+    }
 }
 
 // Lock-step batches: member m of a batched problem lives m * ms bytes after
@@ -298,17 +324,20 @@ template <typename P> __device__ __forceinline__ P* mbr(P* p, long ms)
 }
 __device__ __forceinline__ Red mbr(Red r, long ms) { return Red{mbr(r.partials, ms), mbr(r.out, ms)}; }
 
-// deterministic sum of n partials, returned to every thread of the block
+// deterministic sum of n partials, returned to every thread of the block; once per kernel
+// (the waves' sums stay in LDS)
 template <int NTH> __device__ __forceinline__ double sum_partials(const double* p, int n)
 {
     __shared__ double sh[NTH / 64];
-    __shared__ double res;
     double a = 0.0;
     for (int i = threadIdx.x; i < n; i += NTH) a += p[i];
-    a = block_sum<NTH>(a, sh);
-    if (threadIdx.x == 0) res = a;
+    a = wave_sum(a);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
     __syncthreads();
-    return res;
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < NTH / 64; ++i) s += sh[i];
+    return s;
 }
 
 }  // namespace jfmg

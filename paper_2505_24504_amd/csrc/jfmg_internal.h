@@ -343,7 +343,7 @@ struct Gate {
     int nv = 0;
     double tau2 = 0.0;
 };
-// every wave evaluates it with one load per lane and a butterfly sum (nv <= 64): the
+// every wave evaluates it with one load per lane and the wave's sum (nv <= 64): the
 // same fixed order, so the same value, in every wave and every kernel.  All 64 lanes
 // of the wave must call it (no divergent branch around the call).
 __device__ __forceinline__ double gate_after(const Gate& g)

@@ -90,7 +90,7 @@ void launch_norm2(const double* x, long n, Red red, hipStream_t st, const Mb& mb
 // <w, v_i> for i < nv (and <w, w> as entry nv when self is set): the entries are
 // split into groups of MAXV consecutive ones, one group per grid row (blockIdx.y),
 // so every thread keeps MAXV accumulators in registers whatever nv is (w is read
-// once per group); each wave reduces them with butterflies and one LDS exchange
+// once per group); each wave reduces them (wave_sum) and one LDS exchange
 // combines the waves (a single barrier per block); the block partials [v][block]
 // are summed by the finalize kernel.  Nothing is computed where the gate is closed.
 template <int MAXV>
@@ -182,7 +182,7 @@ void launch_multidot(const double* w, const double* V, long ld, int nv, int self
 // its publication (pub), in one launch:
 //  * gate closed (the pass is skipped): every work-group returns at once;
 //  * gate open: h is not given but formed by every work-group from the multi-dot's hnb block
-//    partials per entry at hpart (lane-strided sums and the wave's butterfly, a fixed order;
+//    partials per entry at hpart (lane-strided sums and the wave sum, a fixed order;
 //    work-group 0 stores it to hout), each work-group updates its part of w and stores its
 //    ||w||^2 partial in red; the last work-group to finish (a release fence and a counter in
 //    device memory, so no work-group waits for another) sums the partials in a fixed order into
