@@ -265,6 +265,13 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     const RefTab& R = A.R;
 
     // ---- every global load first ----
+    PartialSum<NTH> ysum;
+    double ut2 = 0.0, yn1 = 0.0;
+    if constexpr (MODE == 3) {
+        if (ycount > 0) ysum.load(yn2p, ycount);
+        else yn1 = ldv(yn2p);
+        if (eps_mode != 0) ut2 = ldv(ut2p);
+    }
     double s[4][N1], y[4][N1];
     dg_line<N1>(U, N, n0, xd, valid, s);
     if constexpr (MODE == 3) dg_line<N1>(Y, N, n0, xd, valid, y);
@@ -302,11 +309,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     }
     double eps = 0.0;
     if constexpr (MODE == 3) {
-        const double ut2 = eps_mode == 0 ? 0.0 : ut2p[0];
         // ||y||^2: yn2p[0], or with ycount > 0 the sum of the ycount block partials at yn2p
-        double yn2;
-        if (ycount > 0) yn2 = sum_partials<NTH>(yn2p, ycount);
-        else yn2 = yn2p[0];
+        const double yn2 = ycount > 0 ? ysum.sum(yn2p, ycount) : yn1;
         if (!(yn2 > 0.0)) {   // y = 0: the product is 0 (uniform over the grid)
             if (valid && xd)
                 for (int c = 0; c < 4; ++c)

@@ -284,11 +284,8 @@ struct Level {
     void* F0;
     void* buf[3];
     void* b;
-    void* bgc;
-    void* bgf;
-    void* dbgf;
-    void* pc;
-    void* pf;
+    void* rc;   // background records of the cell rows and z-faces
+    void* rf;
 };
 
 }  // namespace
@@ -520,11 +517,8 @@ size_t layout(const jfmg_config& c, char* base, F&& bind)
         const long nc = (long)nxl * nzl;
         const char* fvn[] = {"u", "F0", "x0", "x1", "x2", "b"};
         for (const char* s : fvn) bind(s, cv.take((size_t)4 * nc * ts), l);
-        bind("bgc", cv.take((size_t)nzl * 4 * ts), l);
-        bind("bgf", cv.take((size_t)(nzl + 1) * 4 * ts), l);
-        bind("dbgf", cv.take((size_t)(nzl + 1) * 4 * ts), l);
-        bind("pc", cv.take((size_t)nzl * 2 * ts), l);
-        bind("pf", cv.take((size_t)(nzl + 1) * 2 * ts), l);
+        bind("rc", cv.take((size_t)nzl * 6 * ts), l);
+        bind("rf", cv.take((size_t)(nzl + 1) * 10 * ts), l);
         nxl /= 2;
         nzl /= 2;
     }
@@ -629,8 +623,7 @@ template <typename T> FvArgs<T> fv_args(const jfmg_problem* p, int l)
     A.nxl = L.nx; A.nzl = L.nz; A.bc = p->cfg.bc; A.physics = p->cfg.physics; A.nc = L.nc;
     A.hx = (T)L.hx; A.hz = (T)L.hz; A.area = (T)(L.hx * L.hz); A.iarea = (T)(1.0 / (L.hx * L.hz)); A.g = (T)p->cfg.g; A.mu = (T)p->cfg.mu;
     A.gas = make_gas<T>(p->cfg);
-    A.bgc = (const T*)L.bgc; A.bgf = (const T*)L.bgf; A.dbgf = (const T*)L.dbgf;
-    A.pc = (const T*)L.pc; A.pf = (const T*)L.pf;
+    A.rc = (const T*)L.rc; A.rf = (const T*)L.rf;
     A.tile = L.tile;
     A.lev = l;
     return A;
@@ -1598,23 +1591,23 @@ hipError_t upload_tables(jfmg_problem* p, const jfmg_config& c, size_t off, std:
     for (int l = 0; l < p->nlev && !e; ++l, nzl /= 2) {
         const Level& L = p->lev[l];
         const double hz = (c.z1 - c.z0) / nzl;
-        std::vector<double> c4((size_t)nzl * 4), f4((size_t)(nzl + 1) * 4), df4(f4.size());
-        std::vector<double> pc2((size_t)nzl * 2), pf2((size_t)(nzl + 1) * 2);
+        std::vector<double> rc((size_t)nzl * 6), rf((size_t)(nzl + 1) * 10);
         for (int J = 0; J < nzl; ++J) {
             const BgPoint bp = background_at(c, c.z0 + (J + 0.5) * hz);
-            for (int k = 0; k < 4; ++k) c4[J * 4 + k] = bp.U[k];
-            pc2[2 * J] = bg_pressure(c, bp.U[3]);
-            pc2[2 * J + 1] = 1.0 / bp.U[3];
+            double* r = &rc[6 * (size_t)J];
+            for (int k = 0; k < 4; ++k) r[k] = bp.U[k];
+            r[4] = bg_pressure(c, bp.U[3]);
+            r[5] = 1.0 / bp.U[3];
         }
         for (int J = 0; J <= nzl; ++J) {
             const BgPoint bp = background_at(c, c.z0 + J * hz);
-            for (int k = 0; k < 4; ++k) { f4[J * 4 + k] = bp.U[k]; df4[J * 4 + k] = bp.dU[k]; }
-            pf2[2 * J] = bg_pressure(c, bp.U[3]);
-            pf2[2 * J + 1] = 1.0 / bp.U[3];
+            double* r = &rf[10 * (size_t)J];
+            for (int k = 0; k < 4; ++k) { r[k] = bp.U[k]; r[6 + k] = bp.dU[k]; }
+            r[4] = bg_pressure(c, bp.U[3]);
+            r[5] = 1.0 / bp.U[3];
         }
-        const std::vector<double>* src[5] = {&c4, &f4, &df4, &pc2, &pf2};
-        void* dst[5] = {L.bgc, L.bgf, L.dbgf, L.pc, L.pf};
-        for (int t = 0; t < 5 && !e; ++t) e = up(dst[t], *src[t], p->prec == 32);
+        e = up(L.rc, rc, p->prec == 32);
+        e = e ? e : up(L.rf, rf, p->prec == 32);
     }
     return e;
 }
@@ -1653,7 +1646,7 @@ template <typename T> FvArgs<T> fv_args_of(const jfmg_problem* p, const jfmg_con
     const double hx = (c.x1 - c.x0) / A.nxl, hz = (c.z1 - c.z0) / A.nzl;
     A.hx = (T)hx; A.hz = (T)hz; A.area = (T)(hx * hz); A.iarea = (T)(1.0 / (hx * hz)); A.g = (T)c.g; A.mu = (T)c.mu;
     A.gas = make_gas<T>(c);
-    A.bgc = at(L.bgc); A.bgf = at(L.bgf); A.dbgf = at(L.dbgf); A.pc = at(L.pc); A.pf = at(L.pf);
+    A.rc = at(L.rc); A.rf = at(L.rf);
     A.tile = L.tile;
     A.lev = l;
     return A;
@@ -1739,11 +1732,8 @@ jfmg_status create_impl(const jfmg_config* cfgs, int n, bool ragged, void* works
             else if (nm == "x1") L.buf[1] = ptr;
             else if (nm == "x2") L.buf[2] = ptr;
             else if (nm == "b") L.b = ptr;
-            else if (nm == "bgc") L.bgc = ptr;
-            else if (nm == "bgf") L.bgf = ptr;
-            else if (nm == "dbgf") L.dbgf = ptr;
-            else if (nm == "pc") L.pc = ptr;
-            else if (nm == "pf") L.pf = ptr;
+            else if (nm == "rc") L.rc = ptr;
+            else if (nm == "rf") L.rf = ptr;
         }
     });
     // level geometry (the envelope's for a ragged batch: launch shapes)

@@ -138,7 +138,15 @@ __device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ]
 // flux, along +x or +z) exactly once, and each cell then sums its four faces:
 //   |q| f~ = -hz (Phi_{I+1/2} - Phi_{I-1/2}) - hx (Phi_{J+1/2} - Phi_{J-1/2}) - |q| g w_rho.
 // The flux through a face seen from the other cell is the same number with
-// the opposite sign (HLLC(L,R;n) = -HLLC(R,L;-n)).  Modes:
+// the opposite sign (HLLC(L,R;n) = -HLLC(R,L;-n)).
+// On the small levels a launch is one chain of latencies: of the 11300 cycles that a
+// wave of the 8 x 4 tile lived, 3600 went by before its last load was issued (scalar
+// loads of the level's scalars and of the arguments, each waited for in turn, and loads
+// behind branches) and 2200 until the partial sums were there.  The kernel now fetches
+// its arguments at once, reads the scalars by vector loads, and issues every load before
+// it waits for the first, without a branch in between (a wait behind branches is one for
+// all loads).  FGMRES iteration of 64 x 32 elements, k = 2: 135 -> 123 us; of the density
+// current 216 -> 210 us.  Modes:
 //   LIN     out = F0 = f~(u); ||u + Ubar||^2 and max(|v| + c) block partials (the level
 //           slots and dtau from them: fv_lin_finalize_kernel); with out2 also the next coarser
 //           level's state R u
@@ -164,6 +172,23 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
                TinvOut tv)
 {
     const FvArgs<T>& A = fv_of<T, RG>(Aa, mt);
+    // the arguments that the first loads need, in scalar registers at once (the compiler
+    // would fetch them one by one where they are used, a trip to the kernel arguments each)
+    gptr<T> u_ = (gptr<T>)u, F0_ = (gptr<T>)F0, xp_ = (gptr<T>)xp, x0_ = (gptr<T>)x0, b_ = (gptr<T>)b;
+    gptr<T> rc_ = (gptr<T>)A.rc, rf_ = (gptr<T>)A.rf;
+    gptr<double> xpart_ = (gptr<double>)xpart, slots_ = (gptr<double>)slots;
+    int nxl = A.nxl, nzl = A.nzl;
+    long nc = A.nc;
+    asm volatile("" : "+s"(u_), "+s"(F0_), "+s"(xp_), "+s"(x0_), "+s"(b_), "+s"(xpart_), "+s"(xcount), "+s"(slots_),
+                 "+s"(rc_), "+s"(rf_), "+s"(nxl), "+s"(nzl), "+s"(nc));
+    u = (const T*)u_;
+    F0 = (const T*)F0_;
+    xp = (const T*)xp_;
+    x0 = (const T*)x0_;
+    b = (const T*)b_;
+    xpart = (const double*)xpart_;
+    const T *const rc = (const T*)rc_, *const rf = (const T*)rf_;
+    const double* lslots = (const double*)slots_;
     if constexpr (MB) {   // member blockIdx.z of a lock-step batch
         u = mbr(u, ms);
         F0 = mbr(F0, ms);
@@ -174,7 +199,7 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
         out2 = mbr(out2, ms);
         slots2 = mbr(slots2, ms);
         xpart = mbr(xpart, ms);
-        slots = mbr(slots, ms);
+        lslots = mbr(lslots, ms);
         red = mbr(red, ms);
     }
     double* const zout = MB ? mbr(tv.z, ms) : tv.z;   // STAGE_TINV output (tv stays in the arguments)
@@ -196,8 +221,6 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     __shared__ double sVi[TI ? MAXN1 : 1][MAXN1], sWn[TI ? MAXN1 : 1];
     __shared__ double sHt[TI ? 4 : 1][TI ? TZ : 1][TI ? TX : 1];
     const int tid = threadIdx.x;
-    const long nc = A.nc;
-    const int nxl = A.nxl, nzl = A.nzl;
     // tiles of this member (a one-dimensional grid; in a ragged batch the work-groups
     // beyond a smaller member's tiles only store zero partial sums)
     const unsigned ntx = (unsigned)((nxl + TX - 1) / TX), ntiles = ntx * (unsigned)((nzl + TZ - 1) / TZ);
@@ -222,59 +245,57 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     const bool valid = tid < NCELL && I < nxl && J < nzl;
     const long q = (long)J * nxl + I;
 
-    // ---- every global load first (the level's scalars and background rows, the
-    // own-cell operands, then the halo states), or the own-cell operands only after
-    // the face loop (LATE: fewer live registers).  Nothing below waits on memory
-    // before the partial sums of ||x||^2 have arrived. ----
+    // ---- every global load first (the ||x||^2 partials, the level's scalars and
+    // background rows, the own-cell operands, then the halo states), or the own-cell
+    // operands only after the face loop (LATE: fewer live registers).  Nothing below
+    // waits on memory before the partial sums of ||x||^2 have arrived. ----
+    PartialSum<NTH> xsum;
     double s_utot = 0.0, s_iutot = 0.0, s_dtau = 0.0;
     if constexpr (PERT) {
-        s_utot = slots[LV_UTOT];
-        s_iutot = slots[LV_IUTOT];
+        xsum.load(xpart, xcount);
+        s_utot = ldv(lslots + LV_UTOT);
+        s_iutot = ldv(lslots + LV_IUTOT);
     }
-    if constexpr (STG) s_dtau = slots[LV_DTAU];
-    if constexpr (TI) {
-        if (tid < MAXN1 * MAXN1) sVi[tid / MAXN1][tid % MAXN1] = tv.Vinv[tid / MAXN1][tid % MAXN1];
-        else if (tid < MAXN1 * MAXN1 + MAXN1) sWn[tid - MAXN1 * MAXN1] = tv.wnc[tid - MAXN1 * MAXN1];
-    }
-    if constexpr (MODE == FVM_DEFECT) s_dtau = out2 ? slots2[LV_DTAU] : 0.0;
+    if constexpr (STG) s_dtau = ldv(lslots + LV_DTAU);
+    if constexpr (MODE == FVM_DEFECT) s_dtau = out2 ? ldv(slots2 + LV_DTAU) : 0.0;
     static_assert(NTH >= 6 * TZ + 10 * (TZ + 1), "background staging");
-    T bg_v = T(0);   // this thread's entry of sBc / sBf
-    if (tid < 6 * TZ) {
-        const int r = tid / 6, k = tid - 6 * r, Jr = J0 + r;
-        if (Jr < nzl) bg_v = k < 4 ? A.bgc[4 * Jr + k] : A.pc[2 * Jr + k - 4];
-    } else if (tid < 6 * TZ + 10 * (TZ + 1)) {
-        const int t2 = tid - 6 * TZ, r = t2 / 10, k = t2 - 10 * r, Jr = J0 + r;
-        if (Jr <= nzl) bg_v = k < 4 ? A.bgf[4 * Jr + k] : k < 6 ? A.pf[2 * Jr + k - 4] : A.dbgf[4 * Jr + k - 6];
-    }
+    // this thread's entry of sBc / sBf: the tile's rows are contiguous in the level's records
+    const bool bg_c = tid < 6 * TZ;
+    const int bg_i = bg_c ? tid : tid - 6 * TZ;
+    const bool bg_ok = bg_c ? bg_i < 6 * (nzl - J0) : bg_i < 10 * min(TZ + 1, nzl + 1 - J0);
+    const T* const bg_p = bg_c ? rc + 6L * J0 : rf + 10L * J0;
+    const T bg_v = bg_p[bg_ok ? bg_i : 0];
     T own_x[4] = {T(0), T(0), T(0), T(0)}, own_f0[4] = {T(0), T(0), T(0), T(0)};
     T own_b[4] = {T(0), T(0), T(0), T(0)}, own_x0[4] = {T(0), T(0), T(0), T(0)};
     // STAGE_PC: the finer level's four children of the cell, read with the own-cell
     // operands (before any of them is written)
     T own_xf[4][4] = {};
+    // (threads without a cell read cell 0: loads behind a branch would make the wait for
+    // the partial sums one for all loads)
     auto load_own = [&]() {
-        if (valid) {
-            if constexpr (MODE == FVM_STAGE_PC)
-                if (!fzero) {
-                    const long nxf = 2L * nxl, ncf = 4 * nc;
-                    const long q00 = (long)(2 * J) * nxf + 2 * I, q10 = q00 + nxf;
+        const long qo = valid ? q : 0;
+        if constexpr (MODE == FVM_STAGE_PC)
+            if (!fzero) {
+                const long nxf = 2L * nxl, ncf = 4 * nc;
+                const long q00 = valid ? (long)(2 * J) * nxf + 2 * I : 0, q10 = q00 + nxf;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const T* xf = out2 + c * ncf;
-                        own_xf[c][0] = xf[q00]; own_xf[c][1] = xf[q00 + 1];
-                        own_xf[c][2] = xf[q10]; own_xf[c][3] = xf[q10 + 1];
-                    }
+                for (int c = 0; c < 4; ++c) {
+                    const T* xf = out2 + c * ncf;
+                    own_xf[c][0] = xf[q00]; own_xf[c][1] = xf[q00 + 1];
+                    own_xf[c][2] = xf[q10]; own_xf[c][3] = xf[q10 + 1];
                 }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if constexpr (PERT) { own_x[c] = xp[c * nc + q]; own_f0[c] = F0[c * nc + q]; }
-                if constexpr (STG || MODE == FVM_DEFECT)
-                    own_b[c] = b[c * nc + q];
-                // the first stage of a sweep has x^(0) = x^(j-1): no second load (the copy
-                // is taken where x^(0) is used, so that no load waits for another)
-                if constexpr (STG)
-                    if (x0 && x0 != xp) own_x0[c] = x0[c * nc + q];
             }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if constexpr (PERT) { own_x[c] = xp[c * nc + qo]; own_f0[c] = F0[c * nc + qo]; }
+            if constexpr (STG || MODE == FVM_DEFECT) own_b[c] = b[c * nc + qo];
         }
+        // the first stage of a sweep has x^(0) = x^(j-1): no second load (the copy
+        // is taken where x^(0) is used, so that no load waits for another)
+        if constexpr (STG)
+            if (x0 && x0 != xp)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) own_x0[c] = x0[c * nc + qo];
     };
     if constexpr (!LATE) load_own();
     T hu[HITEMS][4], hx[HITEMS][4];
@@ -283,23 +304,23 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
         const int h = tid + it * NTH;
         int Ih = I0 - 1 + h % HX;
         const int Jh = J0 - 1 + h / HX;
-        bool ok = h < NH && Jh >= 0 && Jh < nzl;
-        if (Ih < 0 || Ih >= nxl) {
-            if (A.bc == 1) Ih = (Ih + nxl) % nxl;
-            else ok = false;
-        }
-        const long qh = (long)Jh * nxl + Ih;
+        // x-periodic: the column before the first and the one after the last wrap around
+        // (columns further out belong to no face)
+        const bool out_l = Ih < 0, out_r = Ih >= nxl;
+        const bool ok = h < NH && Jh >= 0 && Jh < nzl && (!(out_l || out_r) || (A.bc == 1 && Ih <= nxl));
+        Ih = out_l ? nxl - 1 : out_r ? 0 : Ih;
+        const long qh = ok ? (long)Jh * nxl + Ih : 0;   // (a cell that no face reads: cell 0's)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            hu[it][c] = ok ? u[c * nc + qh] : T(0);
-            if constexpr (PERT) hx[it][c] = ok ? xp[c * nc + qh] : T(0);
+            hu[it][c] = u[c * nc + qh];
+            if constexpr (PERT) hx[it][c] = xp[c * nc + qh];
         }
     }
     // eps = sqrt(eps_p) ||u + Ubar|| / ||x|| and adt / eps, from ||x|| and the stored 1/||u + Ubar||
     T eps = T(0), sc = T(0);
     bool xzero = false;   // uniform: g'x = 0 for x = 0
     if constexpr (PERT) {
-        const double xn2 = sum_partials<NTH>(xpart, xcount);   // ||x||^2, same order in every block
+        const double xn2 = xsum.sum(xpart, xcount);   // ||x||^2, same order in every block
         if (!(xn2 > 0.0)) {
             xzero = true;
         } else {
@@ -321,12 +342,10 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
                     sw[c][h / HX][h % HX] = v;
                 }
         }
-        if (tid < 6 * TZ) {
-            const int r = tid / 6, k = tid - 6 * r;
-            if (J0 + r < nzl) sBc[r][k] = bg_v;
-        } else if (tid < 6 * TZ + 10 * (TZ + 1)) {
-            const int t2 = tid - 6 * TZ, r = t2 / 10, k = t2 - 10 * r;
-            if (J0 + r <= nzl) sBf[r][k] = bg_v;
+        if (bg_ok) (bg_c ? &sBc[0][0] : &sBf[0][0])[bg_i] = bg_v;
+        if constexpr (TI) {
+            if (tid < MAXN1 * MAXN1) sVi[tid / MAXN1][tid % MAXN1] = tv.Vinv[tid / MAXN1][tid % MAXN1];
+            else if (tid < MAXN1 * MAXN1 + MAXN1) sWn[tid - MAXN1 * MAXN1] = tv.wnc[tid - MAXN1 * MAXN1];
         }
         __syncthreads();
         // ---- one net flux per face: x-faces in thread order, z-faces in reverse
@@ -342,8 +361,12 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
             for (int fz = (tid + NTH - NFX % NTH) % NTH; fz < NFZ; fz += NTH) face(std::false_type{}, fz);
         if constexpr (LATE) load_own();
         __syncthreads();
-    } else if constexpr (LATE) {
-        load_own();
+    } else {
+        if constexpr (TI) {
+            if (tid < MAXN1 * MAXN1) sVi[tid / MAXN1][tid % MAXN1] = tv.Vinv[tid / MAXN1][tid % MAXN1];
+            else if (tid < MAXN1 * MAXN1 + MAXN1) sWn[tid - MAXN1 * MAXN1] = tv.wnc[tid - MAXN1 * MAXN1];
+        }
+        if constexpr (LATE) load_own();
     }
 
     // ---- per cell ----
@@ -374,7 +397,7 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 out[c * nc + q] = f[c];   // F0
-                Ut[c] = u[c * nc + q] + A.bgc[4 * J + c];
+                Ut[c] = u[c * nc + q] + A.rc[6 * J + c];
                 ss += (double)Ut[c] * (double)Ut[c];
             }
             const double rho = Ut[0], uu = Ut[1] / rho, ww = Ut[2] / rho;

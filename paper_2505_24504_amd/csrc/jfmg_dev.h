@@ -77,14 +77,9 @@ template <typename T> __device__ __forceinline__ void st(T* base, unsigned i, T 
     *(T*)((char*)base + i * (unsigned)sizeof(T)) = v;
 }
 
-// The same (wave-uniform) pointer, opaque to the optimizer: loads through it are
-// issued again instead of being merged with earlier loads of the same address,
-// whose values would otherwise be held in registers in between.
-template <typename T> __device__ __forceinline__ T* opaque(T* p)
-{
-    asm volatile("" : "+s"(p));
-    return p;
-}
+// A device pointer in the global address space: pointers that went through an asm
+// statement are not known to be global any more, and loads through them would be flat.
+template <typename T> using gptr = const __attribute__((address_space(1))) T*;
 
 // A value that is the same in every lane of the wave, moved to scalar registers
 // (keeps it out of the vector register budget).
@@ -324,20 +319,64 @@ template <typename P> __device__ __forceinline__ P* mbr(P* p, long ms)
 }
 __device__ __forceinline__ Red mbr(Red r, long ms) { return Red{mbr(r.partials, ms), mbr(r.out, ms)}; }
 
-// deterministic sum of n partials, returned to every thread of the block; once per kernel
-// (the waves' sums stay in LDS)
-template <int NTH> __device__ __forceinline__ double sum_partials(const double* p, int n)
+// A uniform value that another kernel wrote, read by a vector load.  The compiler would
+// make it a scalar load; scalar loads return out of order, so the first wait for any of
+// the kernel's arguments would also wait for this one's trip to memory.
+template <typename T> __device__ __forceinline__ T ldv(const T* p)
 {
-    __shared__ double sh[NTH / 64];
-    double a = 0.0;
-    for (int i = threadIdx.x; i < n; i += NTH) a += p[i];
-    a = wave_sum(a);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < NTH / 64; ++i) s += sh[i];
-    return s;
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    return p[z];
 }
+
+// Deterministic sum of n partials, returned to every thread of the block; once per
+// kernel.  load() issues the first loads, so that a kernel can issue its other loads
+// behind them; sum() waits for them.  The order: entry i belongs to lane i mod 64 and
+// wave (i / 64) mod NW of a block of NW waves; each lane of each wave adds its entries in
+// turn, then each lane over the waves, then the lanes.  Up to 256 entries every wave
+// holds them all and follows that order by itself, without an exchange through LDS; more
+// are split over the block.  (Entries of zero at the end change nothing: a ragged batch
+// passes the count of its largest member.)
+template <int NTH> struct PartialSum {
+    static constexpr int NW = NTH / 64, NV = 4;
+    double v[NV];
+    __device__ __forceinline__ void load(const double* p, int n)
+    {
+        const bool whole = n <= 64 * NV;
+        const int i0 = whole ? (int)threadIdx.x & 63 : (int)threadIdx.x, st = whole ? 64 : NTH;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const int i = i0 + k * st;
+            const double x = p[i < n ? i : 0];   // (no branch: the wait for them would also
+            v[k] = i < n ? x : 0.0;              // wait for the loads behind them)
+        }
+    }
+    __device__ __forceinline__ double sum(const double* p, int n)
+    {
+        __shared__ double sh[NW][64];
+        double s;
+        if (n <= 64 * NV) {
+            double w[NW < NV ? NW : NV];
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                if (k < NW) w[k] = v[k];
+                else w[k % NW] += v[k];
+            }
+            s = w[0];
+#pragma unroll
+            for (int k = 1; k < (NW < NV ? NW : NV); ++k) s += w[k];
+        } else {
+            double a = ((v[0] + v[1]) + v[2]) + v[3];
+            for (int i = threadIdx.x + NV * NTH; i < n; i += NTH) a += p[i];
+            const int lane = threadIdx.x & 63;
+            sh[threadIdx.x >> 6][lane] = a;
+            __syncthreads();
+            s = sh[0][lane];
+#pragma unroll
+            for (int k = 1; k < NW; ++k) s += sh[k][lane];
+        }
+        return wave_sum(s);
+    }
+};
 
 }  // namespace jfmg

@@ -146,11 +146,8 @@ template <typename T> struct FvArgs {
     int tile;        // jfmg_tile shape of the operator kernels on this level (host side)
     int lev;         // level index (the entry of a ragged batch's member table)
     Gas<T> gas;
-    const T* bgc;    // [nzl][4]   background at cell-centre z
-    const T* bgf;    // [nzl+1][4] background at z-faces
-    const T* dbgf;   // [nzl+1][4] d/dz background at z-faces
-    const T* pc;     // [nzl][2]   background pressure, 1/(rho theta) at cell-centre z
-    const T* pf;     // [nzl+1][2] the same at z-faces
+    const T* rc;     // [nzl][6]    at cell-centre z: Ubar, pressure, 1/(rho theta)
+    const T* rf;     // [nzl+1][10] at z-faces: the same, then d/dz Ubar
 };
 
 // device scalar slots of one FV level (doubles)
