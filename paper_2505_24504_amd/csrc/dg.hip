@@ -28,7 +28,7 @@
 // thread per node, every face point evaluated from both sides and the background's HLLC
 // at each of them, M^-1 L_h took 705 us at 1024 x 1024 elements (viscous, k = 3) and an
 // explicit stage 15.3 us at 256 x 64 and 11.1 us at 197 x 45 (k = 2); this form takes
-// 438, 12.0 and 7.7 us with half the VALU and a third of the LDS work per node.  A
+// 438, 11.8 and 7.4 us with half the VALU and a third of the LDS work per node.  A
 // node-per-thread form with each tile face evaluated once reached 636, 13.3 and 7.9 us.
 // Six waves per work-group (the neighbours' lines and the high faces on two of their
 // own) were slower at k = 3, 18.7 against 15.2 us under counters: two such groups do
@@ -188,19 +188,18 @@ __device__ __forceinline__ void dg_face(const DgArgs& A, double (&tl)[4], const 
 // The line of nodes n0, n0 + 1, ... (x) or n0, n0 + N1, ... (z) of the four components,
 // in the line's frame (component 1 the momentum along it).  xd is wave-uniform.
 template <int N1>
-__device__ __forceinline__ void dg_line(const double* __restrict__ U, long N, unsigned n0, bool xd, bool ok,
-                                        double (&v)[4][N1])
+__device__ __forceinline__ void dg_line(const double* __restrict__ U, long N, unsigned n0, bool xd, double (&v)[4][N1])
 {
     if (xd) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int j = 0; j < N1; ++j) v[c][j] = ok ? ld(U + c * N, n0 + j) : 0.0;
+            for (int j = 0; j < N1; ++j) v[c][j] = ld(U + c * N, n0 + j);
     } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int j = 0; j < N1; ++j) v[c][j] = ok ? ld(U + (c == 1 ? 2 : c == 2 ? 1 : c) * N, n0 + j * N1) : 0.0;
+            for (int j = 0; j < N1; ++j) v[c][j] = ld(U + (c == 1 ? 2 : c == 2 ? 1 : c) * N, n0 + j * N1);
     }
 }
 
@@ -213,6 +212,20 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
           const double* __restrict__ ut2p, int eps_mode, double adt, Red red, long ms, ExStage rk, int ycount)
 {
     const DgArgs& A = dg_of<RG>(Aa, mt);
+    // the arguments that the first loads need, in scalar registers at once
+    gptr<double> U_ = (gptr<double>)U, rec_ = (gptr<double>)A.rec;
+    int nx = A.nx, nz = A.nz;
+    if constexpr (MODE == 3) {
+        gptr<double> Y_ = (gptr<double>)Y, yn2p_ = (gptr<double>)yn2p, ut2p_ = (gptr<double>)ut2p;
+        asm volatile("" : "+s"(U_), "+s"(Y_), "+s"(rec_), "+s"(yn2p_), "+s"(ut2p_), "+s"(ycount), "+s"(nx), "+s"(nz));
+        Y = (const double*)Y_;
+        yn2p = (const double*)yn2p_;
+        ut2p = (const double*)ut2p_;
+    } else {
+        asm volatile("" : "+s"(U_), "+s"(rec_), "+s"(nx), "+s"(nz));
+    }
+    U = (const double*)U_;
+    const double* const grec = (const double*)rec_;
     double* lin0 = A.lin0;
     if (gridDim.z > 1) {   // member of a lock-step batch
         U = mbr(U, ms);
@@ -232,7 +245,6 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     constexpr int TRN = NS ? 8 : 4;                   // trace (and its derivative)
     constexpr int FLN = NS ? 7 : 4;                   // face terms the low side's element needs
     constexpr int FCN = NS ? 10 : 4;                  // stored face terms of the linearization state
-    const int nx = A.nx, nz = A.nz;
     const int ntx = (nx + TEX - 1) / TEX, ntiles = dg_tiles<N1>(nx, nz);   // this member's work-groups
     if ((int)blockIdx.x >= ntiles || (RG && sits_out(mt))) {   // beyond a smaller member, or one that sits out
         if (MODE == 2 && red.partials && threadIdx.x == 0) red.partials[block_linear()] = 0.0;
@@ -242,6 +254,7 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     constexpr int NTR = TRN * NSLOT, NLZ = MODE == 5 ? 1 : 4 * EPB * NP;
     __shared__ double sT[NTR > NLZ ? NTR : NLZ];
     __shared__ double sF[FLN * (NTH + NXF + NZF)];   // face terms [term][own low face, then the tile's high faces]
+    __shared__ double sH[NS && MODE != 5 ? 3 : 1][NS && MODE != 5 ? NTH : 1];   // the low faces' terms of the high side
     __shared__ double sB[S::NROW][BRN];
     constexpr int NFS = NTH + NXF + NZF;
 
@@ -260,7 +273,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     double* const vol0 = lin0;              // [8][N]
     double* const face0 = lin0 + 8 * N;     // [FCN][NF]
     const unsigned NF = (unsigned)(N1 * ((nx + 1) * (long)nz + nx * (long)(nz + 1)));
-    const unsigned e0 = (unsigned)(((ez0 + lz) * (long)nx + ex0 + lx) * NP);
+    // (lanes without a line read element 0's: the loads stay free of branches)
+    const unsigned e0 = valid ? (unsigned)(((ez0 + lz) * (long)nx + ex0 + lx) * NP) : 0u;
     const unsigned n0 = e0 + (xd ? ln * N1 : ln);         // first node of the line
     const RefTab& R = A.R;
 
@@ -273,8 +287,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         if (eps_mode != 0) ut2 = ldv(ut2p);
     }
     double s[4][N1], y[4][N1];
-    dg_line<N1>(U, N, n0, xd, valid, s);
-    if constexpr (MODE == 3) dg_line<N1>(Y, N, n0, xd, valid, y);
+    dg_line<N1>(U, N, n0, xd, s);
+    if constexpr (MODE == 3) dg_line<N1>(Y, N, n0, xd, y);
     // the neighbour elements' lines outside the tile: of bottom and top (z) in wave 2, of
     // left and right (x) in wave 3; at a wall none
     double h[4][N1], hy[4][N1];
@@ -291,21 +305,37 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         else if (ex < 0 || ex >= nx) { ex = up ? 0 : nx - 1; ok = ok && per; }
         if (ok) hslot = NTH + (wv == 2 ? 2 * NXF : 0) + l;
         hhigh = !up;
-        const unsigned o = (unsigned)((ez * (long)nx + ex) * NP) + (wv == 2 ? r : r * N1);
-        dg_line<N1>(U, N, o, wv != 2, ok, h);
-        if constexpr (MODE == 3) dg_line<N1>(Y, N, o, wv != 2, ok, hy);
+        const unsigned o = ok ? (unsigned)((ez * (long)nx + ex) * NP) + (wv == 2 ? r : r * N1) : 0u;
+        dg_line<N1>(U, N, o, wv != 2, h);
+        if constexpr (MODE == 3) dg_line<N1>(Y, N, o, wv != 2, hy);
     }
+    constexpr int NRL = (BRN * ROWS + NTH - 1) / NTH;   // loads per thread for the node rows
+    double rr[NRL], rf = 0.0;
     if constexpr (REC) {
-        const double* rn = A.rec + (long)DG_REC * ez0 * N1;                  // node rows
-        const double* rf = A.rec + (long)DG_REC * ((long)nz * N1 + ez0);     // z-faces
-        for (int i = t; i < BRN * wz * N1; i += NTH) sB[i / BRN][i % BRN] = rn[(i / BRN) * DG_REC + i % BRN];
-        for (int i = t; i < BRN * (wz + 1); i += NTH) sB[ROWS + i / BRN][i % BRN] = rf[(i / BRN) * DG_REC + i % BRN];
+        const double* rn = grec + (long)DG_REC * ez0 * N1;                  // node rows
+        const double* rz = grec + (long)DG_REC * ((long)nz * N1 + ez0);     // z-faces
+#pragma unroll
+        for (int k = 0; k < NRL; ++k) {
+            const int i = t + k * NTH < BRN * wz * N1 ? t + k * NTH : 0;
+            rr[k] = rn[(i / BRN) * DG_REC + i % BRN];
+        }
+        const int i = t < BRN * (wz + 1) ? t : 0;
+        rf = rz[(i / BRN) * DG_REC + i % BRN];
     } else if (t < (BGSUB ? 3 * ROWS : ROWS) + TEZ + 1) {
         // one lane per row; a node row's three flux cases on three lanes
         const bool zr = t < TEZ + 1;   // a z-face row
         const int q = t - (TEZ + 1), v = zr ? 0 : q / ROWS, r = zr ? t : q - v * ROWS;
         if (zr ? r <= wz : r < wz * N1)
             dg_record(A, zr, zr ? ez0 + r : ez0 * N1 + r, v, BGSUB, sB[zr ? ROWS + r : r]);
+    }
+    // (JVP) the stored terms of the linearization state at the line's low face
+    const unsigned fo0 = valid ? (xd ? (unsigned)(((long)(ez0 + lz) * (nx + 1) + ex0 + lx) * N1 + ln)
+                                     : (unsigned)(((long)(nx + 1) * nz + (long)(ez0 + lz) * nx + ex0 + lx) * N1 + ln))
+                               : 0u;
+    double l0[FCN], urho[N1];
+    if constexpr (MODE == 3) {
+#pragma unroll
+        for (int c = 0; c < FCN; ++c) l0[c] = ld(face0 + (long)c * NF, fo0);
     }
     double eps = 0.0;
     if constexpr (MODE == 3) {
@@ -319,6 +349,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         }
         eps = uniform(eps_mode == 0 ? FdEps<double>::sqrt_eps / sqrt(yn2)
                                     : FdEps<double>::sqrt_eps * sqrt(ut2) / sqrt(yn2));
+#pragma unroll
+        for (int j = 0; j < N1; ++j) urho[j] = s[0][j];
         // the line of U' + eps y
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -361,7 +393,22 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
             if constexpr (NS) sT[(4 + c) * NSLOT + hslot] = da;
         }
     }
+    if constexpr (REC) {
+#pragma unroll
+        for (int k = 0; k < NRL; ++k)
+            if (t + k * NTH < BRN * wz * N1) (&sB[0][0])[t + k * NTH] = rr[k];
+        if (t < BRN * (wz + 1)) sB[ROWS + t / BRN][t % BRN] = rf;
+    }
     __syncthreads();
+    // (JVP) the line's stored volume fluxes, read behind the face work
+    double v0[4][N1];
+    if constexpr (MODE == 3) {
+        const long vo = xd ? 0 : 4 * N;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < N1; ++q) v0[c][q] = ld(vol0 + vo + c * N, n0 + q * (xd ? 1 : N1));
+    }
 
     // ---- F: the face point at the line's low end, and wave 1 the tile's high faces ----
     auto traces = [&](int slot, double (&tr)[4], double (&dn)[4]) {
@@ -371,12 +418,7 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
             if constexpr (NS) dn[c] = sT[(4 + c) * NSLOT + slot];
         }
     };
-    // face point of the grid, gx / gz: the face's low-side element is the one before it
-    auto stored_at = [&](bool xf, int gx, int gz, int r) {
-        return xf ? (unsigned)(((long)gz * (nx + 1) + gx) * N1 + r)
-                  : (unsigned)(((long)(nx + 1) * nz + (long)gz * nx + gx) * N1 + r);
-    };
-    auto finish = [&](double (&Phi)[4], double (&slo)[3], double (&shi)[3], unsigned fo, int slot) {
+    auto finish = [&](double (&Phi)[4], double (&slo)[3], double (&shi)[3], unsigned fo, const double (&f0)[FCN], int slot) {
         if constexpr (MODE == 5) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) st(face0 + (long)c * NF, fo, Phi[c]);
@@ -390,12 +432,12 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         } else {
             if constexpr (MODE == 3) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) Phi[c] -= ld(face0 + (long)c * NF, fo);
+                for (int c = 0; c < 4; ++c) Phi[c] -= f0[c];
                 if constexpr (NS) {
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
-                        slo[c] -= ld(face0 + (long)(4 + c) * NF, fo);
-                        shi[c] -= ld(face0 + (long)(7 + c) * NF, fo);
+                        slo[c] -= f0[4 + c];
+                        shi[c] -= f0[7 + c];
                     }
                 }
             }
@@ -407,22 +449,31 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
             }
         }
     };
-    double Phi[4], shi[3];   // of the line's low face
     if (valid) {
         const bool first = xd ? lx == 0 : lz == 0;   // the low neighbour is outside the tile
         const int slot = first ? NTH + (xd ? lz * N1 + ln : 2 * NXF + lx * N1 + ln) : t - (xd ? N1 : TEX * N1);
-        double tl[4], nl[4], slo[3];
+        double tl[4], nl[4], Phi[4], slo[3], shi[3];
         traces(slot, tl, nl);
         const bool wlo = first && (xd ? ex0 == 0 && !per : ez0 == 0);
         dg_face<NS, BGSUB>(A, tl, nl, tlo, dlo, sB[xd ? lz * N1 + ln : ROWS + lz], xd, wlo, false, Phi, slo, shi);
-        finish(Phi, slo, shi, stored_at(xd, ex0 + lx, ez0 + lz, ln), t);
+        finish(Phi, slo, shi, fo0, l0, t);
+        if constexpr (NS && MODE != 5) {   // (in LDS rather than held through V)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sH[c][t] = shi[c];
+        }
     }
     if (wv == 1) {
         const int l = t & 63;
         const bool xf = l < NXF;
         const int q = xf ? l : l - NXF, g = q / N1, r = q - g * N1;
         if (l < NXF + NZF && g < (xf ? wz : wx)) {
-            double tl[4], nl[4], th[4], nh[4], Ph[4], sl[3], sh[3];
+            double tl[4], nl[4], th[4], nh[4], Ph[4], sl[3], sh[3], f1[FCN];
+            const unsigned fo = xf ? (unsigned)(((long)(ez0 + g) * (nx + 1) + ex0 + wx) * N1 + r)
+                                   : (unsigned)(((long)(nx + 1) * nz + (long)(ez0 + wz) * nx + ex0 + g) * N1 + r);
+            if constexpr (MODE == 3) {
+#pragma unroll
+                for (int c = 0; c < FCN; ++c) f1[c] = ld(face0 + (long)c * NF, fo);
+            }
             traces(xf ? (g * TEX + wx - 1) * N1 + r : HALF + ((wz - 1) * TEX + g) * N1 + r, tl, nl);
             traces(NTH + (xf ? NXF : 2 * NXF + NZF) + q, th, nh);
             const bool end = xf ? ex0 + wx == nx : ez0 + wz == nz;
@@ -430,8 +481,7 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
                                sh);
             // (mode 5: a face between tiles is stored by the tile of its high side)
             if (MODE != 5 || end)
-                finish(Ph, sl, sh, xf ? stored_at(true, ex0 + wx, ez0 + g, r) : stored_at(false, ex0 + g, ez0 + wz, r),
-                       NTH + l);
+                finish(Ph, sl, sh, fo, f1, NTH + l);
         }
     }
 
@@ -440,7 +490,6 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     double L[4][N1];
     const double r2 = xd ? A.rdx2 : A.rdz2;
     if (valid) {
-        const long vo = xd ? 0 : 4 * N;   // this direction's stored volume fluxes
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -486,14 +535,14 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
 #pragma unroll
                 for (int c = 1; c < 4; ++c) F[c] -= A.mu * (G[c] - (Ut[c] * ir) * G[0]);
             }
-            const unsigned no = xd ? n0 + q : n0 + q * N1;
             if constexpr (MODE == 5) {
+                const long vo = xd ? 0 : 4 * N;   // this direction's volume fluxes
 #pragma unroll
-                for (int c = 0; c < 4; ++c) st(vol0 + vo + c * N, no, F[c]);
+                for (int c = 0; c < 4; ++c) st(vol0 + vo + c * N, n0 + q * (xd ? 1 : N1), F[c]);
             }
             if constexpr (MODE == 3) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) F[c] -= ld(vol0 + vo + c * N, no);
+                for (int c = 0; c < 4; ++c) F[c] -= v0[c][q];
             }
             if constexpr (MODE != 5) {
 #pragma unroll
@@ -504,6 +553,10 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         }
     }
     if constexpr (MODE == 5) return;
+    // (JVP) y again, for the output
+    if constexpr (MODE == 3) {
+        if (xd) dg_line<N1>(opaque(Y), N, n0, true, y);
+    }
     __syncthreads();
     if (valid) {
         // face terms of the line's ends: the high face's from LDS
@@ -511,12 +564,12 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         const int slot = last ? NTH + (xd ? lz * N1 + ln : NXF + lx * N1 + ln) : t + (xd ? N1 : TEX * N1);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const double ph = sF[c * NFS + slot];
+            const double pl = sF[c * NFS + t], ph = sF[c * NFS + slot];
 #pragma unroll
-            for (int a = 0; a < N1; ++a) L[c][a] += R.lt[a][4] * Phi[c] - R.lt[a][5] * ph;
+            for (int a = 0; a < N1; ++a) L[c][a] += R.lt[a][4] * pl - R.lt[a][5] * ph;
             if constexpr (NS) {
                 if (c > 0) {
-                    const double lo = r2 * shi[c - 1], hi = r2 * sF[(3 + c) * NFS + slot];
+                    const double lo = r2 * sH[c - 1][t], hi = r2 * sF[(3 + c) * NFS + slot];
 #pragma unroll
                     for (int a = 0; a < N1; ++a) L[c][a] += R.lt[a][7] * hi - R.lt[a][6] * lo;
                 }
@@ -544,7 +597,7 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
                 double v = r2 * L[c][a] + sT[(c * EPB + le) * NP + ln * N1 + a];
                 if (c == 2) {
                     // gravity; JVP: of (U' + eps y)_rho - U'_rho
-                    if constexpr (MODE == 3) v -= A.g * (s[0][a] - ld(U, no));
+                    if constexpr (MODE == 3) v -= A.g * (s[0][a] - urho[a]);
                     else v -= A.g * s[0][a];
                 }
                 if constexpr (MODE == 0) st(out + c * N, no, v * (R.w[a] * R.w[ln] * A.J));

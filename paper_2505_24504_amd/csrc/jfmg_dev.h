@@ -81,6 +81,16 @@ template <typename T> __device__ __forceinline__ void st(T* base, unsigned i, T 
 // statement are not known to be global any more, and loads through them would be flat.
 template <typename T> using gptr = const __attribute__((address_space(1))) T*;
 
+// The same (wave-uniform) pointer, opaque to the optimizer: loads through it are
+// issued again instead of being merged with earlier loads of the same address,
+// whose values would otherwise be held in registers in between.
+template <typename T> __device__ __forceinline__ const T* opaque(const T* p)
+{
+    gptr<T> g = (gptr<T>)p;
+    asm volatile("" : "+s"(g));
+    return (const T*)g;
+}
+
 // A value that is the same in every lane of the wave, moved to scalar registers
 // (keeps it out of the vector register budget).
 __device__ __forceinline__ double uniform(double v)
