@@ -258,6 +258,13 @@ class Problem:
     def dg_zeros(self):
         return torch.zeros(self.ndof, dtype=torch.float64, device=self.device)
 
+    # outputs that a call writes in full: not cleared first
+    def _dg_out(self):
+        return torch.empty(self.ndof, dtype=torch.float64, device=self.device)
+
+    def _fv_out(self, level):
+        return torch.empty(self.fv_size(level), dtype=self.fv_dtype, device=self.device)
+
     def state_zeros(self):
         """A state of every member, members back to back."""
         return torch.zeros(sum(self.member_ndof), dtype=torch.float64, device=self.device)
@@ -284,12 +291,12 @@ class Problem:
         return U
 
     def residual(self, U, apply_minv=False):
-        out = self.dg_zeros()
+        out = self._dg_out()
         self._check(self.L.jfmg_residual(self.h, _ptr(U), _ptr(out), int(apply_minv)))
         return out
 
     def stage_residual(self, U, Ubar, alpha_dt):
-        G = self.dg_zeros()
+        G = self._dg_out()
         nrm = C.c_double()
         self._check(self.L.jfmg_stage_residual(self.h, _ptr(U), _ptr(Ubar), float(alpha_dt), _ptr(G),
                                                C.byref(nrm)))
@@ -299,12 +306,12 @@ class Problem:
         self._check(self.L.jfmg_linearize(self.h, _ptr(U), float(alpha_dt)))
 
     def jvp(self, y):
-        out = self.dg_zeros()
+        out = self._dg_out()
         self._check(self.L.jfmg_jvp(self.h, _ptr(y), _ptr(out)))
         return out
 
     def mg_apply(self, r):
-        z = self.dg_zeros()
+        z = self._dg_out()
         self._check(self.L.jfmg_mg_apply(self.h, _ptr(r), _ptr(z)))
         return z
 
@@ -335,24 +342,24 @@ class Problem:
 
     def transfer(self, direction, x):
         if direction == 0:
-            out = self.fv_zeros(0)
+            out = self._fv_out(0)
         else:
-            out = self.dg_zeros()
+            out = self._dg_out()
         self._check(self.L.jfmg_transfer(self.h, int(direction), _ptr(x), _ptr(out)))
         return out
 
     def restrict(self, fine_level, x):
-        out = self.fv_zeros(fine_level + 1)
+        out = self._fv_out(fine_level + 1)
         self._check(self.L.jfmg_restrict(self.h, fine_level, _ptr(x), _ptr(out)))
         return out
 
     def prolong(self, coarse_level, x):
-        out = self.fv_zeros(coarse_level - 1)
+        out = self._fv_out(coarse_level - 1)
         self._check(self.L.jfmg_prolong(self.h, coarse_level, _ptr(x), _ptr(out)))
         return out
 
     def fv_level_state(self, level):
-        out = self.fv_zeros(level)
+        out = self._fv_out(level)
         self._check(self.L.jfmg_fv_level_state(self.h, level, _ptr(out)))
         return out
 
@@ -367,12 +374,12 @@ class Problem:
         return v.value
 
     def fv_matvec(self, level, x):
-        out = self.fv_zeros(level)
+        out = self._fv_out(level)
         self._check(self.L.jfmg_fv_matvec(self.h, level, _ptr(x), _ptr(out)))
         return out
 
     def mg_fv(self, b):
-        x = self.fv_zeros(0)
+        x = self._fv_out(0)
         self._check(self.L.jfmg_mg_fv(self.h, _ptr(b), _ptr(x)))
         return x
 
@@ -391,7 +398,7 @@ class Problem:
         return {KERNEL_CLASSES[i]: {"ms": ms[i], "launches": cnt[i], "bytes": by[i]} for i in range(n)}
 
     def subgrid_map(self):
-        out = torch.zeros(self.fv_size(0) // 4, dtype=torch.int32, device=self.device)
+        out = torch.empty(self.fv_size(0) // 4, dtype=torch.int32, device=self.device)
         self._check(self.L.jfmg_subgrid_map(self.h, _ptr(out)))
         return out
 
