@@ -262,8 +262,10 @@ jfmg_status jfmg_subgrid_map(jfmg_problem* p, int* fv_to_dg);
      JFMG_TILE_8x4   128 threads, every face of the tile on its own thread
      JFMG_TILE_32x4  256 threads, two per cell
      JFMG_TILE_64x4_512  512 threads, two per cell
-   A new problem uses, by level width in cells, 64x8 from 1024, 64x4_512 from
-   512, 16x4 from 256 and 8x4 below.
+   A new problem chooses by the level's number of cells (a ragged batch by that of
+   all its members): 8x4 below 8192, 16x4 below 32768 or where the rows leave more
+   than 30 % of 64-cell rows empty, 64x4_512 below 131072, else 64x4, or 64x8 where
+   its tiles fill one round of work-groups (449 to 512 tiles) and in FP32 from 655360.
    Shapes change the order of the partial sums of the FD step norms only, so
    results agree to rounding; the same shapes give bitwise the same results. */
 typedef enum {
@@ -301,8 +303,8 @@ jfmg_status jfmg_autotune(jfmg_problem* p, int reps, int* shapes, double* times_
 typedef enum {
     JFMG_K_DG_RESIDUAL = 0,   /* stage residual G and ||G||                         */
     JFMG_K_DG_JVP = 1,        /* fused FD Jacobian-vector product                   */
-    JFMG_K_FV_STAGE = 2,      /* RK smoother stage with an FV matvec, levels >= 512
-                                 cells wide (wide-tile kernel)                      */
+    JFMG_K_FV_STAGE = 2,      /* RK smoother stage with an FV matvec, levels with
+                                 64-cell wide tiles (64x4, 64x8, 64x4_512)          */
     JFMG_K_FV_STAGE_ZERO = 3, /* first stage from x = 0 (no matvec)                 */
     JFMG_K_FV_DEFECT = 4,     /* defect + agglomeration restriction                 */
     JFMG_K_FV_PROLONG = 5,    /* injection prolongation + correction               */
@@ -311,7 +313,7 @@ typedef enum {
     JFMG_K_TRANSFER_TINV = 8, /* FV -> DG                                           */
     JFMG_K_MULTIDOT = 9,      /* Arnoldi <w, v_i>                                   */
     JFMG_K_UPDATE = 10,       /* Arnoldi w -= V h                                   */
-    JFMG_K_FV_STAGE_SMALL = 11, /* the same on narrower levels (small-tile kernel)    */
+    JFMG_K_FV_STAGE_SMALL = 11, /* the same on levels with narrower tiles               */
     JFMG_K_DG_SMOOTH = 12,    /* DG-level smoother stage combination (key a, b)     */
     JFMG_K_DG_LINEARIZE = 13, /* fluxes of the linearization state for the JVPs     */
     JFMG_K_NCLASS = 14

@@ -1741,7 +1741,15 @@ jfmg_status create_impl(const jfmg_config* cfgs, int n, bool ragged, void* works
     for (int l = 0; l < p->nlev; ++l) {
         Level& L = p->lev[l];
         L.nx = nxl; L.nz = nzl; L.nc = (long)nxl * nzl;
-        L.tile = fv_default_tile(nxl);
+        // (the members of a ragged batch share a launch; those of a lock-step batch keep the
+        // shape of a single problem, whose results they match bitwise)
+        long cells = 0, padded = 0;
+        for (int m = 0; m < (ragged ? n : 1); ++m) {
+            const long w = (long)p->n1 * cfgs[m].nx >> l, h = (long)p->n1 * cfgs[m].nz >> l;
+            cells += w * h;
+            padded += (w + 63) / 64 * 64 * h;
+        }
+        L.tile = fv_default_tile(cells, padded, cfg->mg_precision == 32);
         L.hx = (cfg->x1 - cfg->x0) / nxl;
         L.hz = (cfg->z1 - cfg->z0) / nzl;
         nxl /= 2;

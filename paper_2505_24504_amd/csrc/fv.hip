@@ -38,11 +38,7 @@ enum { FVM_LIN = 0, FVM_STAGE = 1, FVM_MATVEC = 2, FVM_DEFECT = 3, FVM_STAGE_PC 
 //   64x4 / 512 threads: the 64x4 tile with two threads per cell (twice the waves
 //         of the 256-thread form on a level too small to fill the chip)
 // z-faces are handed out from the last thread down, so that the threads with a
-// second x-face are not those with a second z-face.  Default by level width: 64x8
-// from 1024 cells, 64x4 with 512 threads from 512, 16x4 from 256, 8x4 below (the
-// autotuner's choice on the density-current levels 1024x256 ... 128x32; earlier
-// measurements also ruled out 32x8, 16x4 with 128/192 threads, 64x4 with 2/3 waves
-// per SIMD and early own-cell loads).
+// second x-face are not those with a second z-face.  Default: fv_default_tile.
 
 // Net flux through one face of a tile (HLLC minus the k = 0 interior-penalty diffusion
 // flux, along +x or +z, times the face length) from the tile's staged states; face
@@ -893,11 +889,28 @@ void FvLaunch<T>::norm2(const T* x, long n, Red red, hipStream_t st, const Mb& m
     fv_norm2_kernel<T><<<dim3(norm_blocks(n), 1, mb.n), dim3(256), 0, st>>>(x, n, red, mb.ms);
     if (red.out) launch_finalize(red.partials, norm_blocks(n), 1, red.out, st, Gate{}, mb);
 }
-int fv_default_tile(long nxl)
+// The default shape by the level's cells (in a ragged batch those of all members, which
+// share a launch).  Stage kernel, FP64 / FP32, us (viscous 256 x 64 and 768 x 192 elements
+// of degree 3 and their coarser levels, 24 members of 288 x 144 cells and less):
+//     cells    8x4         16x4        64x4_512    64x4        64x8
+//      4096    4.1 / 3.7   4.5 / 3.8   6.0 / 5.8   6.1 / 5.3   7.4 / 6.6
+//     16384    4.6 / 3.9   4.5 / 4.0   5.8 / 5.9   6.0 / 5.2   7.4 / 6.7
+//     65536   10.3 / 6.4   8.3 / 5.8   6.3 / 5.1   6.5 / 5.4   8.0 / 6.1
+//    147456   16.8 / 10.4 14.2 / 8.9  12.0 / 8.1  10.1 / 7.0  11.6 / 8.2
+//    262144   29.5 / 15.5 22.9 / 13.5 14.8 / 9.9  13.3 / 9.5  12.8 / 9.1
+//    580608   51.5 / 26.4 47.7 / 23.6 33.0 / 19.9 24.7 / 16.0 26.5 / 16.9
+//   2359296    268 / 101   191 / 84.7  129 / 61.1 93.1 / 50.7  102 / 45.6
+// (by the level's width, the rule before, 192 x 96 cells took 8x4, the members 16x4 and a
+// level of 2400 x 80 cells 64x8, 11.7 / 8.7 against 10.5 / 7.8 with 64x4).  64x8 is the
+// fastest where its tiles fill the 512 places of one round, and in FP32 on large levels.
+// Rows that leave more than 30 % of the 64-cell rows empty take 16x4.
+int fv_default_tile(long cells, long padded64, bool f32)
 {
-    return nxl >= 1024 ? JFMG_TILE_64x8
-           : nxl >= 512 ? JFMG_TILE_64x4_512
-           : nxl >= 256 ? JFMG_TILE_16x4 : JFMG_TILE_8x4;
+    if (cells < 8192) return JFMG_TILE_8x4;
+    if (cells < 32768 || 10 * cells < 7 * padded64) return JFMG_TILE_16x4;
+    if (cells < 131072) return JFMG_TILE_64x4_512;
+    const long t8 = padded64 / 512;   // tiles of 64x8
+    return (t8 > 448 && t8 <= 512) || (f32 && cells >= 655360) ? JFMG_TILE_64x8 : JFMG_TILE_64x4;
 }
 bool fv_wide_tile(int tile) { return tile == JFMG_TILE_64x4 || tile == JFMG_TILE_64x8 || tile == JFMG_TILE_64x4_512; }
 bool fv_tile_fits_elements(int tile, int n1)

@@ -260,9 +260,10 @@ void launch_transfer_Tinv(int k, const DgArgs& A, int mass_fix, const T* u, doub
 void launch_subgrid_map(int k, const DgArgs& A, int nxf, int* out, hipStream_t st);
 
 // ---- FV kernels (fv.hip) ----
-// default tile shape of the FV operator kernels on a level nxl cells wide, and
-// whether a shape is one of the wide ones (one wave per 64-cell row)
-int fv_default_tile(long nxl);
+// default tile shape of the FV operator kernels for a level of this many cells, padded64
+// with its rows filled up to 64 cells, and whether a shape is one of the wide ones (one
+// wave per 64-cell row)
+int fv_default_tile(long cells, long padded64, bool f32);
 bool fv_wide_tile(int tile);
 // FV partial-sum blocks needed by the largest launch on a level of nxl x nzl cells
 long fv_partial_blocks(long nxl, long nzl);
