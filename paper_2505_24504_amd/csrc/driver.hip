@@ -1065,10 +1065,9 @@ jfmg_status iter_ops(jfmg_problem* p, int j)
     pub.zn = nv;
     pub.fidx = S_RF - S_H1;
     pub.cnt = (unsigned long long*)(p->scal + S_CNT);
-    { ProfScope ps(p, JFMG_K_MULTIDOT, md); launch_multidot(w, p->V, N, nv, 1, N, Gate{}, red_at(p, S_H1), st, p->mb); }
+    { ProfScope ps(p, JFMG_K_MULTIDOT, md); launch_multidot(w, p->V, N, nv, 1, N, red_at(p, S_H1), st, p->mb); }
     { ProfScope ps(p, JFMG_K_UPDATE, up);
-      launch_update(w, p->V, N, nv, N, p->scal + S_H1, Red{nullptr, nullptr}, st, Gate{}, p->mb, reorth,
-                    p->partials, pub); }
+      launch_update(w, p->V, N, nv, N, p->scal + S_H1, st, p->mb, reorth, p->partials, pub); }
     double* wpart = p->partials + (long)(p->m + 1) * la_blocks(N);
     launch_update2_publish(w, p->V, N, nv, N, reorth, p->partials, p->scal + S_H2, wpart, pub, st, p->mb);
     return check_launch(p);

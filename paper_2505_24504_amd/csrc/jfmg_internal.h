@@ -359,15 +359,15 @@ void launch_norm2(const double* x, long n, Red red, hipStream_t st, const Mb& mb
 void launch_gather(const double* src, int count, double* host, hipStream_t st, const Mb& mb);
 void launch_scatter(double* dst, int count, const double* host, long hstride, hipStream_t st, const Mb& mb);
 // the finalize into red.out is launched only when red.out != nullptr
-void launch_multidot(const double* w, const double* V, long ld, int nv, int self, long n, Gate gate, Red red,
-                     hipStream_t st, const Mb& mb = Mb{});
+void launch_multidot(const double* w, const double* V, long ld, int nv, int self, long n, Red red, hipStream_t st,
+                     const Mb& mb = Mb{});
 struct Publish;
-// w -= sum_i h[i] V_i; optional ||w||^2 into red.out when red.out != nullptr.  With dots (g2.h
-// set), where gate g2 opens, the multi-dot <w_new, v_i> (i < nv) of the updated w follows in the
-// same kernel, its block partials at dots (la_blocks(n) per entry, as launch_multidot stores
-// them); where it stays closed, the kernel publishes (pub) with ||w_new||^2 by Pythagoras.
-void launch_update(double* w, const double* V, long ld, int nv, long n, const double* h, Red red, hipStream_t st,
-                   Gate gate, const Mb& mb, Gate g2, double* dots, const Publish& pub);
+// w -= sum_i h[i] V_i (h the coefficients that g2.h holds).  With dots (g2.h set), where gate
+// g2 opens, the multi-dot <w_new, v_i> (i < nv) of the updated w follows in the same kernel,
+// its block partials at dots (la_blocks(n) per entry, as launch_multidot stores them); where
+// it stays closed, the kernel publishes (pub) with ||w_new||^2 by Pythagoras.
+void launch_update(double* w, const double* V, long ld, int nv, long n, const double* h, hipStream_t st, const Mb& mb,
+                   Gate g2, double* dots, const Publish& pub);
 // Publication of an FGMRES iteration's scalars: src[0..ns) to host-visible pinned memory
 // (host, member m at host + m * host_stride), entry idx replaced by ||w||^2 (also stored to
 // out[0]), entries zoff .. zoff+zn by 0 where the second pass was skipped, entry fidx by 1

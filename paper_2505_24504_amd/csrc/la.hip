@@ -5,9 +5,12 @@
 // reduction is two-level with a fixed summation order (run-to-run identical).
 #include "jfmg_internal.h"
 
+#include <algorithm>
+
 namespace jfmg {
 
 constexpr int LA_NTH = 256, LA_EL = 4;   // threads per block, elements per thread
+constexpr int LA_FILL = 2048;            // blocks up to which the multi-dot splits its groups
 
 int la_blocks(long n)
 {
@@ -27,8 +30,20 @@ __global__ void __launch_bounds__(256) finalize_kernel(const double* __restrict_
         if (threadIdx.x == 0) out[q] = 0.0;
         return;
     }
+    // eight loads in flight per thread
+    const double* pq = p + (long)q * nb;
     double a = 0.0;
-    for (int i = threadIdx.x; i < nb; i += 256) a += p[(long)q * nb + i];
+    for (int i0 = 0; i0 < nb; i0 += 8 * 256) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int i = i0 + k * 256 + (int)threadIdx.x;
+            const double x = pq[i < nb ? i : 0];
+            v[k] = i < nb ? x : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a += v[k];
+    }
     a = block_sum<256>(a, sh);
     if (threadIdx.x == 0) out[q] = a;
 }
@@ -87,88 +102,100 @@ void launch_norm2(const double* x, long n, Red red, hipStream_t st, const Mb& mb
     if (red.out) launch_finalize(red.partials, nb, 1, red.out, st, Gate{}, mb);
 }
 
-// <w, v_i> for i < nv (and <w, w> as entry nv when self is set): the entries are
-// split into groups of MAXV consecutive ones, one group per grid row (blockIdx.y),
-// so every thread keeps MAXV accumulators in registers whatever nv is (w is read
-// once per group); each wave reduces them (wave_sum) and one LDS exchange
-// combines the waves (a single barrier per block); the block partials [v][block]
-// are summed by the finalize kernel.  Nothing is computed where the gate is closed.
-template <int MAXV>
-__global__ void __launch_bounds__(LA_NTH)
-multidot_kernel(const double* __restrict__ w, const double* __restrict__ V, long ld, int nv, int self, long n, Gate gate,
-                Red red, long ms, const MemberArgs* __restrict__ mt)
+// Element k of the thread at base = block start + t (wave-wide loads of 512 contiguous bytes).
+__device__ __forceinline__ long la_el(long base, int k) { return base + (long)k * LA_NTH; }
+__device__ __forceinline__ void ld_els(const double* __restrict__ x, long base, double (&v)[LA_EL])
 {
-    constexpr int NW = LA_NTH / 64;
+#pragma unroll
+    for (int k = 0; k < LA_EL; ++k) v[k] = x[la_el(base, k)];
+}
+
+// <w, v_i> for i < nv (and <w, w> as entry nv when self is set) over one block of w, which
+// stays in registers: the basis vectors come in groups of G, the next group's loads in
+// flight while the current one is reduced (the wave's sums; one LDS exchange at the end
+// combines the waves); the block partials [v][block] are summed by the finalize kernel.
+// Grids too small to fill the chip split the groups over blockIdx.y.
+__global__ void __launch_bounds__(LA_NTH)
+multidot_kernel(const double* __restrict__ w, const double* __restrict__ V, long ld, int nv, int self, long n, Red red,
+                long ms, const MemberArgs* __restrict__ mt)
+{
+    constexpr int NW = LA_NTH / 64, G = 4;
     n = len_of(n, mt);   // a ragged member's length: blocks beyond it store zero partials
-    __shared__ double sh[NW][MAXV];
+    __shared__ double sh[NW][65];
     w = mbr(w, ms);
     V = mbr(V, ms);
-    gate.h = mbr(gate.h, ms);
     red = mbr(red, ms);
-    if (!gate_open(gate)) return;
     const int nt = nv + self;
-    const int v0 = blockIdx.y * MAXV;   // first entry of this block's group
-    const long base = (long)blockIdx.x * LA_NTH * LA_EL + threadIdx.x;
-    double acc[MAXV];
-#pragma unroll
-    for (int q = 0; q < MAXV; ++q) acc[q] = 0.0;
-    if (base - threadIdx.x + LA_NTH * LA_EL <= n && v0 + MAXV <= nv) {
-        // a whole block of basis vectors: every load issued before the first product
-        // (the same products in the same order as below)
-        double wv[LA_EL], vv[LA_EL][MAXV];
-#pragma unroll
-        for (int k = 0; k < LA_EL; ++k) {
-            const long i = base + (long)k * LA_NTH;
-            wv[k] = w[i];
-#pragma unroll
-            for (int q = 0; q < MAXV; ++q) vv[k][q] = V[(long)(v0 + q) * ld + i];
-        }
-#pragma unroll
-        for (int k = 0; k < LA_EL; ++k)
-#pragma unroll
-            for (int q = 0; q < MAXV; ++q) acc[q] += wv[k] * vv[k][q];
+    const long b0 = (long)blockIdx.x * LA_NTH * LA_EL, base = b0 + threadIdx.x;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const bool whole = b0 + LA_NTH * LA_EL <= n;
+    double wv[LA_EL];
+    if (whole) {
+        ld_els(w, base, wv);
     } else {
 #pragma unroll
-        for (int k = 0; k < LA_EL; ++k) {
-            const long i = base + (long)k * LA_NTH;
-            if (i < n) {
-                const double wi = w[i];
+        for (int k = 0; k < LA_EL; ++k) wv[k] = la_el(base, k) < n ? w[la_el(base, k)] : 0.0;
+    }
+    auto load = [&](int v0, double (&a)[G][LA_EL]) {
+        if (whole) {
 #pragma unroll
-                for (int q = 0; q < MAXV; ++q) {
-                    const int v = v0 + q;
-                    if (v < nv) acc[q] += wi * V[(long)v * ld + i];
-                    else if (v == nv && self) acc[q] += wi * wi;
-                }
-            }
+            for (int q = 0; q < G; ++q) ld_els(V + (long)min(v0 + q, nv - 1) * ld, base, a[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+#pragma unroll
+                for (int k = 0; k < LA_EL; ++k)
+                    a[q][k] = la_el(base, k) < n ? V[(long)min(v0 + q, nv - 1) * ld + la_el(base, k)] : 0.0;
+        }
+    };
+    auto dots = [&](int v0, const double (&a)[G][LA_EL]) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < LA_EL; ++k) s += wv[k] * a[q][k];
+            s = wave_sum(s);
+            if (lane == 0 && v0 + q < nv) sh[wid][v0 + q] = s;
+        }
+    };
+    const int step = G * (int)gridDim.y;
+    int v0 = G * (int)blockIdx.y;
+    if (v0 < nv) {
+        double a[G][LA_EL], b[G][LA_EL];
+        load(v0, a);
+        for (; v0 < nv; v0 += 2 * step) {
+            if (v0 + step < nv) load(v0 + step, b);
+            dots(v0, a);
+            if (v0 + step >= nv) break;
+            if (v0 + 2 * step < nv) load(v0 + 2 * step, a);
+            dots(v0 + step, b);
         }
     }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int q = 0; q < MAXV; ++q) {
-        if (v0 + q < nt) {
-            const double s = wave_sum(acc[q]);
-            if (lane == 0) sh[wid][q] = s;
-        }
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < MAXV && v0 + (int)threadIdx.x < nt) {
+    if (self && blockIdx.y == 0) {
         double s = 0.0;
 #pragma unroll
-        for (int r = 0; r < NW; ++r) s += sh[r][threadIdx.x];
-        red.partials[(long)(v0 + threadIdx.x) * gridDim.x + blockIdx.x] = s;
+        for (int k = 0; k < LA_EL; ++k) s += wv[k] * wv[k];
+        s = wave_sum(s);
+        if (lane == 0) sh[wid][nv] = s;
+    }
+    __syncthreads();
+    const int e = threadIdx.x;
+    // this block's entries: its groups', and <w, w> in the first row
+    if (e < nt && (e == nv ? blockIdx.y == 0 : (e / G) % (int)gridDim.y == (int)blockIdx.y)) {
+        double s = 0.0;
+#pragma unroll
+        for (int r = 0; r < NW; ++r) s += sh[r][e];
+        red.partials[(long)e * gridDim.x + blockIdx.x] = s;
     }
 }
 
-void launch_multidot(const double* w, const double* V, long ld, int nv, int self, long n, Gate gate, Red red,
-                     hipStream_t st, const Mb& mb)
+void launch_multidot(const double* w, const double* V, long ld, int nv, int self, long n, Red red, hipStream_t st,
+                     const Mb& mb)
 {
-    // groups of 4 entries: measured at the density-current size (nv up to 30), the mean
-    // first-pass launch takes 23.5 us with groups of 4, 25.7 with 8, 33.5 with 16 and 41.8
-    // with all entries in one group (w is re-read once per group, V once)
-    const int nt = nv + self;
-    const dim3 g(la_blocks(n), (nt + 3) / 4, mb.n);
-    timed_launch(multidot_kernel<4>, g, dim3(LA_NTH), st, w, V, ld, nv, self, n, gate, red, mb.ms, mb.tab);
-    if (red.out) launch_finalize(red.partials, la_blocks(n), nt, red.out, st, gate, mb);
+    const int nb = la_blocks(n), ng = (nv + 3) / 4;
+    const int gy = std::min(ng, std::max(1, LA_FILL / (nb * mb.n)));
+    timed_launch(multidot_kernel, dim3(nb, gy, mb.n), dim3(LA_NTH), st, w, V, ld, nv, self, n, red, mb.ms, mb.tab);
+    if (red.out) launch_finalize(red.partials, nb, nv + self, red.out, st, Gate{}, mb);
 }
 
 // w -= sum_v h[v] V_v.
@@ -199,6 +226,7 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
               const double* __restrict__ hpart, int hnb, double* __restrict__ hout, Gate g2,
               double* __restrict__ dots, Publish pub)
 {
+    constexpr int G = 4;
     n = len_of(n, mt);
     gate.h = mbr(gate.h, ms);
     g2.h = mbr(g2.h, ms);
@@ -206,83 +234,90 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     pub.src = mbr(pub.src, ms);
     pub.cnt = mbr(pub.cnt, ms);
     pub.host += (long)blockIdx.z * pub.host_stride;
-    bool dots2 = false;
     if constexpr (SELF) {
         if (!gate_open(gate)) return;   // every lane takes part in the gate's wave sum
-    } else {
-        if (!gate_open(gate)) return;
-        if (dots) {
-            const double after = gate_after(g2);   // every lane, as above
-            dots2 = after < g2.tau2 * g2.h[g2.nv];   // gate_open's decision
-            if (!dots2 && blockIdx.x == 0) {
-                if (threadIdx.x == 0) pub.out[0] = after;
-                for (int i = threadIdx.x; i < pub.ns; i += LA_NTH)
-                    pub.host[i] = (i == pub.idx)                             ? after
-                                  : (i == pub.fidx)                          ? 0.0
-                                  : (i >= pub.zoff && i < pub.zoff + pub.zn) ? 0.0
-                                                                             : pub.src[i];
-            }
-        }
     }
     w = mbr(w, ms);
     V = mbr(V, ms);
     red = mbr(red, ms);
-    __shared__ double hs[SELF ? 64 : 1];
+    const int lane = threadIdx.x & 63;
+    const long b0 = (long)blockIdx.x * LA_NTH * LA_EL, base = b0 + threadIdx.x;
+    const bool whole = b0 + LA_NTH * LA_EL <= n;
+    // coefficient v in lane v of every wave
+    double hl = 0.0, acc[LA_EL], a[G][LA_EL], b[G][LA_EL];
+    if constexpr (!SELF) hl = mbr(h, ms)[min(lane, nv - 1)];
+    auto load = [&](int v0, double (&x)[G][LA_EL]) {   // (beyond nv: the last vector, not used)
+        if (whole) {
+#pragma unroll
+            for (int q = 0; q < G; ++q) ld_els(V + (long)min(v0 + q, nv - 1) * ld, base, x[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+#pragma unroll
+                for (int k = 0; k < LA_EL; ++k)
+                    x[q][k] = la_el(base, k) < n ? V[(long)min(v0 + q, nv - 1) * ld + la_el(base, k)] : 0.0;
+        }
+    };
+    if (whole) {
+        ld_els(w, base, acc);
+    } else {
+#pragma unroll
+        for (int k = 0; k < LA_EL; ++k) acc[k] = la_el(base, k) < n ? w[la_el(base, k)] : 0.0;
+    }
+    load(0, a);
+    bool dots2 = false;
     if constexpr (SELF) {
+        __shared__ double hs[64];
         hpart = mbr(hpart, ms);
-        const int lane = threadIdx.x & 63;
         for (int q = threadIdx.x >> 6; q < nv; q += LA_NTH / 64) {
-            double a = 0.0;
-            for (int i = lane; i < hnb; i += 64) a += hpart[(long)q * hnb + i];
-            a = wave_sum(a);
-            if (lane == 0) hs[q] = a;
+            double t = 0.0;
+            for (int i = lane; i < hnb; i += 64) t += hpart[(long)q * hnb + i];
+            t = wave_sum(t);
+            if (lane == 0) hs[q] = t;
         }
         __syncthreads();
-        if (blockIdx.x == 0 && (int)threadIdx.x < nv) mbr(hout, ms)[threadIdx.x] = hs[threadIdx.x];
-    } else {
-        h = mbr(h, ms);
-    }
-    auto coef = [&](int v) { if constexpr (SELF) return hs[v]; else return h[v]; };
-    const long base = (long)blockIdx.x * LA_NTH * LA_EL + threadIdx.x;
-    double acc[LA_EL];
-#pragma unroll
-    for (int k = 0; k < LA_EL; ++k) {
-        const long i = base + (long)k * LA_NTH;
-        acc[k] = i < n ? w[i] : 0.0;
-    }
-    int v = 0;
-    if (base - threadIdx.x + LA_NTH * LA_EL <= n) {
-        // whole block: four basis vectors at a time, every load issued before the
-        // products (the same products in the same order as below)
-        for (; v + 4 <= nv; v += 4) {
-            double vv[4][LA_EL];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int k = 0; k < LA_EL; ++k) vv[r][k] = V[(long)(v + r) * ld + base + (long)k * LA_NTH];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double hv = coef(v + r);
-#pragma unroll
-                for (int k = 0; k < LA_EL; ++k) acc[k] -= hv * vv[r][k];
-            }
+        hl = hs[min(lane, nv - 1)];
+        if (blockIdx.x == 0 && (int)threadIdx.x < nv) mbr(hout, ms)[threadIdx.x] = hl;
+    } else if (dots) {
+        // gate_after from the coefficients that every wave holds
+        const double before = ldv(g2.h + g2.nv);
+        const double after = before - wave_sum(lane < nv ? hl * hl : 0.0);
+        dots2 = after < g2.tau2 * before;   // gate_open's decision
+        if (!dots2 && blockIdx.x == 0) {
+            if (threadIdx.x == 0) pub.out[0] = after;
+            for (int i = threadIdx.x; i < pub.ns; i += LA_NTH)
+                pub.host[i] = (i == pub.idx)                             ? after
+                              : (i == pub.fidx)                          ? 0.0
+                              : (i >= pub.zoff && i < pub.zoff + pub.zn) ? 0.0
+                                                                         : pub.src[i];
         }
     }
-    for (; v < nv; ++v) {
-        const double hv = coef(v);
-        const double* Vi = V + (long)v * ld;
+    auto coef = [&](int v) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, hl);
+        const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, v), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), v);
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    };
+    auto subtract = [&](int v0, const double (&x)[G][LA_EL]) {
 #pragma unroll
-        for (int k = 0; k < LA_EL; ++k) {
-            const long i = base + (long)k * LA_NTH;
-            if (i < n) acc[k] -= hv * Vi[i];
+        for (int q = 0; q < G; ++q) {
+            const double hv = v0 + q < nv ? coef(min(v0 + q, nv - 1)) : 0.0;
+            if (v0 + q < nv)
+#pragma unroll
+                for (int k = 0; k < LA_EL; ++k) acc[k] -= hv * x[q][k];
         }
+    };
+    for (int v0 = 0; v0 < nv; v0 += 2 * G) {   // the next group's loads in flight
+        if (v0 + G < nv) load(v0 + G, b);
+        subtract(v0, a);
+        if (v0 + G >= nv) break;
+        if (v0 + 2 * G < nv) load(v0 + 2 * G, a);
+        subtract(v0 + G, b);
     }
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < LA_EL; ++k) {
-        const long i = base + (long)k * LA_NTH;
-        if (i < n) {
-            w[i] = acc[k];
+        if (la_el(base, k) < n) {
+            w[la_el(base, k)] = acc[k];
             s += acc[k] * acc[k];
         }
     }
@@ -299,12 +334,12 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
         __syncthreads();
         if (!last) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every work-group's partial after its count
-        double a = 0.0;
-        for (int i = threadIdx.x; i < (int)gridDim.x; i += LA_NTH) a += red.partials[i];
-        a = block_sum<LA_NTH>(a, sh);   // in thread 0
+        double t = 0.0;
+        for (int i = threadIdx.x; i < (int)gridDim.x; i += LA_NTH) t += red.partials[i];
+        t = block_sum<LA_NTH>(t, sh);   // in thread 0
         if (threadIdx.x == 0) {
-            pub.out[0] = a;
-            total = a;
+            pub.out[0] = t;
+            total = t;
             atomicExch(pub.cnt, 0ull);
         }
         __syncthreads();
@@ -314,41 +349,22 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     }
     if (!dots2) return;
     dots = mbr(dots, ms);
-    constexpr int NW = LA_NTH / 64, G = 4;
+    constexpr int NW = LA_NTH / 64;
     __shared__ double sd[NW][G];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const bool whole = base - threadIdx.x + LA_NTH * LA_EL <= n;
+    const int wid = threadIdx.x >> 6;
+    if (!whole) {   // (entries beyond the vector: zeros)
+#pragma unroll
+        for (int k = 0; k < LA_EL; ++k) acc[k] = la_el(base, k) < n ? acc[k] : 0.0;
+    }
     for (int v0 = 0; v0 < nv; v0 += G) {
-        double a[G];
-#pragma unroll
-        for (int q = 0; q < G; ++q) a[q] = 0.0;
-        if (whole && v0 + G <= nv) {
-            double vv[LA_EL][G];
-#pragma unroll
-            for (int k = 0; k < LA_EL; ++k)
-#pragma unroll
-                for (int q = 0; q < G; ++q) vv[k][q] = V[(long)(v0 + q) * ld + base + (long)k * LA_NTH];
-#pragma unroll
-            for (int k = 0; k < LA_EL; ++k)
-#pragma unroll
-                for (int q = 0; q < G; ++q) a[q] += acc[k] * vv[k][q];
-        } else {
-#pragma unroll
-            for (int k = 0; k < LA_EL; ++k) {
-                const long i = base + (long)k * LA_NTH;
-                if (i < n) {
-#pragma unroll
-                    for (int q = 0; q < G; ++q)
-                        if (v0 + q < nv) a[q] += acc[k] * V[(long)(v0 + q) * ld + i];
-                }
-            }
-        }
+        load(v0, a);
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-            if (v0 + q < nv) {
-                const double t = wave_sum(a[q]);
-                if (lane == 0) sd[wid][q] = t;
-            }
+            double t = 0.0;
+#pragma unroll
+            for (int k = 0; k < LA_EL; ++k) t += acc[k] * a[q][k];
+            t = wave_sum(t);
+            if (lane == 0) sd[wid][q] = t;
         }
         __syncthreads();
         if ((int)threadIdx.x < G && v0 + (int)threadIdx.x < nv) {
@@ -361,12 +377,11 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     }
 }
 
-void launch_update(double* w, const double* V, long ld, int nv, long n, const double* h, Red red, hipStream_t st,
-                   Gate gate, const Mb& mb, Gate g2, double* dots, const Publish& pub)
+void launch_update(double* w, const double* V, long ld, int nv, long n, const double* h, hipStream_t st, const Mb& mb,
+                   Gate g2, double* dots, const Publish& pub)
 {
-    timed_launch(update_kernel<false>, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, h, gate,
-                 red, mb.ms, mb.tab, (const double*)nullptr, 0, (double*)nullptr, g2, dots, pub);
-    if (red.out) launch_finalize(red.partials, la_blocks(n), 1, red.out, st, Gate{}, mb);
+    timed_launch(update_kernel<false>, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, h, Gate{},
+                 Red{nullptr, nullptr}, mb.ms, mb.tab, (const double*)nullptr, 0, (double*)nullptr, g2, dots, pub);
 }
 
 void launch_update2_publish(double* w, const double* V, long ld, int nv, long n, Gate gate, const double* hpart,
