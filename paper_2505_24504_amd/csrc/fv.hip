@@ -40,99 +40,97 @@ enum { FVM_LIN = 0, FVM_STAGE = 1, FVM_MATVEC = 2, FVM_DEFECT = 3, FVM_STAGE_PC 
 // z-faces are handed out from the last thread down, so that the threads with a
 // second x-face are not those with a second z-face.  Default: fv_default_tile.
 
+// HLLC flux (Toro) for the normal +e_D without the face's background pressure (the
+// pressures less pb enter wherever the pressure is added; see the file comment), Davis wave
+// speeds.  On the side K of the contact: F_0 = rho*_K S*, F_D = F_0 S* + p*_K,
+// F_c = (U_c / rho)_K F_0, rho*_K = rho_K (S_K - q_K) / (S_K - S*),
+// p*_K = p_K + rho_K (S_K - q_K)(S* - q_K); S* = q_K in the supersonic cases turns the same
+// expressions into the physical flux.  18 operations fewer than the S*-factored form
+// (S*(S_K U_K - F_K) + S_K p*_K e_D) / (S_K - S*).
+template <typename T, int D>
+__device__ __forceinline__ void fv_hllc(const Gas<T>& G, const T (&UL)[4], const T (&UR)[4], T pL, T pR, T dpL, T dpR,
+                                        T irL, T irR, T (&F)[4])
+{
+    constexpr int E = 3 - D;   // tangential momentum
+    const T qL = UL[D] * irL, qR = UR[D] * irR;
+    const T cL = psqrt<T>(G.gamma * pL * irL), cR = psqrt<T>(G.gamma * pR * irR);
+    const T SL = fmin(qL - cL, qR - cR);
+    const T SR = fmax(qL + cL, qR + cR);
+    const T mL = UL[0] * (SL - qL), mR = UR[0] * (SR - qR);
+    const T Ss = (dpR - dpL + qL * mL - qR * mR) * frcp<T>(mL - mR);
+    const bool supL = SL >= T(0), supR = SR <= T(0);
+    const bool lk = supL | (!supR & (Ss >= T(0)));
+    const T SK = lk ? SL : SR, mK = lk ? mL : mR, qK = lk ? qL : qR, dpK = lk ? dpL : dpR;
+    const T uE = lk ? UL[E] * irL : UR[E] * irR, u3 = lk ? UL[3] * irL : UR[3] * irR;
+    const T S = (supL | supR) ? qK : Ss;
+    F[0] = mK * frcp<T>(SK - S) * S;
+    F[D] = F[0] * S + (dpK + mK * (S - qK));
+    F[E] = uE * F[0];
+    F[3] = u3 * F[0];
+}
+
 // Net flux through one face of a tile (HLLC minus the k = 0 interior-penalty diffusion
-// flux, along +x or +z, times the face length) from the tile's staged states; face
-// idx of the x-faces (XF) or z-faces in row-major order of the tile.
+// flux, along +x or +z) from the tile's staged states; face idx of the x-faces (XF: the low
+// faces of the tile's cells row by row, then the last column's high faces) or of the
+// z-faces (row by row).  Beyond a wall the halo holds a copy of the inside cell (and beyond
+// the domain's last cells the tile copies of them), so that a slip wall needs only the
+// mirrored state's normal momentum negated, and faces outside the domain, which no cell
+// reads, compute with finite values instead of behind a branch.
 template <typename T, int TX, int TZ, int HZ, int HX, bool XF>
 __device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ][HX], const T (&sBc)[TZ][6],
                                         const T (&sBf)[TZ + 1][10], T (&sFx)[TZ][TX + 1][4], T (&sFz)[TZ + 1][TX][4],
-                                        int I0, int J0, int nxl, int nzl, int idx)
+                                        int I0, int J0, int nxl, int nzl, bool per, int idx)
 {
     constexpr int D = XF ? 1 : 2;   // normal momentum component
-    int rl, cl, rr, cr, brow;       // LDS row/col of the low (L) and high (R) cell; background row of the tile
-    bool skip, wallL, wallR;
-    if constexpr (XF) {
-        const int jj = idx / (TX + 1), fi = idx - jj * (TX + 1);
-        const int Jf = J0 + jj, Ir = I0 + fi, Il = Ir - 1;
-        skip = (Jf >= nzl) || (Il >= nxl);
-        wallL = (Ir == 0) && A.bc != 1;
-        wallR = (Il == nxl - 1) && A.bc != 1;
-        rl = jj + 1; rr = jj + 1; cl = fi; cr = fi + 1;
-        brow = jj;
-    } else {
-        const int fj = idx / TX, ii = idx - fj * TX;
-        const int If = I0 + ii, Ja = J0 + fj, Jb = Ja - 1;
-        skip = (If >= nxl) || (Jb >= nzl);
-        wallL = (Jb < 0);
-        wallR = (Ja == nzl);
-        rl = fj; rr = fj + 1; cl = ii + 1; cr = ii + 1;
-        brow = fj;
-    }
-    T Phi[4] = {T(0), T(0), T(0), T(0)};
-    if (!skip) {
-        const T* bg = XF ? &sBc[brow][0] : &sBf[brow][0];   // Ubar, then p, 1/(rho theta)
-        const T* pr = bg + 4;
-        const bool wall = wallL || wallR;
-        // a slip wall: the missing side is the inside cell mirrored (normal momentum negated)
-        const int rlx = wallL ? rr : rl, clx = wallL ? cr : cl;
-        const int rrx = wallR ? rl : rr, crx = wallR ? cl : cr;
-        T wL[4], wR[4], UL[4], UR[4];
+    // tile row (the face's background row) and column
+    const int r = XF && idx >= TX * TZ ? idx - TX * TZ : idx / TX;
+    const int x = XF && idx >= TX * TZ ? TX : idx % TX;
+    const bool wallL = XF ? !per && I0 + x == 0 : J0 + r == 0;
+    const bool wallR = XF ? !per && I0 + x == nxl : J0 + r == nzl;
+    const T* bg = XF ? &sBc[r][0] : &sBf[XF ? 0 : r][0];   // Ubar, then p, 1/(rho theta)
+    T wL[4], wR[4], UL[4], UR[4], Phi[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            wL[c] = sw[c][rlx][clx];
-            wR[c] = sw[c][rrx][crx];
-            UL[c] = wL[c] + bg[c];
-            UR[c] = wR[c] + bg[c];
+    for (int c = 0; c < 4; ++c) {
+        wL[c] = sw[c][XF ? r + 1 : r][XF ? x : x + 1];
+        wR[c] = sw[c][r + 1][x + 1];
+        UL[c] = wL[c] + bg[c];
+        UR[c] = wR[c] + bg[c];
+    }
+    UL[D] = wallL ? -UL[D] : UL[D];
+    UR[D] = wallR ? -UR[D] : UR[D];
+    const T pb = bg[4], irb = bg[5];
+    const T rt[2] = {wL[3], wR[3]}, ir2[2] = {irb, irb}, pb2[2] = {pb, pb};
+    T dp[2];
+    pert_pressures<T, 2, true>(A.gas, rt, ir2, pb2, dp);
+    const T irL = frcp<T>(UL[0]), irR = frcp<T>(UR[0]);
+    fv_hllc<T, D>(A.gas, UL, UR, pb + dp[0], pb + dp[1], dp[0], dp[1], irL, irR, Phi);
+    if (A.physics == 1) {
+        // k = 0 diffusion: mean of mu (G_c - (U_c/rho) G_rho) over both sides, where the
+        // only gradient is the background's (z-faces), minus the interior penalty
+        // (mu/h) (dw_c - (U_c/rho)_avg dw_rho), dw = w_L - w_R, on the averaged state;
+        // none through a wall
+        const T mu = (wallL | wallR) ? T(0) : A.mu;
+        const T muh = mu / (XF ? A.hx : A.hz);
+        const T irs = frcp<T>(UL[0] + UR[0]);
+        const T* dbg = &sBf[XF ? 0 : r][6];
+        const T dw0 = (wL[0] - wR[0]) * irs;
+        const T hg0 = XF ? T(0) : T(0.5) * mu * dbg[0];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+            if constexpr (!XF) Phi[c] += hg0 * (UL[c] * irL + UR[c] * irR) - mu * dbg[c];
+            Phi[c] += muh * ((wL[c] - wR[c]) - (UL[c] + UR[c]) * dw0);
         }
-        if (wallL) UL[D] = -UL[D];
-        if (wallR) UR[D] = -UR[D];
-        const T pb = pr[0], irb = pr[1];
-        // the face's background pressure is left out of the flux (see the file comment)
-        const T rt[2] = {wL[3], wR[3]}, ir2[2] = {irb, irb}, pb2[2] = {pb, pb};
-        T dp[2];
-        pert_pressures<T, 2, true>(A.gas, rt, ir2, pb2, dp);
-        const T pL = pb + dp[0], pR = pb + dp[1];
-        const T irL = frcp<T>(UL[0]), irR = frcp<T>(UR[0]);
-        hllc_ax<T, D>(A.gas, UL, UR, pL, pR, dp[0], dp[1], irL, irR, Phi);
-        if (A.physics == 1 && !wall) {
-            // k = 0 diffusion: mean of mu (G_c - (U_c/rho) G_rho) over both sides, where the
-            // only gradient is the background's (z-faces), minus the interior penalty
-            // (mu/h) (dw_c - (U_c/rho)_avg dw_rho), dw = w_L - w_R, on the averaged state
-            const T irs = frcp<T>(UL[0] + UR[0]);
-            const T muh = A.mu / (XF ? A.hx : A.hz);
-            const T* dbg = &sBf[brow][6];
-            const T dw0 = wL[0] - wR[0];
-#pragma unroll
-            for (int c = 1; c < 4; ++c) {
-                if constexpr (!XF) {
-                    const T fl = A.mu * (dbg[c] - UL[c] * irL * dbg[0]);
-                    const T fr = A.mu * (dbg[c] - UR[c] * irR * dbg[0]);
-                    Phi[c] -= T(0.5) * (fl + fr);
-                }
-                const T rr = (UL[c] + UR[c]) * irs;
-                Phi[c] += muh * ((wL[c] - wR[c]) - rr * dw0);
-            }
-        }
-        const T elen = XF ? A.hz : A.hx;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) Phi[c] *= elen;
     }
-    if constexpr (XF) {
-        const int jj = idx / (TX + 1), fi = idx - jj * (TX + 1);
+    T* F = XF ? &sFx[XF ? r : 0][x][0] : &sFz[r][XF ? 0 : x][0];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sFx[jj][fi][c] = Phi[c];
-    } else {
-        const int fj = idx / TX, ii = idx - fj * TX;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sFz[fj][ii][c] = Phi[c];
-    }
+    for (int c = 0; c < 4; ++c) F[c] = Phi[c];
 }
 
 // FV operator on one tile of TX x TZ cells, face-centric: the perturbed states
 // w = u + eps x of the tile and a one-cell halo are staged in LDS, every face
 // of the tile gets its net flux Phi (HLLC minus the interior-penalty diffusion
 // flux, along +x or +z) exactly once, and each cell then sums its four faces:
-//   |q| f~ = -hz (Phi_{I+1/2} - Phi_{I-1/2}) - hx (Phi_{J+1/2} - Phi_{J-1/2}) - |q| g w_rho.
+//   f~ = -(Phi_{I+1/2} - Phi_{I-1/2}) / hx - (Phi_{J+1/2} - Phi_{J-1/2}) / hz - g w_rho.
 // The flux through a face seen from the other cell is the same number with
 // the opposite sign (HLLC(L,R;n) = -HLLC(R,L;-n)).
 // On the small levels a launch is one chain of latencies: of the 11300 cycles that a
@@ -142,7 +140,12 @@ __device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ]
 // its arguments at once, reads the scalars by vector loads, and issues every load before
 // it waits for the first, without a branch in between (a wait behind branches is one for
 // all loads).  FGMRES iteration of 64 x 32 elements, k = 2: 135 -> 123 us; of the density
-// current 216 -> 210 us.  Modes:
+// current 216 -> 210 us.
+// On the large levels the vector instructions bound it (56 to 75 % of the time): 856 per
+// wave in FP32 and 934 in FP64 on the 64x8 tile before, 703 and 831 with a wall's ghost
+// state in the halo instead of behind selects, each thread's own cell staged from its own
+// loads, 32-bit offsets, the shorter HLLC form and no branch around the faces.  Step of
+// 1024x256 nodes 24.2 -> 23.2 ms, of 2048x1024 (FP32 multigrid) 131.5 -> 126.7 ms.  Modes:
 //   LIN     out = F0 = f~(u); ||u + Ubar||^2 and max(|v| + c) block partials (the level
 //           slots and dtau from them: fv_lin_finalize_kernel); with out2 also the next coarser
 //           level's state R u
@@ -200,7 +203,10 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     }
     double* const zout = MB ? mbr(tv.z, ms) : tv.z;   // STAGE_TINV output (tv stays in the arguments)
     constexpr int NCELL = TX * TZ, HX = TX + 2, HZ = TZ + 2;
-    constexpr int NH = HX * HZ, HITEMS = (NH + NTH - 1) / NTH;
+    // halo cells that a face reads: the rows below and above the tile, the columns beside it
+    constexpr int RING = 2 * TX + 2 * TZ;
+    constexpr bool ONE = NTH >= NCELL + RING;   // one staged cell per thread
+    static_assert(ONE || (NTH == NCELL && NTH >= 64 + RING), "halo staging");
     constexpr int NFX = TZ * (TX + 1), NFZ = (TZ + 1) * TX;
     constexpr bool PERT = (MODE != FVM_LIN);
     constexpr bool STG = (MODE == FVM_STAGE || MODE == FVM_STAGE_PC || MODE == FVM_STAGE_TINV);
@@ -238,8 +244,29 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     // own cell (threads tid < NCELL)
     const int ti = tid % TX, tj = tid / TX;
     const int I = I0 + ti, J = J0 + tj;
-    const bool valid = tid < NCELL && I < nxl && J < nzl;
-    const long q = (long)J * nxl + I;
+    const bool cell = NTH == NCELL || tid < NCELL;
+    const bool valid = cell && I < nxl && J < nzl;
+    // halo cell r (the last one beyond the list), tile coordinates
+    const bool per = A.bc == 1;
+    auto ring_cell = [&](int r, int& i, int& j) {
+        const int s = r - 2 * TX;
+        j = r < TX ? -1 : s < 0 ? TZ : s & (TZ - 1);
+        i = s < 0 ? r & (TX - 1) : s < TZ ? -1 : TX;
+    };
+    static_assert((TX & (TX - 1)) == 0 && (TZ & (TZ - 1)) == 0, "halo staging");
+    // index of the cell at tile coordinates (i, j): beyond the domain the wrapped-round
+    // column (x-periodic) or the nearest cell
+    const int below = per ? nxl - 1 : 0, beyond = per ? 0 : nxl - 1;
+    auto cell_index = [&](int i, int j) {
+        const int Ig = I0 + i, Jg = min(max(J0 + j, 0), nzl - 1);
+        return (unsigned)(Jg * nxl + (Ig < 0 ? below : Ig >= nxl ? beyond : Ig));
+    };
+    // this thread's staged cell, its own where it has one
+    int si = ti, sj = tj;
+    if constexpr (ONE)
+        if (!cell) ring_cell(min(tid - NCELL, RING - 1), si, sj);
+    const unsigned qs = cell_index(si, sj);
+    const unsigned q = ONE ? (cell ? qs : 0u) : qs;
 
     // ---- every global load first (the ||x||^2 partials, the level's scalars and
     // background rows, the own-cell operands, then the halo states), or the own-cell
@@ -258,60 +285,65 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     // this thread's entry of sBc / sBf: the tile's rows are contiguous in the level's records
     const bool bg_c = tid < 6 * TZ;
     const int bg_i = bg_c ? tid : tid - 6 * TZ;
-    const bool bg_ok = bg_c ? bg_i < 6 * (nzl - J0) : bg_i < 10 * min(TZ + 1, nzl + 1 - J0);
+    const bool bg_ok = bg_c || bg_i < 10 * (TZ + 1);
+    // (rows beyond the level's last: the tile's first row)
+    const int bg_j = bg_c ? (bg_i < 6 * (nzl - J0) ? bg_i : bg_i % 6)
+                          : (bg_i < 10 * min(TZ + 1, nzl + 1 - J0) ? bg_i : bg_i % 10);
     const T* const bg_p = bg_c ? rc + 6L * J0 : rf + 10L * J0;
-    const T bg_v = bg_p[bg_ok ? bg_i : 0];
-    T own_x[4] = {T(0), T(0), T(0), T(0)}, own_f0[4] = {T(0), T(0), T(0), T(0)};
-    T own_b[4] = {T(0), T(0), T(0), T(0)}, own_x0[4] = {T(0), T(0), T(0), T(0)};
+    const T bg_v = bg_p[bg_j];
+    // (LATE in FP64: the cell's x is read again with them instead of held over the faces)
+    constexpr bool AGAIN = LATE && sizeof(T) == 8;
+    T su[4], own_x[4], ru[4], rx[4];
+    T own_f0[4], own_b[4], own_x0[4] = {T(0), T(0), T(0), T(0)};
     // STAGE_PC: the finer level's four children of the cell, read with the own-cell
     // operands (before any of them is written)
     T own_xf[4][4] = {};
-    // (threads without a cell read cell 0: loads behind a branch would make the wait for
-    // the partial sums one for all loads)
+    // (threads without a cell read a neighbouring one, or cell 0: loads behind a branch
+    // would make the wait for the partial sums one for all loads)
+    const unsigned nxf = 2u * (unsigned)nxl;
+    const long ncf = 4 * nc;
+    const unsigned q00 = MODE == FVM_STAGE_PC ? 4u * q - 2u * (q % (unsigned)nxl) : 0u;
     auto load_own = [&]() {
-        const long qo = valid ? q : 0;
         if constexpr (MODE == FVM_STAGE_PC)
             if (!fzero) {
-                const long nxf = 2L * nxl, ncf = 4 * nc;
-                const long q00 = valid ? (long)(2 * J) * nxf + 2 * I : 0, q10 = q00 + nxf;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const T* xf = out2 + c * ncf;
-                    own_xf[c][0] = xf[q00]; own_xf[c][1] = xf[q00 + 1];
-                    own_xf[c][2] = xf[q10]; own_xf[c][3] = xf[q10 + 1];
+                    own_xf[c][0] = ld(xf, q00); own_xf[c][1] = ld(xf, q00 + 1);
+                    own_xf[c][2] = ld(xf, q00 + nxf); own_xf[c][3] = ld(xf, q00 + nxf + 1);
                 }
             }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            if constexpr (PERT) { own_x[c] = xp[c * nc + qo]; own_f0[c] = F0[c * nc + qo]; }
-            if constexpr (STG || MODE == FVM_DEFECT) own_b[c] = b[c * nc + qo];
+            if constexpr (PERT) own_f0[c] = ld(F0 + c * nc, q);
+            if constexpr (PERT && AGAIN) own_x[c] = ld(opaque(xp) + c * nc, q);
+            if constexpr (STG || MODE == FVM_DEFECT) own_b[c] = ld(b + c * nc, q);
         }
         // the first stage of a sweep has x^(0) = x^(j-1): no second load (the copy
         // is taken where x^(0) is used, so that no load waits for another)
         if constexpr (STG)
             if (x0 && x0 != xp)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) own_x0[c] = x0[c * nc + qo];
+                for (int c = 0; c < 4; ++c) own_x0[c] = ld(x0 + c * nc, q);
     };
     if constexpr (!LATE) load_own();
-    T hu[HITEMS][4], hx[HITEMS][4];
-#pragma unroll
-    for (int it = 0; it < HITEMS; ++it) {
-        const int h = tid + it * NTH;
-        int Ih = I0 - 1 + h % HX;
-        const int Jh = J0 - 1 + h / HX;
-        // x-periodic: the column before the first and the one after the last wrap around
-        // (columns further out belong to no face)
-        const bool out_l = Ih < 0, out_r = Ih >= nxl;
-        const bool ok = h < NH && Jh >= 0 && Jh < nzl && (!(out_l || out_r) || (A.bc == 1 && Ih <= nxl));
-        Ih = out_l ? nxl - 1 : out_r ? 0 : Ih;
-        const long qh = ok ? (long)Jh * nxl + Ih : 0;   // (a cell that no face reads: cell 0's)
+    auto load_cell = [&](unsigned qc, T (&cu)[4], T (&cx)[4]) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            hu[it][c] = u[c * nc + qh];
-            if constexpr (PERT) hx[it][c] = xp[c * nc + qh];
+            cu[c] = ld(u + c * nc, qc);
+            if constexpr (PERT) cx[c] = ld(xp + c * nc, qc);
         }
-    }
+    };
+    load_cell(qs, su, own_x);
+    // the halo cells of a tile with a cell for each thread: by waves 1 and up (wave 0 has
+    // the x-faces beyond one per thread)
+    const bool ring = !ONE && tid >= 64 && tid < 64 + RING;
+    int ri = 0, rj = 0;
+    if constexpr (!ONE)
+        if (ring) {
+            ring_cell(tid - 64, ri, rj);
+            load_cell(cell_index(ri, rj), ru, rx);
+        }
     // eps = sqrt(eps_p) ||u + Ubar|| / ||x|| and adt / eps, from ||x|| and the stored 1/||u + Ubar||
     T eps = T(0), sc = T(0);
     bool xzero = false;   // uniform: g'x = 0 for x = 0
@@ -327,17 +359,16 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     }
 
     if (!xzero) {
+        auto stage = [&](int i, int j, const T (&cu)[4], const T (&cx)[4]) {
 #pragma unroll
-        for (int it = 0; it < HITEMS; ++it) {
-            const int h = tid + it * NTH;
-            if (h < NH)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    T v = hu[it][c];
-                    if constexpr (PERT) v = v + eps * hx[it][c];
-                    sw[c][h / HX][h % HX] = v;
-                }
-        }
+            for (int c = 0; c < 4; ++c) {
+                T v = cu[c];
+                if constexpr (PERT) v = v + eps * cx[c];
+                sw[c][j + 1][i + 1] = v;
+            }
+        };
+        stage(si, sj, su, own_x);   // (threads beyond the halo's last cell: that cell again)
+        if (ring) stage(ri, rj, ru, rx);
         if (bg_ok) (bg_c ? &sBc[0][0] : &sBf[0][0])[bg_i] = bg_v;
         if constexpr (TI) {
             if (tid < MAXN1 * MAXN1) sVi[tid / MAXN1][tid % MAXN1] = tv.Vinv[tid / MAXN1][tid % MAXN1];
@@ -348,7 +379,7 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
         // thread order (the threads with a second x-face are not those with a
         // second z-face) ----
         auto face = [&](auto xf_tag, int idx) {
-            fv_face<T, TX, TZ, HZ, HX, decltype(xf_tag)::value>(A, sw, sBc, sBf, sFx, sFz, I0, J0, nxl, nzl, idx);
+            fv_face<T, TX, TZ, HZ, HX, decltype(xf_tag)::value>(A, sw, sBc, sBf, sFx, sFz, I0, J0, nxl, nzl, per, idx);
         };
         for (int fx = tid; fx < NFX; fx += NTH) face(std::true_type{}, fx);
         if constexpr (ZREV)   // z-faces from the last thread down
@@ -367,13 +398,12 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
 
     // ---- per cell ----
     T f[4] = {T(0), T(0), T(0), T(0)};
-    if (valid && !xzero) {
-        const T iarea = A.iarea;
+    if (cell && !xzero) {
+        const T ihx = A.hz * A.iarea, ihz = A.hx * A.iarea;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            T L = -(sFx[tj][ti + 1][c] - sFx[tj][ti][c]) - (sFz[tj + 1][ti][c] - sFz[tj][ti][c]);
-            if (c == 2) L += A.area * (-A.g * sw[0][tj + 1][ti + 1]);
-            f[c] = L * iarea;
+            f[c] = -(sFx[tj][ti + 1][c] - sFx[tj][ti][c]) * ihx - (sFz[tj + 1][ti][c] - sFz[tj][ti][c]) * ihz;
+            if (c == 2) f[c] -= A.g * sw[0][tj + 1][ti + 1];
         }
     }
     if constexpr (MODE == FVM_LIN) {
@@ -392,8 +422,8 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
             T Ut[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                out[c * nc + q] = f[c];   // F0
-                Ut[c] = u[c * nc + q] + A.rc[6 * J + c];
+                st(out + c * nc, q, f[c]);   // F0
+                Ut[c] = su[c] + sBc[tj][c];
                 ss += (double)Ut[c] * (double)Ut[c];
             }
             const double rho = Ut[0], uu = Ut[1] / rho, ww = Ut[2] / rho;
@@ -411,14 +441,14 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
         return;
     } else {
         T Ax[4] = {T(0), T(0), T(0), T(0)};
-        if (valid && !xzero) {
+        if (cell && !xzero) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) Ax[c] = own_x[c] - sc * (f[c] - own_f0[c]);
         }
         if constexpr (MODE == FVM_MATVEC) {
             if (valid)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) out[c * nc + q] = Ax[c];
+                for (int c = 0; c < 4; ++c) st(out + c * nc, q, Ax[c]);
         } else if constexpr (MODE == FVM_STAGE) {
             double nrm = 0.0;
             if (valid) {
@@ -426,7 +456,7 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const T v = (x0 == xp ? own_x[c] : own_x0[c]) + s * (own_b[c] - Ax[c]);
-                    out[c * nc + q] = v;
+                    st(out + c * nc, q, v);
                     nrm += (double)v * (double)v;
                 }
             }
@@ -435,8 +465,6 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
             double nrm = 0.0;
             if (valid) {
                 const T s = (T)(alpha_j * s_dtau);
-                const long nxf = 2L * nxl, ncf = 4 * nc;
-                const long q00 = (long)(2 * J) * nxf + 2 * I, q10 = q00 + nxf;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const T v = (x0 == xp ? own_x[c] : own_x0[c]) + s * (own_b[c] - Ax[c]);
@@ -446,8 +474,8 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
                         f00 = own_xf[c][0] - v; f01 = own_xf[c][1] - v;
                         f10 = own_xf[c][2] - v; f11 = own_xf[c][3] - v;
                     }
-                    xf[q00] = f00; xf[q00 + 1] = f01;
-                    xf[q10] = f10; xf[q10 + 1] = f11;
+                    st(xf, q00, f00); st(xf, q00 + 1, f01);
+                    st(xf, q00 + nxf, f10); st(xf, q00 + nxf + 1, f11);
                     nrm += ((double)f00 * (double)f00 + (double)f01 * (double)f01) +
                            ((double)f10 * (double)f10 + (double)f11 * (double)f11);
                 }

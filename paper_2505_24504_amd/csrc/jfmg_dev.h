@@ -40,13 +40,16 @@ template <typename T> __device__ __forceinline__ T dsqrt(T a)
     else return sqrt(a);
 }
 // Square root of a positive normal number (sound speeds): hardware 1/sqrt
-// estimate, one coupled Goldschmidt step for g ~ sqrt(a), h ~ 1/(2 sqrt(a)),
-// then two Newton corrections g += h (a - g^2).  Without the rescaling of
-// denormal, zero and infinite arguments that the library square root carries.
+// estimate; in FP64 one coupled Goldschmidt step for g ~ sqrt(a), h ~ 1/(2 sqrt(a)),
+// then two Newton corrections g += h (a - g^2); in FP32, where the estimate is good
+// to one ulp, one correction (5 operations instead of the library's 16).  Without the
+// rescaling of denormal, zero and infinite arguments that the library square root carries.
 template <typename T> __device__ __forceinline__ T psqrt(T a)
 {
     if constexpr (std::is_same_v<T, float>) {
-        return sqrtf(a);
+        const float y = __builtin_amdgcn_rsqf(a);
+        const float g = a * y;
+        return fmaf(fmaf(-g, g, a), 0.5f * y, g);
     } else {
         const double y = __builtin_amdgcn_rsq(a);
         double g = a * y, h = 0.5 * y;
