@@ -497,7 +497,7 @@ size_t layout(const jfmg_config& c, char* base, F&& bind)
     size_t npart = (size_t)std::max<long>({la * (m + 2), 2 * fvblk, dgblk, 2048, 4096});
     bind("scal", cv.take(NSCAL * 8), 0);
     bind("partials", cv.take(npart * 8), npart);
-    const size_t fvp = (size_t)std::max<long>(fvblk, transfer_grid(c.k, ne));   // FV stages, fused transfer
+    const size_t fvp = (size_t)std::max<long>(fvblk, transfer_grid(c.k, ne)) + 1;   // FV stages, fused transfer; their sum
     bind("fvpart", cv.take(fvp * FVP_PER_LEVEL * c.mg_levels * 8), fvp);
     bind("bg_node", cv.take((size_t)c.nz * n1 * 4 * 8), 0);
     bind("dbg_node", cv.take((size_t)c.nz * n1 * 4 * 8), 0);

@@ -20,6 +20,7 @@
 
 namespace jfmg {
 
+constexpr int FV_SUM_MAX = 3072;   // partials that a consumer sums itself
 constexpr int FV_TX = 64, FV_TZ = 4, FV_NTH = FV_TX * FV_TZ;
 
 enum { FVM_LIN = 0, FVM_STAGE = 1, FVM_MATVEC = 2, FVM_DEFECT = 3, FVM_STAGE_PC = 4, FVM_STAGE_TINV = 5 };
@@ -599,6 +600,18 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     }
 }
 
+// The sum of n partials, in the order of a consumer of NTH threads, to p[n]: that entry alone
+// gives the consumer the same bits.
+template <int NTH>
+__global__ void __launch_bounds__(NTH) fv_sum_kernel(double* __restrict__ p, int n, long ms)
+{
+    p = mbr(p, ms);
+    PartialSum<NTH> x;
+    x.load(p, n);
+    const double s = x.sum(p, n);
+    if (threadIdx.x == 0) p[n] = s;
+}
+
 // first stage of a sweep from x = 0: out = alpha_1 dtau b, with ||out||^2
 template <typename T, bool RG>
 __global__ void __launch_bounds__(256)
@@ -778,6 +791,15 @@ static int tile_launch_shape(const FvArgs<T>& A, const T* u, const T* F0, const 
 {
     const unsigned nt = (unsigned)((A.nxl + TX - 1) / TX) * (unsigned)((A.nzl + TZ - 1) / TZ);
     const dim3 g(nt, 1, (unsigned)mb.n);
+    // Every work-group sums all partials of ||x||^2 by itself, which saves a launch (3 us)
+    // while they are few; 4608 of them, read by as many work-groups, made the second stage of
+    // 2.4 M cells take 82 us where the one after 1024 partials took 45: one launch before it.
+    if (MODE != FVM_LIN && xcount > FV_SUM_MAX) {
+        timed_launch(fv_sum_kernel<NTH>, dim3(1, 1, (unsigned)mb.n), dim3(NTH), st, const_cast<double*>(xpart), xcount,
+                     mb.n > 1 ? mb.ms : 0L);
+        xpart += xcount;
+        xcount = 1;
+    }
     if (mb.tab)
         timed_launch(fv_tile_kernel<T, TX, TZ, NTH, WPE, LATE, ZREV, true, MODE, true>, g, dim3(NTH), st, A, mb.tab, u,
                      F0, xp, x0, b, out, out2, xpart, xcount, slots, slots2, alpha_j, adt, fzero, red, mb.ms, tv);

@@ -380,7 +380,17 @@ template <int NTH> struct PartialSum {
             for (int k = 1; k < (NW < NV ? NW : NV); ++k) s += w[k];
         } else {
             double a = ((v[0] + v[1]) + v[2]) + v[3];
-            for (int i = threadIdx.x + NV * NTH; i < n; i += NTH) a += p[i];
+            for (int i0 = threadIdx.x + NV * NTH; i0 < n; i0 += 8 * NTH) {   // eight loads in flight
+                double x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int i = i0 + k * NTH;
+                    const double y = p[i < n ? i : 0];
+                    x[k] = i < n ? y : 0.0;
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) a += x[k];
+            }
             const int lane = threadIdx.x & 63;
             sh[threadIdx.x >> 6][lane] = a;
             __syncthreads();

@@ -42,3 +42,31 @@ def test_matvec_tile_edges(size, bc, physics):
         p.linearize(to_dev(U), adt)
         err = np.linalg.norm(to_np(p.fv_matvec(0, to_dev(x))) - want)
         assert err <= tol, (tile, err, tol)
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+def test_partials_summed_before_their_consumers(prec):
+    """More than 3072 partial sums of ||x||^2 (the density current's 1024 x 256 cells in 8x4
+    tiles: 8192) are added up by a kernel before their consumers.  A small member of a ragged
+    batch, whose partials then go that way too, keeps the bits that it has alone, where each
+    consumer adds them itself; the large one agrees with its step in 64x4 tiles (1024
+    partials) as two steps do whose Newton iterations stop at the same relative residual: to
+    ten times that residual, relative to the update."""
+    a, pert, _ = W.density_current()
+    a = dict(a, mg_precision=prec)
+    b = dict(a, nx=64, nz=16)
+    tiles = ["8x4"] * a["mg_levels"]
+    pb = jfmg.Problem([a, b], device="cuda:0")
+    pb.set_tiles(tiles)
+    U0 = [jfmg.Problem(m, device="cuda:0").initial_state(pert) for m in (a, b)]
+    U = torch.cat(U0)
+    assert pb.implicit_step(U)["status"] == 0
+    parts = [U[s] for s in pb.member_slices()]
+    for i, (m, shapes) in enumerate([(a, ["64x4"] * len(tiles)), (b, tiles)]):
+        q = jfmg.Problem(m, device="cuda:0")
+        q.set_tiles(shapes)
+        V = U0[i].clone()
+        assert q.implicit_step(V)["status"] == 0
+        rel = float((V - parts[i]).norm() / (V - U0[i]).norm())
+        print(f"fp{prec} member {i}: rel(update) {rel:.3e}", flush=True)
+        assert torch.equal(V, parts[i]) if i else rel <= 10 * a["newton_rtol"]
