@@ -804,12 +804,61 @@ template <typename T> struct Mg {
         return fused;
     }
 
+    // whether one launch takes the levels l .. nlev - 1 (a V-cycle's, with sweeps on both sides,
+    // entered with the first stage from x = 0 made by the producer of b)
+    bool tail_fits(int l, int pc) const
+    {
+        const Key& k = p->key;
+        if (l < 1 || pc != l - 1 || k.cycle != 1 || k.e < 1 || k.f < 1 || p->nlev - l > TAIL_LEV) return false;
+        if (!s.xzero[l] || s.xzero[pc] || s.pre[l] < 1 || s.pre[l] > 256) return false;
+        for (int m = l; m < p->nlev; ++m)
+            if (!fv_tail_fits(p->lev[m].nx, p->lev[m].nz, p->lev[m].tile)) return false;
+        return true;
+    }
+    void tail(int l, int pc)
+    {
+        const Key& k = p->key;
+        const int S = p->cfg.rk_stages;
+        TailArgs<T> a{};
+        a.n = p->nlev - l;
+        a.lev0 = l;
+        a.pre = k.e;
+        a.post = k.f;
+        a.S = S;
+        for (int j = 0; j < S; ++j) a.alpha[j] = alpha[j];
+        a.adt = p->adt;
+        a.A = fv_args<T>(p, l);
+        double bytes = 0.0;
+        for (int m = 0; m < a.n; ++m) {
+            Level& L = p->lev[l + m];
+            a.rc[m] = (const T*)L.rc;
+            a.rf[m] = (const T*)L.rf;
+            a.u[m] = (const T*)L.u;
+            a.F0[m] = (const T*)L.F0;
+            bytes += (m == 0 ? 11.0 : 2.0) * 4.0 * L.nc * sizeof(T);   // u, F0; the top level's b, and x_f read and written
+            p->mv_count[l + m] += (k.e + k.f) * S - 1 + (m < a.n - 1 ? 1 : 0);
+        }
+        a.slots = p->scal + S_LEV + 4 * l;
+        a.b = (const T*)p->lev[l].b;
+        a.xpart = fvpart(p, l, 1);
+        a.xcount = s.pre[l];
+        a.xf = (T*)p->lev[pc].buf[s.xi[pc]];
+        a.red = Red{fvpart(p, pc, s.xi[pc]), nullptr};
+        ProfScope ps(p, JFMG_K_FV_STAGE_SMALL, bytes);
+        p->xcnt[pc][s.xi[pc]] = FvLaunch<T>::tail(a, p->st, p->mb);
+        s.pre[l] = 0;
+    }
+
     // MG_l; with pc >= 0 the final smoother stage applies the correction of level pc
     // (see smooth); returns whether it did
     bool cycle(int l, int pc = -1)
     {
         const Key& k = p->key;
         const bool fine = (l == 0);
+        if (tail_fits(l, pc)) {
+            tail(l, pc);
+            return true;
+        }
         smooth(l, fine ? k.c : k.e);
         if (l + 1 < p->nlev) {
             const FvArgs<T> A = fv_args<T>(p, l);

@@ -70,30 +70,18 @@ __device__ __forceinline__ void fv_hllc(const Gas<T>& G, const T (&UL)[4], const
     F[3] = u3 * F[0];
 }
 
-// Net flux through one face of a tile (HLLC minus the k = 0 interior-penalty diffusion
-// flux, along +x or +z) from the tile's staged states; face idx of the x-faces (XF: the low
-// faces of the tile's cells row by row, then the last column's high faces) or of the
-// z-faces (row by row).  Beyond a wall the halo holds a copy of the inside cell (and beyond
-// the domain's last cells the tile copies of them), so that a slip wall needs only the
-// mirrored state's normal momentum negated, and faces outside the domain, which no cell
-// reads, compute with finite values instead of behind a branch.
-template <typename T, int TX, int TZ, int HZ, int HX, bool XF>
-__device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ][HX], const T (&sBc)[TZ][6],
-                                        const T (&sBf)[TZ + 1][10], T (&sFx)[TZ][TX + 1][4], T (&sFz)[TZ + 1][TX][4],
-                                        int I0, int J0, int nxl, int nzl, bool per, int idx)
+// Net flux through one face (HLLC minus the k = 0 interior-penalty diffusion flux, along +x,
+// D = 1, or +z, D = 2) from the staged states of its low and high cell.  bg: the face's
+// background Ubar, p, 1/(rho theta), dbg (z-faces) its derivative.  A slip wall's missing
+// state is a copy of the inside cell (wallL, wallR: the low, the high side's), whose normal
+// momentum is negated here.
+template <typename T, int D>
+__device__ __forceinline__ void fv_flux(const FvArgs<T>& A, const T (&wL)[4], const T (&wR)[4], const T* bg, const T* dbg,
+                                        bool wallL, bool wallR, T (&Phi)[4])
 {
-    constexpr int D = XF ? 1 : 2;   // normal momentum component
-    // tile row (the face's background row) and column
-    const int r = XF && idx >= TX * TZ ? idx - TX * TZ : idx / TX;
-    const int x = XF && idx >= TX * TZ ? TX : idx % TX;
-    const bool wallL = XF ? !per && I0 + x == 0 : J0 + r == 0;
-    const bool wallR = XF ? !per && I0 + x == nxl : J0 + r == nzl;
-    const T* bg = XF ? &sBc[r][0] : &sBf[XF ? 0 : r][0];   // Ubar, then p, 1/(rho theta)
-    T wL[4], wR[4], UL[4], UR[4], Phi[4];
+    T UL[4], UR[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        wL[c] = sw[c][XF ? r + 1 : r][XF ? x : x + 1];
-        wR[c] = sw[c][r + 1][x + 1];
         UL[c] = wL[c] + bg[c];
         UR[c] = wR[c] + bg[c];
     }
@@ -111,17 +99,40 @@ __device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ]
         // (mu/h) (dw_c - (U_c/rho)_avg dw_rho), dw = w_L - w_R, on the averaged state;
         // none through a wall
         const T mu = (wallL | wallR) ? T(0) : A.mu;
-        const T muh = mu / (XF ? A.hx : A.hz);
+        const T muh = mu / (D == 1 ? A.hx : A.hz);
         const T irs = frcp<T>(UL[0] + UR[0]);
-        const T* dbg = &sBf[XF ? 0 : r][6];
         const T dw0 = (wL[0] - wR[0]) * irs;
-        const T hg0 = XF ? T(0) : T(0.5) * mu * dbg[0];
+        const T hg0 = D == 1 ? T(0) : T(0.5) * mu * dbg[0];
 #pragma unroll
         for (int c = 1; c < 4; ++c) {
-            if constexpr (!XF) Phi[c] += hg0 * (UL[c] * irL + UR[c] * irR) - mu * dbg[c];
+            if constexpr (D == 2) Phi[c] += hg0 * (UL[c] * irL + UR[c] * irR) - mu * dbg[c];
             Phi[c] += muh * ((wL[c] - wR[c]) - (UL[c] + UR[c]) * dw0);
         }
     }
+}
+
+// The flux through face idx of a tile's x-faces (XF: the low faces of the cells row by row,
+// then the last column's high faces) or z-faces (row by row).  Beyond a wall the halo holds a
+// copy of the inside cell (and beyond the domain's last cells the tile copies of them), so
+// that faces outside the domain, which no cell reads, compute with finite values instead of
+// behind a branch.
+template <typename T, int TX, int TZ, int HZ, int HX, bool XF>
+__device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ][HX], const T (&sBc)[TZ][6],
+                                        const T (&sBf)[TZ + 1][10], T (&sFx)[TZ][TX + 1][4], T (&sFz)[TZ + 1][TX][4],
+                                        int I0, int J0, int nxl, int nzl, bool per, int idx)
+{
+    // tile row (the face's background row) and column
+    const int r = XF && idx >= TX * TZ ? idx - TX * TZ : idx / TX;
+    const int x = XF && idx >= TX * TZ ? TX : idx % TX;
+    const bool wallL = XF ? !per && I0 + x == 0 : J0 + r == 0;
+    const bool wallR = XF ? !per && I0 + x == nxl : J0 + r == nzl;
+    T wL[4], wR[4], Phi[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        wL[c] = sw[c][XF ? r + 1 : r][XF ? x : x + 1];
+        wR[c] = sw[c][r + 1][x + 1];
+    }
+    fv_flux<T, XF ? 1 : 2>(A, wL, wR, XF ? &sBc[XF ? r : 0][0] : &sBf[r][0], &sBf[XF ? 0 : r][6], wallL, wallR, Phi);
     T* F = XF ? &sFx[XF ? r : 0][x][0] : &sFz[r][XF ? 0 : x][0];
 #pragma unroll
     for (int c = 0; c < 4; ++c) F[c] = Phi[c];
@@ -600,6 +611,294 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     }
 }
 
+// The coarsest levels of a V-cycle in one launch, one work-group per member: pre-smoothing,
+// defect, the coarser levels and post-smoothing of at most TAIL_LEV levels, and the correction
+// of the next finer level's x with its ||x_f||^2 partials.  On such a level a launch is one
+// chain of latencies, 4.3 us whatever its size and the gap to the next one; here a stage is
+// three barriers of one work-group, and states, right-hand sides and fluxes stay in LDS.  One
+// thread per face, one per cell in the order of the 8x4 tiles' threads (half a wave per tile);
+// the arithmetic and the order of every sum are those of the 8x4 tile kernels, so that it does
+// not matter to the bits which of the two a level takes.  On entry the top level's first stage
+// from x = 0 has its ||x||^2 partials at xpart (written with b by the producer).
+// FP64, 16x16 and 8x8 cells, three stages: 62 us for the 24 launches' 104 (implicit Euler step
+// of that problem 12.6 -> 9.3 ms); FP32, 24x12 cells, one stage: 12.4 us for 13 of three
+// launches, without their gaps (step 15.8 -> 15.1 ms).
+template <typename T, bool RG>
+__global__ void __launch_bounds__(TAIL_NTH)
+fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
+{
+    __shared__ T sw[4 * TAIL_HALO];             // staged states [component][row][column] with a halo, or defects
+    __shared__ T sF[TAIL_NTH][4];               // fluxes, by thread
+    __shared__ T sV[16 * TAIL_SUM];             // per level [u, F0, b, x][component][cell]
+    __shared__ T sBc[2 * TAIL_ROWS][6], sBf[2 * TAIL_ROWS + TAIL_LEV][10];   // the levels' background rows
+    __shared__ double sS[TAIL_LEV][4], part[32];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const Red red = mbr(a.red, ms);
+    if (RG && sits_out(mt)) {
+        if (tid < a.nparts) red.partials[tid] = 0.0;
+        return;
+    }
+    const double* const xpart = mbr(a.xpart, ms);
+    PartialSum<128> xsum;
+    xsum.load(xpart, a.xcount);
+    // The arguments of the top level; the coarser ones' differ by powers of two only.
+    FvArgs<T> A;
+    if constexpr (RG) A = fv_entry<T>(mt, a.lev0);
+    else A = a.A;
+    const T top_hx = A.hx, top_hz = A.hz, top_ia = A.iarea;
+    const bool per = A.bc == 1;
+    // everything that the levels need from memory
+    {
+        const T* b = (const T*)(gptr<T>)mbr(a.b, ms);
+        int o = 0, oc = 0, of = 0;
+#pragma unroll
+        for (int l = 0; l < TAIL_LEV; ++l) {
+            if (l < a.n) {
+                const int nz = A.nzl >> l, n4 = 4 * (A.nxl >> l) * nz;
+                const T *rc = a.rc[l], *rf = a.rf[l];
+                if constexpr (RG) {
+                    rc = fv_entry<T>(mt, a.lev0 + l).rc;
+                    rf = fv_entry<T>(mt, a.lev0 + l).rf;
+                }
+                rc = (const T*)(gptr<T>)rc;
+                rf = (const T*)(gptr<T>)rf;
+                const T *u = (const T*)(gptr<T>)mbr(a.u[l], ms), *F0 = (const T*)(gptr<T>)mbr(a.F0[l], ms);
+                for (int i = tid; i < n4; i += TAIL_NTH) {
+                    sV[o + i] = u[i];
+                    sV[o + n4 + i] = F0[i];
+                    if (l == 0) sV[o + 2 * n4 + i] = b[i];
+                }
+                for (int i = tid; i < 6 * nz; i += TAIL_NTH) (&sBc[oc][0])[i] = rc[i];
+                for (int i = tid; i < 10 * (nz + 1); i += TAIL_NTH) (&sBf[of][0])[i] = rf[i];
+                o += 4 * n4;
+                oc += nz;
+                of += nz + 1;
+            }
+        }
+        if (tid < 4 * a.n) (&sS[0][0])[tid] = (mbr(a.slots, ms))[tid];
+    }
+    // the level, and this thread's cell of it
+    int nxl, nzl, nc, nt, I, J, q, off, hx, hn, oc, of, flo, frow, fx, fz;
+    bool valid, xf, face, fwl, fwr;
+    double utot, iutot, dtau;
+    auto enter = [&](int l) __attribute__((always_inline)) {
+        nxl = A.nxl >> l;
+        nzl = A.nzl >> l;
+        nc = nxl * nzl;
+        off = oc = of = 0;
+        for (int m = 0; m < l; ++m) {
+            off += 16 * (A.nxl >> m) * (A.nzl >> m);
+            oc += A.nzl >> m;
+            of += (A.nzl >> m) + 1;
+        }
+        const T two = (T)(1 << l);
+        A.hx = top_hx * two;
+        A.hz = top_hz * two;
+        A.iarea = top_ia * (T(1) / (two * two));
+        const int ntx = (nxl + 7) / 8;
+        nt = ntx * ((nzl + 3) / 4);
+        const int g = tid >> 5, tile = g < nt ? (int)xcd_tile(g, nt) : 0;
+        I = (tile % ntx) * 8 + (tid & 7);
+        J = (tile / ntx) * 4 + ((tid >> 3) & 3);
+        valid = g < nt && I < nxl && J < nzl;
+        I = valid ? I : 0;
+        J = valid ? J : 0;
+        q = J * nxl + I;
+        hx = nxl + 2;
+        hn = hx * (nzl + 2);
+        // this thread's face: x-faces from thread 0, z-faces from the next wave on
+        const int nxf = (nxl + 1) * nzl, nxp = (nxf + 63) & ~63, nzf = nxl * (nzl + 1);
+        xf = __builtin_amdgcn_readfirstlane(tid) < nxp;
+        const int k = xf ? tid : tid - nxp, fw = xf ? nxl + 1 : nxl;
+        const int r = k / fw, cc = k - r * fw;
+        face = k < (xf ? nxf : nzf);
+        flo = xf ? (r + 1) * hx + cc : r * hx + cc + 1;
+        frow = xf ? oc + r : of + r;
+        fwl = xf ? !per && cc == 0 : r == 0;
+        fwr = xf ? !per && cc == nxl : r == nzl;
+        fx = J * (nxl + 1) + I;
+        fz = nxp + q;
+        utot = sS[l][LV_UTOT];
+        iutot = sS[l][LV_IUTOT];
+        dtau = sS[l][LV_DTAU];
+    };
+    auto vec = [&](int k, int c, int i) -> T& { return sV[off + (4 * k + c) * nc + i]; };   // k: 0 u, 1 F0, 2 b, 3 x
+    // sum of v over the level's cells from the tiles' sums, every thread; a barrier inside
+    auto tile_sums = [&](double v, double* out) {
+        v += dpp_move<0x111, 0xf>(v);
+        v += dpp_move<0x112, 0xf>(v);
+        v += dpp_move<0x114, 0xf>(v);
+        v += dpp_move<0x118, 0xf>(v);
+        v += dpp_move<0x142, 0xa>(v);
+        if ((tid & 31) == 31 && (tid >> 5) < nt) out[tid >> 5] = v;
+    };
+    auto total = [&](double v) {
+        tile_sums(v, part);
+        __syncthreads();
+        return wave_sum(lane < nt ? part[lane] : 0.0);
+    };
+    // g'x of this thread's cell (the states staged in sw)
+    T x[4], Ax[4];
+    auto apply = [&](double xn2) __attribute__((always_inline)) {
+        if (!(xn2 > 0.0)) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Ax[c] = T(0);
+            __syncthreads();
+            return;
+        }
+        const double xn = psqrt(xn2);
+        const T eps = (T)(FdEps<T>::sqrt_eps * utot * frcp(xn));
+        const T sc = (T)(a.adt * xn * (FdEps<T>::inv_sqrt_eps * iutot));
+        const int h = (J + 1) * hx + I + 1;
+        if (valid)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const T w = vec(0, c, q) + eps * x[c];
+                T* s = sw + c * hn + h;
+                *s = w;
+                if (J == 0) s[-hx] = w;
+                if (J == nzl - 1) s[hx] = w;
+                if (I == 0) s[per ? nxl : -1] = w;
+                if (I == nxl - 1) s[per ? -nxl : 1] = w;
+            }
+        __syncthreads();
+        if (face) {
+            T wL[4], wR[4], Phi[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                wL[c] = sw[c * hn + flo];
+                wR[c] = sw[c * hn + flo + (xf ? 1 : hx)];
+            }
+            if (xf) fv_flux<T, 1>(A, wL, wR, &sBc[frow][0], &sBf[0][6], fwl, fwr, Phi);
+            else fv_flux<T, 2>(A, wL, wR, &sBf[frow][0], &sBf[frow][6], fwl, fwr, Phi);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sF[tid][c] = Phi[c];
+        }
+        __syncthreads();
+        const T ihx = A.hz * A.iarea, ihz = A.hx * A.iarea;
+        if (valid)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                T f = -(sF[fx + 1][c] - sF[fx][c]) * ihx - (sF[fz + nxl][c] - sF[fz][c]) * ihz;
+                if (c == 2) f -= A.g * sw[h];
+                Ax[c] = x[c] - sc * (f - vec(1, c, q));
+            }
+    };
+    int l = 0;
+    const double xn2_0 = xsum.sum(xpart, a.xcount);
+    __syncthreads();
+    enter(0);
+    double xn2 = xn2_0;
+    T x0[4];   // at the sweep's start
+    {
+        const T s = (T)(a.alpha[0] * dtau);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            x[c] = s * vec(2, c, q);
+            x0[c] = T(0);
+        }
+    }
+    bool post = false;
+    for (int sweep = 0, j = 1;;) {   // one product g'x per turn: of a stage, or of the defect after the pre-smoothing
+        if (j == a.S) {
+            ++sweep;
+            j = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x0[c] = x[c];
+        }
+        const bool done = !post && sweep == a.pre, defect = done && l < a.n - 1;
+        if (done && !defect) {
+            post = true;
+            sweep = 0;
+        }
+        apply(xn2);
+        if (defect) {
+            // down: the coarse level's b = R(g'x - b) and its first stage from zero
+            T d[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) d[c] = Ax[c] - vec(2, c, q);
+            __syncthreads();   // the staged states are read no more
+            if (valid)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    vec(3, c, q) = x[c];
+                    sw[c * nc + q] = d[c];
+                }
+            __syncthreads();
+            const int fnx = nxl, fnc = nc;
+            auto coarse = [&](int c, int o) {
+                const T* p = sw + c * fnc + o;
+                return ((p[0] + p[1]) + (p[fnx] + p[fnx + 1])) * T(0.25);
+            };
+            // the stage's norm as this level's tiles sum it
+            const T s1 = (T)(a.alpha[0] * sS[l + 1][LV_DTAU]);
+            double nrm = 0.0;
+            if (valid && !(I & 1) && !(J & 1))
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const T v = s1 * coarse(c, q);
+                    nrm += (double)v * (double)v;
+                }
+            xn2 = total(nrm);
+            ++l;
+            enter(l);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const T r = coarse(c, 2 * J * fnx + 2 * I);
+                if (valid) vec(2, c, q) = r;
+                x[c] = s1 * r;
+                x0[c] = T(0);
+            }
+            sweep = 0;
+            j = 1;
+            __syncthreads();   // (the defects are read no more)
+            continue;
+        }
+        const T s = (T)(a.alpha[j] * dtau);
+        double nrm = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const T v = x0[c] + s * (vec(2, c, q) - Ax[c]);
+            x[c] = v;
+            nrm += (double)v * (double)v;
+        }
+        ++j;
+        if (!(post && sweep == a.post - 1 && j == a.S)) {
+            xn2 = total(valid ? nrm : 0.0);
+            continue;
+        }
+        // up: the last result corrects the finer level's x
+        const int ncf = 4 * nc, nxf = 2 * nxl, q00 = 2 * J * nxf + 2 * I;
+        nrm = 0.0;
+        auto correct = [&](T* xf) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                T* p = xf + c * ncf + q00;
+                const T v = x[c];
+                const T f00 = p[0] - v, f01 = p[1] - v, f10 = p[nxf] - v, f11 = p[nxf + 1] - v;
+                p[0] = f00; p[1] = f01;
+                p[nxf] = f10; p[nxf + 1] = f11;
+                nrm += ((double)f00 * (double)f00 + (double)f01 * (double)f01) +
+                       ((double)f10 * (double)f10 + (double)f11 * (double)f11);
+            }
+        };
+        if (l == 0) {
+            if (valid) correct(mbr(a.xf, ms));
+            tile_sums(nrm, red.partials);
+            if (tid >= nt && tid < a.nparts) red.partials[tid] = 0.0;
+            return;
+        }
+        if (valid) correct(sV + off - 4 * ncf);
+        xn2 = total(nrm);
+        --l;
+        enter(l);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x0[c] = x[c] = vec(3, c, q);
+        sweep = 0;
+        j = 0;
+    }
+}
+
 // The sum of n partials, in the order of a consumer of NTH threads, to p[n]: that entry alone
 // gives the consumer the same bits.
 template <int NTH>
@@ -976,6 +1275,24 @@ long fv_partial_blocks(long nxl, long nzl)
     const long smallest = ((nxl + 7) / 8) * ((nzl + 3) / 4);
     const long pro = ((nxl + FV_TX - 1) / FV_TX) * ((nzl + FV_TZ - 1) / FV_TZ);
     return std::max(std::max(smallest, pro), 1024L);
+}
+// Levels that the tail kernel takes: its LDS holds them, and the work-group has a thread for
+// each face.
+bool fv_tail_fits(int nxl, int nzl, int tile)
+{
+    const int nt = ((nxl + 7) / 8) * ((nzl + 3) / 4);
+    return tile == JFMG_TILE_8x4 && nxl * nzl <= TAIL_CELLS && nt <= TAIL_NTH / 32 && nzl <= TAIL_ROWS &&
+           (nxl + 2) * (nzl + 2) <= TAIL_HALO && (((nxl + 1) * nzl + 63) & ~63) + nxl * (nzl + 1) <= TAIL_NTH;
+}
+template <typename T> int FvLaunch<T>::tail(const TailArgs<T>& a0, hipStream_t st, const Mb& mb)
+{
+    TailArgs<T> a = a0;
+    a.nparts = ((a.A.nxl + 7) / 8) * ((a.A.nzl + 3) / 4);
+    const dim3 g(1, 1, (unsigned)mb.n);
+    const long ms = mb.n > 1 ? mb.ms : 0L;
+    if (mb.tab) timed_launch(fv_tail_kernel<T, true>, g, dim3(TAIL_NTH), st, a, mb.tab, ms);
+    else timed_launch(fv_tail_kernel<T, false>, g, dim3(TAIL_NTH), st, a, mb.tab, ms);
+    return a.nparts;
 }
 template <typename T> int FvLaunch<T>::norm_blocks(long n)
 {

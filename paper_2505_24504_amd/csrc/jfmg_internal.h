@@ -286,6 +286,25 @@ struct LinLevels {
     double hx[MAXLEV], hz[MAXLEV];
 };
 
+// The coarsest levels of a V-cycle in one launch (fv_tail_kernel): limits of a level, and the
+// sum of the levels' cells (each a quarter of the one before).
+constexpr int TAIL_LEV = 3, TAIL_NTH = 640, TAIL_CELLS = 320, TAIL_SUM = 420, TAIL_ROWS = 64, TAIL_HALO = 512;
+bool fv_tail_fits(int nxl, int nzl, int tile);
+template <typename T> struct TailArgs {
+    int n, lev0;           // levels, the first one's index
+    int pre, post, S;      // sweeps before and after the coarser levels, stages of a sweep
+    double alpha[4], adt;
+    FvArgs<T> A;           // of level lev0
+    const T *u[TAIL_LEV], *F0[TAIL_LEV], *rc[TAIL_LEV], *rf[TAIL_LEV];
+    const double* slots;   // of level lev0, the others' behind it
+    const T* b;            // the top level's right-hand side
+    const double* xpart;   // ||x||^2 partials of its first stage from x = 0
+    int xcount;
+    T* xf;                 // the next finer level's x
+    Red red;               // ||x_f||^2 partials
+    int nparts;            // their number (set by the launcher)
+};
+
 template <typename T> struct FvLaunch {
     // F0 = f~(u) and the block partials of ||u + Ubar||^2 and max |v| + c (2 x the returned
     // count at red.partials); with uc != nullptr also uc = R u, the next coarser level's state
@@ -320,6 +339,9 @@ template <typename T> struct FvLaunch {
     static int defect_restrict(const FvArgs<T>& A, const T* u, const T* F0, const T* x, const T* b, T* rc,
                                const double* xpart, int xcount, const double* slots, double adt, int zero,
                                hipStream_t st, const Mb& mb = Mb{}, const ZeroStage<T>& z0 = ZeroStage<T>{});
+    // levels lev0 .. lev0 + n - 1 of a V-cycle from the top level's first stage to the
+    // correction of the finer level's x; returns the number of ||x_f||^2 partials
+    static int tail(const TailArgs<T>& a, hipStream_t st, const Mb& mb = Mb{});
     static int prolong_correct(const FvArgs<T>& Af, T* x, const T* v, Red red, hipStream_t st, const Mb& mb = Mb{});
     static void restrict_(const FvArgs<T>& Af, const T* f, T* c, hipStream_t st, const Mb& mb = Mb{});
     static void prolong(const FvArgs<T>& Af, const T* c, T* f, hipStream_t st, const Mb& mb = Mb{});

@@ -70,3 +70,38 @@ def test_partials_summed_before_their_consumers(prec):
         rel = float((V - parts[i]).norm() / (V - U0[i]).norm())
         print(f"fp{prec} member {i}: rel(update) {rel:.3e}", flush=True)
         assert torch.equal(V, parts[i]) if i else rel <= 10 * a["newton_rtol"]
+
+
+# (k, nx, nz, levels, stages, bc, physics, precision): the coarser levels, small enough for one
+# launch of one work-group, are 16x16 and 8x8 cells; 18x6 (behind 36x12, which is too large);
+# 12x4 and 6x2, x-periodic; 36x8, 18x4 and 9x2; 2x2, less than a tile
+TAILS = [(1, 16, 16, 3, 3, 0, 0, 64), (2, 24, 8, 3, 1, 0, 1, 32), (3, 6, 2, 3, 1, 1, 0, 64), (2, 24, 16, 4, 2, 1, 1, 32),
+         (1, 2, 2, 2, 1, 0, 0, 64)]
+
+
+@pytest.mark.parametrize("case", TAILS)
+def test_coarse_levels_in_one_launch(case):
+    """The coarsest levels of a V-cycle go in one launch where all members' fit; in a ragged
+    batch with a member whose levels do not, each level takes its own kernels.  A member's step
+    has the same bits either way."""
+    k, nx, nz, levels, stages, bc, physics, prec = case
+    h = 50.0
+    d = W.small(nx=nx, nz=nz, k=k, bc=bc, physics=physics, mu=75.0 if physics else 0.0, scheme=0, dt=0.015 * h,
+                mg_levels=levels, rk_stages=stages, mg_precision=prec, newton_rtol=1e-8, newton_stall=1e-7, gmres_m=30,
+                x0=0.0, x1=h * nx, z0=0.0, z1=h * nz)
+    big = dict(d, nx=96, nz=64, x1=h * 96, z1=h * 64)
+    members = [(big, dict(shape=0, amp=2.0, xc=48 * h, zc=30 * h, xr=20 * h, zr=20 * h)),
+               (d, dict(shape=0, amp=2.0, xc=h * nx / 2, zc=h * nz / 2, xr=h * nx / 3, zr=h * nz / 3))]
+    print(f"case {case}", flush=True)
+    pb = jfmg.Problem([m for m, _ in members], device="cuda:0")
+    tiles = ["8x4"] * levels
+    pb.set_tiles(tiles)
+    U0 = [jfmg.Problem(m, device="cuda:0").initial_state(pert) for m, pert in members]
+    U = torch.cat(U0)
+    assert pb.implicit_step(U)["status"] == 0
+    q = jfmg.Problem(d, device="cuda:0")
+    q.set_tiles(tiles)
+    V = U0[1].clone()
+    assert q.implicit_step(V)["status"] == 0
+    assert not torch.equal(V, U0[1])
+    assert torch.equal(V, U[pb.member_slices()[1]])
