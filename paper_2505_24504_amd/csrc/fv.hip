@@ -620,15 +620,16 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
 // the arithmetic and the order of every sum are those of the 8x4 tile kernels, so that it does
 // not matter to the bits which of the two a level takes.  On entry the top level's first stage
 // from x = 0 has its ||x||^2 partials at xpart (written with b by the producer).
-// FP64, 16x16 and 8x8 cells, three stages: 62 us for the 24 launches' 104 (implicit Euler step
-// of that problem 12.6 -> 9.3 ms); FP32, 24x12 cells, one stage: 12.4 us for 13 of three
-// launches, without their gaps (step 15.8 -> 15.1 ms).
+// FP64, 16x16 and 8x8 cells, three stages: 56 us for the 24 launches' 104 (implicit Euler step
+// of that problem 12.6 -> 8.9 ms); FP32, 24x12 cells, one stage: 11.5 us for 13 of three
+// launches, without their gaps (step 15.8 -> 14.9 ms).  Halo cells written behind branches
+// (a face knows its two cells instead) and one load waited for at a time made it 62 and 12.4.
 template <typename T, bool RG>
 __global__ void __launch_bounds__(TAIL_NTH)
 fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
 {
-    __shared__ T sw[4 * TAIL_HALO];             // staged states [component][row][column] with a halo, or defects
-    __shared__ T sF[TAIL_NTH][4];               // fluxes, by thread
+    __shared__ T sw[4 * TAIL_CELLS];            // staged states, or defects, [component][cell]
+    __shared__ T sF[4][TAIL_NTH];               // fluxes, by thread
     __shared__ T sV[16 * TAIL_SUM];             // per level [u, F0, b, x][component][cell]
     __shared__ T sBc[2 * TAIL_ROWS][6], sBf[2 * TAIL_ROWS + TAIL_LEV][10];   // the levels' background rows
     __shared__ double sS[TAIL_LEV][4], part[32];
@@ -647,38 +648,61 @@ fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
     else A = a.A;
     const T top_hx = A.hx, top_hz = A.hz, top_ia = A.iarea;
     const bool per = A.bc == 1;
-    // everything that the levels need from memory
+    // everything that the levels need from memory, every load before the first store
     {
+        static_assert(4 * TAIL_CELLS <= 2 * TAIL_NTH && 10 * (TAIL_ROWS + 1) <= 2 * TAIL_NTH, "staging");
+        T ru[TAIL_LEV][2], rF[TAIL_LEV][2], rb[2], rrc[TAIL_LEV], rrf[TAIL_LEV][2];
+        double rs = 0.0;
         const T* b = (const T*)(gptr<T>)mbr(a.b, ms);
+        auto fetch = [&](const T* p, int i, int n) { return p[i < n ? i : 0]; };
+#pragma unroll
+        for (int l = 0; l < TAIL_LEV; ++l) {
+            const int m = l < a.n ? l : 0;   // (a level that is not there: the first one's, not stored)
+            const int nz = A.nzl >> m, n4 = 4 * (A.nxl >> m) * nz;
+            const T *rc = a.rc[m], *rf = a.rf[m];
+            if constexpr (RG) {
+                rc = fv_entry<T>(mt, a.lev0 + m).rc;
+                rf = fv_entry<T>(mt, a.lev0 + m).rf;
+            }
+            rc = (const T*)(gptr<T>)rc;
+            rf = (const T*)(gptr<T>)rf;
+            const T *u = (const T*)(gptr<T>)mbr(a.u[m], ms), *F0 = (const T*)(gptr<T>)mbr(a.F0[m], ms);
+#pragma unroll
+            for (int k = 0; k < (l == 0 ? 2 : 1); ++k) {
+                const int i = tid + k * TAIL_NTH;
+                ru[l][k] = fetch(u, i, n4);
+                rF[l][k] = fetch(F0, i, n4);
+                if (l == 0) rb[k] = fetch(b, i, n4);
+                rrf[l][k] = fetch(rf, i, 10 * (nz + 1));
+            }
+            rrc[l] = fetch(rc, tid, 6 * nz);
+        }
+        if (tid < 4 * a.n) rs = mbr(a.slots, ms)[tid];
         int o = 0, oc = 0, of = 0;
 #pragma unroll
         for (int l = 0; l < TAIL_LEV; ++l) {
             if (l < a.n) {
                 const int nz = A.nzl >> l, n4 = 4 * (A.nxl >> l) * nz;
-                const T *rc = a.rc[l], *rf = a.rf[l];
-                if constexpr (RG) {
-                    rc = fv_entry<T>(mt, a.lev0 + l).rc;
-                    rf = fv_entry<T>(mt, a.lev0 + l).rf;
+#pragma unroll
+                for (int k = 0; k < (l == 0 ? 2 : 1); ++k) {
+                    const int i = tid + k * TAIL_NTH;
+                    if (i < n4) {
+                        sV[o + i] = ru[l][k];
+                        sV[o + n4 + i] = rF[l][k];
+                        if (l == 0) sV[o + 2 * n4 + i] = rb[k];
+                    }
+                    if (i < 10 * (nz + 1)) (&sBf[of][0])[i] = rrf[l][k];
                 }
-                rc = (const T*)(gptr<T>)rc;
-                rf = (const T*)(gptr<T>)rf;
-                const T *u = (const T*)(gptr<T>)mbr(a.u[l], ms), *F0 = (const T*)(gptr<T>)mbr(a.F0[l], ms);
-                for (int i = tid; i < n4; i += TAIL_NTH) {
-                    sV[o + i] = u[i];
-                    sV[o + n4 + i] = F0[i];
-                    if (l == 0) sV[o + 2 * n4 + i] = b[i];
-                }
-                for (int i = tid; i < 6 * nz; i += TAIL_NTH) (&sBc[oc][0])[i] = rc[i];
-                for (int i = tid; i < 10 * (nz + 1); i += TAIL_NTH) (&sBf[of][0])[i] = rf[i];
+                if (tid < 6 * nz) (&sBc[oc][0])[tid] = rrc[l];
                 o += 4 * n4;
                 oc += nz;
                 of += nz + 1;
             }
         }
-        if (tid < 4 * a.n) (&sS[0][0])[tid] = (mbr(a.slots, ms))[tid];
+        if (tid < 4 * a.n) (&sS[0][0])[tid] = rs;
     }
     // the level, and this thread's cell of it
-    int nxl, nzl, nc, nt, I, J, q, off, hx, hn, oc, of, flo, frow, fx, fz;
+    int nxl, nzl, nc, nt, I, J, q, off, oc, of, flo, fhi, frow, fx, fz;
     bool valid, xf, face, fwl, fwr;
     double utot, iutot, dtau;
     auto enter = [&](int l) __attribute__((always_inline)) {
@@ -704,15 +728,16 @@ fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
         I = valid ? I : 0;
         J = valid ? J : 0;
         q = J * nxl + I;
-        hx = nxl + 2;
-        hn = hx * (nzl + 2);
         // this thread's face: x-faces from thread 0, z-faces from the next wave on
         const int nxf = (nxl + 1) * nzl, nxp = (nxf + 63) & ~63, nzf = nxl * (nzl + 1);
         xf = __builtin_amdgcn_readfirstlane(tid) < nxp;
         const int k = xf ? tid : tid - nxp, fw = xf ? nxl + 1 : nxl;
         const int r = k / fw, cc = k - r * fw;
         face = k < (xf ? nxf : nzf);
-        flo = xf ? (r + 1) * hx + cc : r * hx + cc + 1;
+        // its low and high cell; beyond a wall the inside one (see fv_flux)
+        const int e = per ? nxl - 1 : 0;   // x-periodic: the other end
+        flo = xf ? r * nxl + (cc > 0 ? cc - 1 : e) : (r > 0 ? k - nxl : k);
+        fhi = xf ? r * nxl + (cc < nxl ? cc : nxl - 1 - e) : (r < nzl ? k : k - nxl);
         frow = xf ? oc + r : of + r;
         fwl = xf ? !per && cc == 0 : r == 0;
         fwr = xf ? !per && cc == nxl : r == nzl;
@@ -738,50 +763,49 @@ fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
         return wave_sum(lane < nt ? part[lane] : 0.0);
     };
     // g'x of this thread's cell (the states staged in sw)
-    T x[4], Ax[4];
+    T x[4], Ax[4], f0[4], b[4];   // (F0 and b read behind the face)
     auto apply = [&](double xn2) __attribute__((always_inline)) {
         if (!(xn2 > 0.0)) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) Ax[c] = T(0);
+            for (int c = 0; c < 4; ++c) {
+                Ax[c] = T(0);
+                b[c] = vec(2, c, q);
+            }
             __syncthreads();
             return;
         }
         const double xn = psqrt(xn2);
         const T eps = (T)(FdEps<T>::sqrt_eps * utot * frcp(xn));
         const T sc = (T)(a.adt * xn * (FdEps<T>::inv_sqrt_eps * iutot));
-        const int h = (J + 1) * hx + I + 1;
         if (valid)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const T w = vec(0, c, q) + eps * x[c];
-                T* s = sw + c * hn + h;
-                *s = w;
-                if (J == 0) s[-hx] = w;
-                if (J == nzl - 1) s[hx] = w;
-                if (I == 0) s[per ? nxl : -1] = w;
-                if (I == nxl - 1) s[per ? -nxl : 1] = w;
-            }
+            for (int c = 0; c < 4; ++c) sw[c * nc + q] = vec(0, c, q) + eps * x[c];
         __syncthreads();
         if (face) {
             T wL[4], wR[4], Phi[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                wL[c] = sw[c * hn + flo];
-                wR[c] = sw[c * hn + flo + (xf ? 1 : hx)];
+                wL[c] = sw[c * nc + flo];
+                wR[c] = sw[c * nc + fhi];
             }
             if (xf) fv_flux<T, 1>(A, wL, wR, &sBc[frow][0], &sBf[0][6], fwl, fwr, Phi);
             else fv_flux<T, 2>(A, wL, wR, &sBf[frow][0], &sBf[frow][6], fwl, fwr, Phi);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) sF[tid][c] = Phi[c];
+            for (int c = 0; c < 4; ++c) sF[c][tid] = Phi[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            f0[c] = vec(1, c, q);
+            b[c] = vec(2, c, q);
         }
         __syncthreads();
         const T ihx = A.hz * A.iarea, ihz = A.hx * A.iarea;
         if (valid)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                T f = -(sF[fx + 1][c] - sF[fx][c]) * ihx - (sF[fz + nxl][c] - sF[fz][c]) * ihz;
-                if (c == 2) f -= A.g * sw[h];
-                Ax[c] = x[c] - sc * (f - vec(1, c, q));
+                T f = -(sF[c][fx + 1] - sF[c][fx]) * ihx - (sF[c][fz + nxl] - sF[c][fz]) * ihz;
+                if (c == 2) f -= A.g * sw[q];
+                Ax[c] = x[c] - sc * (f - f0[c]);
             }
     };
     int l = 0;
@@ -816,7 +840,7 @@ fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
             // down: the coarse level's b = R(g'x - b) and its first stage from zero
             T d[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) d[c] = Ax[c] - vec(2, c, q);
+            for (int c = 0; c < 4; ++c) d[c] = Ax[c] - b[c];
             __syncthreads();   // the staged states are read no more
             if (valid)
 #pragma unroll
@@ -858,7 +882,7 @@ fv_tail_kernel(const TailArgs<T> a, const MemberArgs* __restrict__ mt, long ms)
         double nrm = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const T v = x0[c] + s * (vec(2, c, q) - Ax[c]);
+            const T v = x0[c] + s * (b[c] - Ax[c]);
             x[c] = v;
             nrm += (double)v * (double)v;
         }
@@ -1282,7 +1306,7 @@ bool fv_tail_fits(int nxl, int nzl, int tile)
 {
     const int nt = ((nxl + 7) / 8) * ((nzl + 3) / 4);
     return tile == JFMG_TILE_8x4 && nxl * nzl <= TAIL_CELLS && nt <= TAIL_NTH / 32 && nzl <= TAIL_ROWS &&
-           (nxl + 2) * (nzl + 2) <= TAIL_HALO && (((nxl + 1) * nzl + 63) & ~63) + nxl * (nzl + 1) <= TAIL_NTH;
+           (((nxl + 1) * nzl + 63) & ~63) + nxl * (nzl + 1) <= TAIL_NTH;
 }
 template <typename T> int FvLaunch<T>::tail(const TailArgs<T>& a0, hipStream_t st, const Mb& mb)
 {

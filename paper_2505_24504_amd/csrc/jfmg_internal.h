@@ -288,7 +288,7 @@ struct LinLevels {
 
 // The coarsest levels of a V-cycle in one launch (fv_tail_kernel): limits of a level, and the
 // sum of the levels' cells (each a quarter of the one before).
-constexpr int TAIL_LEV = 3, TAIL_NTH = 640, TAIL_CELLS = 320, TAIL_SUM = 420, TAIL_ROWS = 64, TAIL_HALO = 512;
+constexpr int TAIL_LEV = 3, TAIL_NTH = 640, TAIL_CELLS = 320, TAIL_SUM = 420, TAIL_ROWS = 64;
 bool fv_tail_fits(int nxl, int nzl, int tile);
 template <typename T> struct TailArgs {
     int n, lev0;           // levels, the first one's index
