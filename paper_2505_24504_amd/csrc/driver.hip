@@ -494,7 +494,7 @@ size_t layout(const jfmg_config& c, char* base, F&& bind)
     long nfv = (long)n1 * c.nx * n1 * c.nz;
     const long fvblk = fv_partial_blocks((long)n1 * c.nx, (long)n1 * c.nz);   // blocks of the finest FV level
     const long dgblk = ne;   // at most one block per element
-    size_t npart = (size_t)std::max<long>({la * (m + 2), 2 * fvblk, dgblk, 2048, 4096});
+    size_t npart = (size_t)std::max<long>({la * (m + 2) + (la <= UPDATE_SUM_MAX ? la * (m + 1) : 0), 2 * fvblk, dgblk, 2048, 4096});
     bind("scal", cv.take(NSCAL * 8), 0);
     bind("partials", cv.take(npart * 8), npart);
     const size_t fvp = (size_t)std::max<long>(fvblk, transfer_grid(c.k, ne)) + 1;   // FV stages, fused transfer; their sum
@@ -1114,9 +1114,16 @@ jfmg_status iter_ops(jfmg_problem* p, int j)
     pub.zn = nv;
     pub.fidx = S_RF - S_H1;
     pub.cnt = (unsigned long long*)(p->scal + S_CNT);
-    { ProfScope ps(p, JFMG_K_MULTIDOT, md); launch_multidot(w, p->V, N, nv, 1, N, red_at(p, S_H1), st, p->mb); }
+    // Up to UPDATE_SUM_MAX blocks the update sums the multi-dot's partials itself instead of
+    // behind a finalize launch: a work-group's sums take 1 us, the launch 2.5 us and a gap (the
+    // step of 73728 unknowns 14.9 -> 14.7 ms); with 162 blocks in each of 24 members the sums
+    // would read as much again as the kernel's own vectors.
+    const bool fin = la_blocks(N) > UPDATE_SUM_MAX;
+    double* hpart = p->partials + (fin ? 0 : (long)(p->m + 2) * la_blocks(N));   // apart from the second pass's
+    { ProfScope ps(p, JFMG_K_MULTIDOT, md);
+      launch_multidot(w, p->V, N, nv, 1, N, Red{hpart, fin ? p->scal + S_H1 : nullptr}, st, p->mb); }
     { ProfScope ps(p, JFMG_K_UPDATE, up);
-      launch_update(w, p->V, N, nv, N, p->scal + S_H1, st, p->mb, reorth, p->partials, pub); }
+      launch_update(w, p->V, N, nv, N, p->scal + S_H1, st, p->mb, reorth, p->partials, pub, fin ? nullptr : hpart); }
     double* wpart = p->partials + (long)(p->m + 1) * la_blocks(N);
     launch_update2_publish(w, p->V, N, nv, N, reorth, p->partials, p->scal + S_H2, wpart, pub, st, p->mb);
     return check_launch(p);

@@ -387,9 +387,12 @@ struct Publish;
 // w -= sum_i h[i] V_i (h the coefficients that g2.h holds).  With dots (g2.h set), where gate
 // g2 opens, the multi-dot <w_new, v_i> (i < nv) of the updated w follows in the same kernel,
 // its block partials at dots (la_blocks(n) per entry, as launch_multidot stores them); where
-// it stays closed, the kernel publishes (pub) with ||w_new||^2 by Pythagoras.
-void launch_update(double* w, const double* V, long ld, int nv, long n, const double* h, hipStream_t st, const Mb& mb,
-                   Gate g2, double* dots, const Publish& pub);
+// it stays closed, the kernel publishes (pub) with ||w_new||^2 by Pythagoras.  With hpart (at
+// most UPDATE_SUM_MAX blocks) the coefficients and ||w||^2 are not at h yet but formed by
+// every work-group from the multi-dot's partials at hpart, and stored to h.
+constexpr int UPDATE_SUM_MAX = 128;
+void launch_update(double* w, const double* V, long ld, int nv, long n, double* h, hipStream_t st, const Mb& mb, Gate g2,
+                   double* dots, const Publish& pub, const double* hpart = nullptr);
 // Publication of an FGMRES iteration's scalars: src[0..ns) to host-visible pinned memory
 // (host, member m at host + m * host_stride), entry idx replaced by ||w||^2 (also stored to
 // out[0]), entries zoff .. zoff+zn by 0 where the second pass was skipped, entry fidx by 1

@@ -110,6 +110,14 @@ __device__ __forceinline__ void ld_els(const double* __restrict__ x, long base, 
     for (int k = 0; k < LA_EL; ++k) v[k] = x[la_el(base, k)];
 }
 
+// v of lane l (l wave-uniform), in scalar registers
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, l), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), l);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
 // <w, v_i> for i < nv (and <w, w> as entry nv when self is set) over one block of w, which
 // stays in registers: the basis vectors come in groups of G, the next group's loads in
 // flight while the current one is reduced (the wave's sums; one LDS exchange at the end
@@ -244,8 +252,13 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     const long b0 = (long)blockIdx.x * LA_NTH * LA_EL, base = b0 + threadIdx.x;
     const bool whole = b0 + LA_NTH * LA_EL <= n;
     // coefficient v in lane v of every wave
-    double hl = 0.0, acc[LA_EL], a[G][LA_EL], b[G][LA_EL];
-    if constexpr (!SELF) hl = mbr(h, ms)[min(lane, nv - 1)];
+    double hl = 0.0, before = 0.0, acc[LA_EL], a[G][LA_EL], b[G][LA_EL];
+    if constexpr (!SELF) {
+        if (!hpart) {
+            hl = mbr(h, ms)[min(lane, nv - 1)];
+            before = ldv(g2.h + nv);
+        }
+    }
     auto load = [&](int v0, double (&x)[G][LA_EL]) {   // (beyond nv: the last vector, not used)
         if (whole) {
 #pragma unroll
@@ -266,8 +279,8 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     }
     load(0, a);
     bool dots2 = false;
+    __shared__ double hs[65];
     if constexpr (SELF) {
-        __shared__ double hs[64];
         hpart = mbr(hpart, ms);
         for (int q = threadIdx.x >> 6; q < nv; q += LA_NTH / 64) {
             double t = 0.0;
@@ -278,9 +291,34 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
         __syncthreads();
         hl = hs[min(lane, nv - 1)];
         if (blockIdx.x == 0 && (int)threadIdx.x < nv) mbr(hout, ms)[threadIdx.x] = hl;
-    } else if (dots) {
+    } else if (hpart) {
+        // the multi-dot's partials (at most 128 per entry), in the finalize kernel's order
+        hpart = mbr(hpart, ms);
+        for (int q0 = threadIdx.x >> 6; q0 <= nv; q0 += 4 * (LA_NTH / 64)) {
+            double p0[4], p1[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double* p = hpart + (long)min(q0 + r * (LA_NTH / 64), nv) * hnb;
+                p0[r] = p[min(lane, hnb - 1)];
+                p1[r] = p[min(lane + 64, hnb - 1)];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int q = q0 + r * (LA_NTH / 64);
+                const double t = wave_sum(lane < hnb ? p0[r] : 0.0) + wave_sum(lane + 64 < hnb ? p1[r] : 0.0);
+                if (lane == 0 && q <= nv) hs[q] = t;
+            }
+        }
+        __syncthreads();
+        hl = hs[min(lane, nv - 1)];
+        before = hs[nv];
+        if (blockIdx.x == 0) {
+            if ((int)threadIdx.x <= nv) mbr(hout, ms)[threadIdx.x] = hs[threadIdx.x];
+            __syncthreads();   // (published below)
+        }
+    }
+    if (!SELF && dots) {
         // gate_after from the coefficients that every wave holds
-        const double before = ldv(g2.h + g2.nv);
         const double after = before - wave_sum(lane < nv ? hl * hl : 0.0);
         dots2 = after < g2.tau2 * before;   // gate_open's decision
         if (!dots2 && blockIdx.x == 0) {
@@ -292,15 +330,10 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
                                                                          : pub.src[i];
         }
     }
-    auto coef = [&](int v) {
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, hl);
-        const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, v), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), v);
-        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-    };
     auto subtract = [&](int v0, const double (&x)[G][LA_EL]) {
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-            const double hv = v0 + q < nv ? coef(min(v0 + q, nv - 1)) : 0.0;
+            const double hv = v0 + q < nv ? lane_value(hl, min(v0 + q, nv - 1)) : 0.0;
             if (v0 + q < nv)
 #pragma unroll
                 for (int k = 0; k < LA_EL; ++k) acc[k] -= hv * x[q][k];
@@ -377,11 +410,11 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     }
 }
 
-void launch_update(double* w, const double* V, long ld, int nv, long n, const double* h, hipStream_t st, const Mb& mb,
-                   Gate g2, double* dots, const Publish& pub)
+void launch_update(double* w, const double* V, long ld, int nv, long n, double* h, hipStream_t st, const Mb& mb, Gate g2,
+                   double* dots, const Publish& pub, const double* hpart)
 {
-    timed_launch(update_kernel<false>, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, h, Gate{},
-                 Red{nullptr, nullptr}, mb.ms, mb.tab, (const double*)nullptr, 0, (double*)nullptr, g2, dots, pub);
+    timed_launch(update_kernel<false>, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, (const double*)h,
+                 Gate{}, Red{nullptr, nullptr}, mb.ms, mb.tab, hpart, la_blocks(n), h, g2, dots, pub);
 }
 
 void launch_update2_publish(double* w, const double* V, long ld, int nv, long n, Gate gate, const double* hpart,
@@ -422,28 +455,47 @@ lincomb_kernel(double* out, const double* base_, const double* __restrict__ Z, l
     base_ = mbr(base_, ms);
     Z = mbr(Z, ms);
     y = mbr(y, ms);
-    const long base = (long)blockIdx.x * LA_NTH * LA_EL + threadIdx.x;
-    double acc[LA_EL];
+    constexpr int G = 4;
+    const int lane = threadIdx.x & 63;
+    const long b0 = (long)blockIdx.x * LA_NTH * LA_EL, base = b0 + threadIdx.x;
+    if (b0 >= n) return;
+    // coefficient v in lane v; columns behind the last nonzero one are not read
+    const double yl = lane < nv ? y[lane] : 0.0;
+    const unsigned long long nz = __ballot(yl != 0.0);
+    nv = nz ? 64 - __builtin_clzll(nz) : 0;
+    double acc[LA_EL], a[G][LA_EL], b[G][LA_EL];
+    // (elements beyond the vector: its first ones, not stored)
+    long el[LA_EL];
 #pragma unroll
-    for (int k = 0; k < LA_EL; ++k) {
-        const long i = base + (long)k * LA_NTH;
-        acc[k] = (i < n && base_) ? base_[i] : 0.0;
-    }
-    for (int v = 0; v < nv; ++v) {
-        const double yv = y[v];
-        if (yv == 0.0) continue;   // a zero coefficient adds nothing (its column may be unset)
-        const double* Zi = Z + (long)v * ld;
+    for (int k = 0; k < LA_EL; ++k) el[k] = la_el(base, k) < n ? la_el(base, k) : 0;
 #pragma unroll
-        for (int k = 0; k < LA_EL; ++k) {
-            const long i = base + (long)k * LA_NTH;
-            if (i < n) acc[k] += yv * Zi[i];
+    for (int k = 0; k < LA_EL; ++k) acc[k] = base_ ? base_[el[k]] : 0.0;
+    auto load = [&](int v0, double (&x)[G][LA_EL]) {
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+#pragma unroll
+            for (int k = 0; k < LA_EL; ++k) x[q][k] = Z[(long)min(v0 + q, nv - 1) * ld + el[k]];
+    };
+    auto add = [&](int v0, const double (&x)[G][LA_EL]) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const double yv = lane_value(yl, min(v0 + q, 63));
+            if (v0 + q < nv && yv != 0.0)   // a zero coefficient adds nothing (its column may be unset)
+#pragma unroll
+                for (int k = 0; k < LA_EL; ++k) acc[k] += yv * x[q][k];
         }
+    };
+    if (nv > 0) load(0, a);
+    for (int v0 = 0; v0 < nv; v0 += 2 * G) {   // the next group's loads in flight
+        if (v0 + G < nv) load(v0 + G, b);
+        add(v0, a);
+        if (v0 + G >= nv) break;
+        if (v0 + 2 * G < nv) load(v0 + 2 * G, a);
+        add(v0 + G, b);
     }
 #pragma unroll
-    for (int k = 0; k < LA_EL; ++k) {
-        const long i = base + (long)k * LA_NTH;
-        if (i < n) out[i] = acc[k];
-    }
+    for (int k = 0; k < LA_EL; ++k)
+        if (la_el(base, k) < n) out[el[k]] = acc[k];
 }
 
 void launch_lincomb(double* out, const double* base, const double* Z, long ld, int nv, long n, const double* y,
