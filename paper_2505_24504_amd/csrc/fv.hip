@@ -156,8 +156,9 @@ __device__ __forceinline__ void fv_face(const FvArgs<T>& A, const T (&sw)[4][HZ]
 // On the large levels the vector instructions bound it (56 to 75 % of the time): 856 per
 // wave in FP32 and 934 in FP64 on the 64x8 tile before, 703 and 831 with a wall's ghost
 // state in the halo instead of behind selects, each thread's own cell staged from its own
-// loads, 32-bit offsets, the shorter HLLC form and no branch around the faces.  Step of
-// 1024x256 nodes 24.2 -> 23.2 ms, of 2048x1024 (FP32 multigrid) 131.5 -> 126.7 ms.  Modes:
+// loads, 32-bit offsets, the shorter HLLC form and no branch around the faces: step of
+// 1024x256 nodes 24.2 -> 23.2 ms, of 2048x1024 (FP32 multigrid) 131.5 -> 126.7 ms; another 76
+// less with the faces handed out without a loop: 23.3 -> 22.7 and 118.1 -> 116.9 ms.  Modes:
 //   LIN     out = F0 = f~(u); ||u + Ubar||^2 and max(|v| + c) block partials (the level
 //           slots and dtau from them: fv_lin_finalize_kernel); with out2 also the next coarser
 //           level's state R u
@@ -303,8 +304,6 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
                           : (bg_i < 10 * min(TZ + 1, nzl + 1 - J0) ? bg_i : bg_i % 10);
     const T* const bg_p = bg_c ? rc + 6L * J0 : rf + 10L * J0;
     const T bg_v = bg_p[bg_j];
-    // (LATE in FP64: the cell's x is read again with them instead of held over the faces)
-    constexpr bool AGAIN = LATE && sizeof(T) == 8;
     T su[4], own_x[4], ru[4], rx[4];
     T own_f0[4], own_b[4], own_x0[4] = {T(0), T(0), T(0), T(0)};
     // STAGE_PC: the finer level's four children of the cell, read with the own-cell
@@ -328,7 +327,6 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if constexpr (PERT) own_f0[c] = ld(F0 + c * nc, q);
-            if constexpr (PERT && AGAIN) own_x[c] = ld(opaque(xp) + c * nc, q);
             if constexpr (STG || MODE == FVM_DEFECT) own_b[c] = ld(b + c * nc, q);
         }
         // the first stage of a sweep has x^(0) = x^(j-1): no second load (the copy
@@ -393,11 +391,16 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
         auto face = [&](auto xf_tag, int idx) {
             fv_face<T, TX, TZ, HZ, HX, decltype(xf_tag)::value>(A, sw, sBc, sBf, sFx, sFz, I0, J0, nxl, nzl, per, idx);
         };
-        for (int fx = tid; fx < NFX; fx += NTH) face(std::true_type{}, fx);
-        if constexpr (ZREV)   // z-faces from the last thread down
-            for (int fz = NTH - 1 - tid; fz < NFZ; fz += NTH) face(std::false_type{}, fz);
-        else                  // z-faces continue the numbering after the x-faces
-            for (int fz = (tid + NTH - NFX % NTH) % NTH; fz < NFZ; fz += NTH) face(std::false_type{}, fz);
+        // (not loops: the constants of the general power, the rare branch of the pressures,
+        // would be set up before each of them, 38 moves and as many registers)
+#pragma unroll
+        for (int k = 0; k < (NFX + NTH - 1) / NTH; ++k)
+            if (NFX >= (k + 1) * NTH || tid < NFX - k * NTH) face(std::true_type{}, tid + k * NTH);
+        const int tz = ZREV ? NTH - 1 - tid                          // z-faces from the last thread down
+                            : (tid + NTH - NFX % NTH) % NTH;         // or numbered on after the x-faces
+#pragma unroll
+        for (int k = 0; k < (NFZ + NTH - 1) / NTH; ++k)
+            if (NFZ >= (k + 1) * NTH || tz < NFZ - k * NTH) face(std::false_type{}, tz + k * NTH);
         if constexpr (LATE) load_own();
         __syncthreads();
     } else {
