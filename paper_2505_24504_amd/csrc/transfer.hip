@@ -6,9 +6,13 @@
 //          centre values with the modified Newton-Cotes weights w)
 //   T^-1,mf: u_ab = sum_ij Vinv_ai Vinv_bj t_ij - (sum_ij w_i w_j t_ij - mean(t))
 //
-// One thread per node/subcell, EPB elements per work-group; the (k+1)^2 x
-// (k+1)^2 operator is applied as two 1D contractions through LDS.  The kernels
-// are bound by HBM (<= 2 x 16 FMAs per output value), so no matrix cores.
+// One thread per node/subcell, an element's threads in one wave (16, 7 or 4 elements per wave
+// for k = 1, 2, 3); the (k+1)^2 x (k+1)^2 operator is applied as two 1D contractions through
+// LDS.  The kernels are bound by HBM (<= 2 x 16 FMAs per output value), so no matrix cores; on
+// small grids by the chain of one wave's latencies.  LDS serves a wave's accesses in their
+// order, so that between writing and reading an element's values no work-group barrier is
+// needed (five of them, two waits for scalars, a 64-bit division and loads behind branches
+// before: T of 1024x256 nodes 9.6 -> 9.1 us, of 18432 nodes 5.3 -> 4.6 us, back 4.4 -> 3.9).
 // Subcell (i, j) of element (ex, ez) is FV cell (ex (k+1) + i, ez (k+1) + j).
 #include "jfmg_internal.h"
 
@@ -16,13 +20,48 @@ namespace jfmg {
 
 template <int N1> struct TrShape {
     static constexpr int NP = N1 * N1;
-    static constexpr int NTH = (N1 == 2) ? 64 : 128;
-    static constexpr int EPB = NTH / NP;
+    static constexpr int NTH = (N1 == 2) ? 64 : 256;
+    static constexpr int EPW = 64 / NP;                // elements per wave
+    static constexpr int EPB = EPW * (NTH / 64);
 };
 
 __device__ __forceinline__ long subcell_index(int ex, int ez, int i, int j, int n1, int nxf)
 {
     return (long)(ez * n1 + j) * nxf + (long)ex * n1 + i;
+}
+
+// The wave's LDS writes before its reads behind: no instruction, an order for the compiler.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The mass-fix sums of an element with subcell values v[component][subcell]: its mean (times
+// NP) and Newton-Cotes quadrature of each component, each summed in this order by one of the
+// element's threads nd, into ssum[8].
+template <int N1>
+__device__ __forceinline__ void mass_sums(const RefTab& R, const double (&v)[4][N1 * N1], int nd, double* ssum)
+{
+    for (int q = nd; q < 8; q += N1 * N1) {
+        const int c = q & 3;
+        double acc = 0.0;
+        if (q < 4) {
+#pragma unroll
+            for (int jj = 0; jj < N1; ++jj)
+#pragma unroll
+                for (int ii = 0; ii < N1; ++ii) acc += v[c][jj * N1 + ii];
+        } else {
+#pragma unroll
+            for (int jj = 0; jj < N1; ++jj)
+#pragma unroll
+                for (int ii = 0; ii < N1; ++ii) {
+                    const double w = v[c][jj * N1 + ii];
+                    acc += R.wnc[ii] * R.wnc[jj] * w;
+                }
+        }
+        ssum[q] = acc;
+    }
 }
 
 // snrm2 != nullptr: the input is sgn U / ||U|| (||U||^2 = snrm2[0]); the scaled DG
@@ -37,120 +76,106 @@ transfer_T_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, int mass_fix, co
                   double alpha, Red red, long ms, double sgn)
 {
     const DgArgs& A = dg_of<RG>(Aa, mt);
-    if (RG) nxf = N1 * A.nx;
-    U = mbr(U, ms);
+    // the arguments that the first loads need, in scalar registers at once
+    gptr<double> U_ = (gptr<double>)U, snrm2_ = (gptr<double>)snrm2, slots_ = (gptr<double>)slots;
+    int nx = A.nx;
+    long ne = A.ne;
+    asm volatile("" : "+s"(U_), "+s"(snrm2_), "+s"(slots_), "+s"(nx), "+s"(ne));
+    if (RG) nxf = N1 * nx;
+    U = mbr((const double*)U_, ms);
     u = mbr(u, ms);
-    snrm2 = mbr(snrm2, ms);
+    snrm2 = mbr((const double*)snrm2_, ms);
     Us = mbr(Us, ms);
     x1 = mbr(x1, ms);
-    slots = mbr(slots, ms);
+    slots = mbr((const double*)slots_, ms);
     red = mbr(red, ms);
-    constexpr int NP = TrShape<N1>::NP, EPB = TrShape<N1>::EPB;
-    if ((long)blockIdx.x * EPB >= A.ne || sits_out(mt)) {   // beyond a smaller member, or one that sits out
+    using S = TrShape<N1>;
+    constexpr int NP = S::NP, EPB = S::EPB, EPW = S::EPW;
+    if ((long)blockIdx.x * EPB >= ne || sits_out(mt)) {   // beyond a smaller member, or one that sits out
         if (x1 && threadIdx.x == 0) red.partials[block_linear()] = 0.0;
         return;
     }
     __shared__ double sU[EPB][4][NP];
     __shared__ double sH[EPB][4][NP];
-    const int t = threadIdx.x, le = t / NP, nd = t - le * NP;
-    const bool act = le < EPB;
-    const long e = (long)blockIdx.x * EPB + le;
-    const bool valid = act && e < A.ne;
-    const long N = A.ne * NP;
-    const long nc = N;   // number of finest FV cells
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lw = lane / NP, nd = lane - lw * NP;
+    const bool act = lw < EPW;
+    const int le = act ? wv * EPW + lw : 0;
+    const unsigned e = blockIdx.x * EPB + le;
+    const bool valid = act && e < (unsigned)ne;
+    const long N = ne * NP;   // nodes, and cells of the finest FV level
     const int i = nd % N1, j = nd / N1;   // this thread: x-index i, z-index j
     // every global load first (the node's four components, ||U||^2, the pseudo time
-    // step and this thread's rows of V), so that their latencies overlap
-    double uv[4] = {0.0, 0.0, 0.0, 0.0};
-    if (valid)
+    // step and this thread's rows of V), so that their latencies overlap (threads without
+    // an element read element 0's)
+    const unsigned n = valid ? e * NP + nd : 0u;
+    const double sn2 = ldv(snrm2 ? snrm2 : U);
+    const double dtau = ldv(x1 ? slots + LV_DTAU : U);
+    double uv[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) uv[c] = U[c * N + e * NP + nd];
-    const double sn2 = snrm2 ? snrm2[0] : 1.0;
-    const double dtau = x1 ? slots[LV_DTAU] : 0.0;
+    for (int c = 0; c < 4; ++c) uv[c] = ld(U + c * N, n);
     double Vi[N1], Vj[N1];
 #pragma unroll
     for (int a = 0; a < N1; ++a) {
         Vi[a] = A.R.V[i][a];
         Vj[a] = A.R.V[j][a];
     }
-    const double s = snrm2 ? sgn / sqrt(sn2) : 1.0;
-    if (act)
+    if (snrm2) {
+        const double s = sgn / sqrt(sn2);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            double v = uv[c];
-            if (valid && snrm2) {
-                v = v * s;
-                Us[c * N + e * NP + nd] = v;
-            }
-            sU[le][c][nd] = v;
+            uv[c] = uv[c] * s;
+            if (valid) st(Us + c * N, n, uv[c]);
         }
-    __syncthreads();
-    // first contraction along x: h_{b,i} = sum_a V_ia u_ab (stored at node slot b*N1+i)
-    if (act)
+    }
+    double tv[4];
+    if (act) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sU[le][c][nd] = uv[c];
+        wave_sync();
+        // first contraction along x: h_{b,i} = sum_a V_ia u_ab (stored at node slot b*N1+i)
+#pragma unroll
         for (int c = 0; c < 4; ++c) {
             double s2 = 0.0;
 #pragma unroll
             for (int a = 0; a < N1; ++a) s2 += Vi[a] * sU[le][c][j * N1 + a];
             sH[le][c][j * N1 + i] = s2;
         }
-    __syncthreads();
-    double tv[4];
-    if (act)
+        wave_sync();
+#pragma unroll
         for (int c = 0; c < 4; ++c) {
             double s2 = 0.0;
 #pragma unroll
             for (int bb = 0; bb < N1; ++bb) s2 += Vj[bb] * sH[le][c][bb * N1 + i];
             tv[c] = s2;
         }
-    __syncthreads();
-    if (act)
-        for (int c = 0; c < 4; ++c) sU[le][c][nd] = tv[c];
-    __syncthreads();
-    // the element's mass-fix sums (mean and Newton-Cotes quadrature of each component, each
-    // summed in the order below by one of the element's threads) into sH, which the
-    // contractions are done with: [le] as 8 consecutive doubles
-    double* const ssum = &sH[act ? le : 0][0][0];
-    if (mass_fix) {
-        if (act)
-            for (int q = nd; q < 8; q += NP) {
-                const int c = q & 3;
-                double acc = 0.0;
-                if (q < 4) {
+        if (mass_fix) {   // its sums in sH, which the contractions are done with
 #pragma unroll
-                    for (int jj = 0; jj < N1; ++jj)
-#pragma unroll
-                        for (int ii = 0; ii < N1; ++ii) acc += sU[le][c][jj * N1 + ii];
-                } else {
-#pragma unroll
-                    for (int jj = 0; jj < N1; ++jj)
-#pragma unroll
-                        for (int ii = 0; ii < N1; ++ii) {
-                            const double v = sU[le][c][jj * N1 + ii];
-                            acc += A.R.wnc[ii] * A.R.wnc[jj] * v;
-                        }
-                }
-                ssum[q] = acc;
-            }
-        __syncthreads();
+            for (int c = 0; c < 4; ++c) sU[le][c][nd] = tv[c];
+            wave_sync();
+            mass_sums<N1>(A.R, sU[le], nd, &sH[le][0][0]);
+            wave_sync();
+        }
     }
     double nrm = 0.0;
     if (valid) {
-        const int ez = (int)(e / A.nx), ex = (int)(e - (long)ez * A.nx);
-        const long o = subcell_index(ex, ez, i, j, N1, nxf);
+        const unsigned ez = e / (unsigned)nx, ex = e - ez * nx;
+        const unsigned o = (unsigned)subcell_index(ex, ez, i, j, N1, nxf);
         const T s1 = x1 ? (T)(alpha * dtau) : T(0);
+        const double* const ssum = &sH[le][0][0];
+#pragma unroll
         for (int c = 0; c < 4; ++c) {
             double shift = 0.0;
             if (mass_fix) shift = ssum[c] / NP - ssum[4 + c];   // mean / NP - quad
             const T b = (T)(tv[c] - shift);
-            u[c * nc + o] = b;
+            st(u + c * N, o, b);
             if (x1) {
                 const T v = s1 * b;
-                x1[c * nc + o] = v;
+                st(x1 + c * N, o, v);
                 nrm += (double)v * (double)v;
             }
         }
     }
-    if (x1) put_partial<TrShape<N1>::NTH>(red, nrm);
+    if (x1) put_partial<S::NTH>(red, nrm);
 }
 
 template <int N1, typename T, bool RG>
@@ -159,74 +184,72 @@ transfer_Tinv_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, int mass_fix,
                      double* __restrict__ U, int nxf, Red red, long ms)
 {
     const DgArgs& A = dg_of<RG>(Aa, mt);
-    if (RG) nxf = N1 * A.nx;
-    u = mbr(u, ms);
+    gptr<T> u_ = (gptr<T>)u;
+    int nx = A.nx;
+    long ne = A.ne;
+    asm volatile("" : "+s"(u_), "+s"(nxf), "+s"(nx), "+s"(ne));
+    if (RG) nxf = N1 * nx;
+    u = mbr((const T*)u_, ms);
     U = mbr(U, ms);
     red = mbr(red, ms);
-    constexpr int NP = TrShape<N1>::NP, NTH = TrShape<N1>::NTH, EPB = TrShape<N1>::EPB;
-    if ((long)blockIdx.x * EPB >= A.ne || sits_out(mt)) {   // beyond a smaller member, or one that sits out
+    using S = TrShape<N1>;
+    constexpr int NP = S::NP, EPB = S::EPB, EPW = S::EPW;
+    if ((long)blockIdx.x * EPB >= ne || sits_out(mt)) {   // beyond a smaller member, or one that sits out
         if (red.partials && threadIdx.x == 0) red.partials[block_linear()] = 0.0;
         return;
     }
     __shared__ double sT[EPB][4][NP];
     __shared__ double sH[EPB][4][NP];
-    const int t = threadIdx.x, le = t / NP, nd = t - le * NP;
-    const bool act = le < EPB;
-    const long e = (long)blockIdx.x * EPB + le;
-    const bool valid = act && e < A.ne;
-    const long N = A.ne * NP;
-    const int ez = valid ? (int)(e / A.nx) : 0, ex = valid ? (int)(e - (long)ez * A.nx) : 0;
-    const int i = nd % N1, j = nd / N1;
+    __shared__ double sS[EPB][8];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lw = lane / NP, nd = lane - lw * NP;
+    const bool act = lw < EPW;
+    const int le = act ? wv * EPW + lw : 0;
+    const unsigned e = blockIdx.x * EPB + le;
+    const bool valid = act && e < (unsigned)ne;
+    const long N = ne * NP;
+    const unsigned ez = valid ? e / (unsigned)nx : 0u, ex = valid ? e - ez * nx : 0u;
+    // thread slot nd = b*N1 + a reads subcell (a, b) and computes DG node (a, b)
+    const int a = nd % N1, b = nd / N1;
     // every global load first: the subcell's four components and this thread's rows
     // of V^-1
-    T tv[4] = {T(0), T(0), T(0), T(0)};
-    if (valid)
+    const unsigned o = (unsigned)subcell_index(ex, ez, a, b, N1, nxf);
+    T tv[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) tv[c] = u[c * N + subcell_index(ex, ez, i, j, N1, nxf)];
-    // thread slot nd = b*N1 + a computes DG node (a, b)
-    const int a = i, b = j;
+    for (int c = 0; c < 4; ++c) tv[c] = ld(u + c * N, o);
     double Va[N1], Vb[N1];
 #pragma unroll
     for (int q = 0; q < N1; ++q) {
         Va[q] = A.R.Vinv[a][q];
         Vb[q] = A.R.Vinv[b][q];
     }
-    if (act)
+    double nrm = 0.0;
+    if (act) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) sT[le][c][nd] = (double)tv[c];
-    __syncthreads();
-    if (act)
+        wave_sync();
+#pragma unroll
         for (int c = 0; c < 4; ++c) {
             double s = 0.0;   // h_{jj,a} = sum_i Vinv_ai t_{i,jj}, stored at slot jj*N1+a
 #pragma unroll
             for (int ii = 0; ii < N1; ++ii) s += Va[ii] * sT[le][c][b * N1 + ii];
             sH[le][c][b * N1 + a] = s;
         }
-    __syncthreads();
-    double nrm = 0.0;
-    if (valid)
-        for (int c = 0; c < 4; ++c) {
-            double s = 0.0;
+        if (mass_fix) mass_sums<N1>(A.R, sT[le], nd, sS[le]);
+        wave_sync();
+        if (valid)
 #pragma unroll
-            for (int jj = 0; jj < N1; ++jj) s += Vb[jj] * sH[le][c][jj * N1 + a];
-            double shift = 0.0;
-            if (mass_fix) {
-                double mean = 0.0, quad = 0.0;
+            for (int c = 0; c < 4; ++c) {
+                double s = 0.0;
 #pragma unroll
-                for (int jj = 0; jj < N1; ++jj)
-#pragma unroll
-                    for (int ii = 0; ii < N1; ++ii) {
-                        const double v = sT[le][c][jj * N1 + ii];
-                        mean += v;
-                        quad += A.R.wnc[ii] * A.R.wnc[jj] * v;
-                    }
-                shift = quad - mean / NP;
+                for (int jj = 0; jj < N1; ++jj) s += Vb[jj] * sH[le][c][jj * N1 + a];
+                double shift = 0.0;
+                if (mass_fix) shift = sS[le][4 + c] - sS[le][c] / NP;
+                const double v = s - shift;
+                st(U + c * N, e * NP + nd, v);
+                nrm += v * v;
             }
-            const double v = s - shift;
-            U[c * N + e * NP + nd] = v;
-            nrm += v * v;
-        }
-    if (red.partials) put_partial<NTH>(red, nrm);
+    }
+    if (red.partials) put_partial<S::NTH>(red, nrm);
 }
 
 template <int N1>
