@@ -10,6 +10,7 @@
 namespace jfmg {
 
 constexpr int LA_NTH = 256, LA_EL = 4;   // threads per block, elements per thread
+constexpr int UPDATE2_GROUPS = 1024;     // work-groups of the second Gram-Schmidt pass
 constexpr int LA_FILL = 2048;            // blocks up to which the multi-dot splits its groups
 
 int la_blocks(long n)
@@ -213,51 +214,33 @@ void launch_multidot(const double* w, const double* V, long ld, int nv, int self
 // kernel's products, order and partial layout (its launch, one kernel per iteration, is
 // saved); where it stays closed, work-group 0 stores ||w||^2 after this pass, by Pythagoras,
 // to pub.out and publishes (first thing, so that its loads and host stores overlap the update).
-// SELF: the gated second Gram-Schmidt pass together with the iteration's last reduction and
-// its publication (pub), in one launch:
-//  * gate closed (the pass is skipped): every work-group returns at once;
-//  * gate open: h is not given but formed by every work-group from the multi-dot's hnb block
-//    partials per entry at hpart (lane-strided sums and the wave sum, a fixed order;
-//    work-group 0 stores it to hout), each work-group updates its part of w and stores its
-//    ||w||^2 partial in red; the last work-group to finish (a release fence and a counter in
-//    device memory, so no work-group waits for another) sums the partials in a fixed order into
-//    pub.out, publishes, and clears the counter for the next launch.
 // Publishing stores the scalar block pub.src[0..ns) to host-visible pinned memory, entry idx
 // replaced by pub.out's value, entry fidx by 1 where the second pass ran (else 0) and, where
 // the gate is closed, entries zoff .. zoff+zn (the skipped pass's coefficients) by 0, so the
 // host reads the Hessenberg column after the iteration's completion event without a separate
 // copy.
-template <bool SELF>
 __global__ void __launch_bounds__(LA_NTH)
 update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int nv, long n,
-              const double* __restrict__ h, Gate gate, Red red, long ms, const MemberArgs* __restrict__ mt,
-              const double* __restrict__ hpart, int hnb, double* __restrict__ hout, Gate g2,
-              double* __restrict__ dots, Publish pub)
+              double* __restrict__ h, long ms, const MemberArgs* __restrict__ mt, const double* __restrict__ hpart,
+              int hnb, Gate g2, double* __restrict__ dots, Publish pub)
 {
     constexpr int G = 4;
     n = len_of(n, mt);
-    gate.h = mbr(gate.h, ms);
     g2.h = mbr(g2.h, ms);
     pub.out = mbr(pub.out, ms);
     pub.src = mbr(pub.src, ms);
-    pub.cnt = mbr(pub.cnt, ms);
     pub.host += (long)blockIdx.z * pub.host_stride;
-    if constexpr (SELF) {
-        if (!gate_open(gate)) return;   // every lane takes part in the gate's wave sum
-    }
     w = mbr(w, ms);
     V = mbr(V, ms);
-    red = mbr(red, ms);
+    h = mbr(h, ms);
     const int lane = threadIdx.x & 63;
     const long b0 = (long)blockIdx.x * LA_NTH * LA_EL, base = b0 + threadIdx.x;
     const bool whole = b0 + LA_NTH * LA_EL <= n;
     // coefficient v in lane v of every wave
     double hl = 0.0, before = 0.0, acc[LA_EL], a[G][LA_EL], b[G][LA_EL];
-    if constexpr (!SELF) {
-        if (!hpart) {
-            hl = mbr(h, ms)[min(lane, nv - 1)];
-            before = ldv(g2.h + nv);
-        }
+    if (!hpart) {
+        hl = h[min(lane, nv - 1)];
+        before = ldv(g2.h + nv);
     }
     auto load = [&](int v0, double (&x)[G][LA_EL]) {   // (beyond nv: the last vector, not used)
         if (whole) {
@@ -280,18 +263,7 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
     load(0, a);
     bool dots2 = false;
     __shared__ double hs[65];
-    if constexpr (SELF) {
-        hpart = mbr(hpart, ms);
-        for (int q = threadIdx.x >> 6; q < nv; q += LA_NTH / 64) {
-            double t = 0.0;
-            for (int i = lane; i < hnb; i += 64) t += hpart[(long)q * hnb + i];
-            t = wave_sum(t);
-            if (lane == 0) hs[q] = t;
-        }
-        __syncthreads();
-        hl = hs[min(lane, nv - 1)];
-        if (blockIdx.x == 0 && (int)threadIdx.x < nv) mbr(hout, ms)[threadIdx.x] = hl;
-    } else if (hpart) {
+    if (hpart) {
         // the multi-dot's partials (at most 128 per entry), in the finalize kernel's order
         hpart = mbr(hpart, ms);
         for (int q0 = threadIdx.x >> 6; q0 <= nv; q0 += 4 * (LA_NTH / 64)) {
@@ -313,11 +285,11 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
         hl = hs[min(lane, nv - 1)];
         before = hs[nv];
         if (blockIdx.x == 0) {
-            if ((int)threadIdx.x <= nv) mbr(hout, ms)[threadIdx.x] = hs[threadIdx.x];
+            if ((int)threadIdx.x <= nv) h[threadIdx.x] = hs[threadIdx.x];
             __syncthreads();   // (published below)
         }
     }
-    if (!SELF && dots) {
+    if (dots) {
         // gate_after from the coefficients that every wave holds
         const double after = before - wave_sum(lane < nv ? hl * hl : 0.0);
         dots2 = after < g2.tau2 * before;   // gate_open's decision
@@ -346,40 +318,9 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
         if (v0 + 2 * G < nv) load(v0 + 2 * G, a);
         subtract(v0 + G, b);
     }
-    double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < LA_EL; ++k) {
-        if (la_el(base, k) < n) {
-            w[la_el(base, k)] = acc[k];
-            s += acc[k] * acc[k];
-        }
-    }
-    if (red.partials) put_partial<LA_NTH>(red, s);
-    if constexpr (SELF) {
-        __shared__ bool last;
-        __shared__ double sh[LA_NTH / 64], total;
-        if (threadIdx.x == 0) {
-            // release: this work-group's partial (and work-group 0's hout) before its count
-            // (no cache invalidation, which the other work-groups' reads of hpart would pay)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            last = atomicAdd(pub.cnt, 1ull) == (unsigned long long)(gridDim.x - 1);
-        }
-        __syncthreads();
-        if (!last) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every work-group's partial after its count
-        double t = 0.0;
-        for (int i = threadIdx.x; i < (int)gridDim.x; i += LA_NTH) t += red.partials[i];
-        t = block_sum<LA_NTH>(t, sh);   // in thread 0
-        if (threadIdx.x == 0) {
-            pub.out[0] = t;
-            total = t;
-            atomicExch(pub.cnt, 0ull);
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < pub.ns; i += LA_NTH)
-            pub.host[i] = (i == pub.idx) ? total : (i == pub.fidx) ? 1.0 : pub.src[i];
-        return;
-    }
+    for (int k = 0; k < LA_EL; ++k)
+        if (la_el(base, k) < n) w[la_el(base, k)] = acc[k];
     if (!dots2) return;
     dots = mbr(dots, ms);
     constexpr int NW = LA_NTH / 64;
@@ -413,16 +354,109 @@ update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int
 void launch_update(double* w, const double* V, long ld, int nv, long n, double* h, hipStream_t st, const Mb& mb, Gate g2,
                    double* dots, const Publish& pub, const double* hpart)
 {
-    timed_launch(update_kernel<false>, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, (const double*)h,
-                 Gate{}, Red{nullptr, nullptr}, mb.ms, mb.tab, hpart, la_blocks(n), h, g2, dots, pub);
+    timed_launch(update_kernel, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, h, mb.ms, mb.tab, hpart,
+                 la_blocks(n), g2, dots, pub);
+}
+
+// The gated second Gram-Schmidt pass together with the iteration's last reduction and its
+// publication (pub), in one launch.  Where the gate is open h is not given but formed by every
+// work-group from the multi-dot's hnb block partials per entry at hpart (lane-strided sums and
+// the wave sum, a fixed order; work-group 0 stores it to hout), each work-group updates its
+// blocks of w and stores their ||w||^2 partials in red; the last work-group to finish (a
+// release fence and a counter in device memory, so no work-group waits for another) sums the
+// partials in a fixed order into pub.out, publishes, and clears the counter for the next
+// launch.  Where it is closed every work-group returns at once: there are at most
+// UPDATE2_GROUPS of them over all members, each taking blocks of w in turn (with one per
+// block, 9216 of them, the closed gate, the usual case, took 12 us; 1024 of them 4.1).
+__global__ void __launch_bounds__(LA_NTH)
+update2_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int nv, long n, Gate gate, Red red,
+               long ms, const MemberArgs* __restrict__ mt, const double* __restrict__ hpart, int hnb,
+               double* __restrict__ hout, Publish pub)
+{
+    constexpr int G = 4;
+    __shared__ double hs[64], sh[LA_NTH / 64], total;
+    __shared__ bool last;
+    n = len_of(n, mt);
+    gate.h = mbr(gate.h, ms);
+    if (!gate_open(gate)) return;   // every lane takes part in the gate's wave sum
+    pub.out = mbr(pub.out, ms);
+    pub.src = mbr(pub.src, ms);
+    pub.cnt = mbr(pub.cnt, ms);
+    pub.host += (long)blockIdx.z * pub.host_stride;
+    w = mbr(w, ms);
+    V = mbr(V, ms);
+    red = mbr(red, ms);
+    hpart = mbr(hpart, ms);
+    const int lane = threadIdx.x & 63;
+    for (int q = threadIdx.x >> 6; q < nv; q += LA_NTH / 64) {
+        double t = 0.0;
+        for (int i = lane; i < hnb; i += 64) t += hpart[(long)q * hnb + i];
+        t = wave_sum(t);
+        if (lane == 0) hs[q] = t;
+    }
+    __syncthreads();
+    const double hl = hs[min(lane, nv - 1)];   // coefficient v in lane v of every wave
+    if (blockIdx.x == 0 && (int)threadIdx.x < nv) mbr(hout, ms)[threadIdx.x] = hl;
+    for (int blk = blockIdx.x; blk < hnb; blk += gridDim.x) {
+        const long base = (long)blk * LA_NTH * LA_EL + threadIdx.x;
+        double acc[LA_EL];
+        long el[LA_EL];   // (beyond the vector: its first elements, not stored)
+#pragma unroll
+        for (int k = 0; k < LA_EL; ++k) el[k] = la_el(base, k) < n ? la_el(base, k) : 0;
+#pragma unroll
+        for (int k = 0; k < LA_EL; ++k) acc[k] = w[el[k]];
+        for (int v0 = 0; v0 < nv; v0 += G) {
+            double a[G][LA_EL];
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+#pragma unroll
+                for (int k = 0; k < LA_EL; ++k) a[q][k] = V[(long)min(v0 + q, nv - 1) * ld + el[k]];
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const double hv = lane_value(hl, min(v0 + q, nv - 1));
+                if (v0 + q < nv)
+#pragma unroll
+                    for (int k = 0; k < LA_EL; ++k) acc[k] -= hv * a[q][k];
+            }
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < LA_EL; ++k)
+            if (la_el(base, k) < n) {
+                w[el[k]] = acc[k];
+                s += acc[k] * acc[k];
+            }
+        s = block_sum<LA_NTH>(s, sh);   // in thread 0; ends with a barrier
+        if (threadIdx.x == 0) red.partials[blk] = s;
+    }
+    if (threadIdx.x == 0) {
+        // release: this work-group's partials (and work-group 0's hout) before its count
+        // (no cache invalidation, which the other work-groups' reads of hpart would pay)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        last = atomicAdd(pub.cnt, 1ull) == (unsigned long long)(gridDim.x - 1);
+    }
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every work-group's partials after its count
+    double t = 0.0;
+    for (int i = threadIdx.x; i < hnb; i += LA_NTH) t += red.partials[i];
+    t = block_sum<LA_NTH>(t, sh);   // in thread 0
+    if (threadIdx.x == 0) {
+        pub.out[0] = t;
+        total = t;
+        atomicExch(pub.cnt, 0ull);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < pub.ns; i += LA_NTH)
+        pub.host[i] = (i == pub.idx) ? total : (i == pub.fidx) ? 1.0 : pub.src[i];
 }
 
 void launch_update2_publish(double* w, const double* V, long ld, int nv, long n, Gate gate, const double* hpart,
                             double* hout, double* wpart, const Publish& pub, hipStream_t st, const Mb& mb)
 {
-    timed_launch(update_kernel<true>, dim3(la_blocks(n), 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n,
-                 (const double*)nullptr, gate, Red{wpart, nullptr}, mb.ms, mb.tab, hpart, la_blocks(n), hout, Gate{},
-                 (double*)nullptr, pub);
+    const int nb = la_blocks(n), g = std::min(nb, std::max(1, UPDATE2_GROUPS / mb.n));
+    timed_launch(update2_kernel, dim3(g, 1, mb.n), dim3(LA_NTH), st, w, V, ld, nv, n, gate, Red{wpart, nullptr}, mb.ms,
+                 mb.tab, hpart, nb, hout, pub);
 }
 
 __global__ void __launch_bounds__(256)
