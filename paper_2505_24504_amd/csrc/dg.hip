@@ -203,10 +203,20 @@ __device__ __forceinline__ void dg_line(const double* __restrict__ U, long N, un
     }
 }
 
+// The JVP (MODE 3) reads its stored terms ahead and holds a line of both vectors and of the
+// halo's at once: two waves per SIMD, the shorter chain where all work-groups run at the same
+// time (two per CU, 512).  With more of them, LEAN: the halo's lines after the own, the stored
+// terms where they are used, three waves per SIMD; the same products and sums.  Inviscid
+// k = 2, 24 members: 34.3 -> 30.6 us per launch, the ensemble's step 71.5 -> 70.3 ms.  Not
+// for the viscous kernels and k = 3, whose registers would spill (k = 3 viscous, 9.4 M
+// unknowns: 169 us, 201 so).
+constexpr long DG_LEAN_TILES = 512;
+template <int N1, bool NS> constexpr bool DG_LEAN = !NS && N1 <= 3;
+
 // REC: the background records are read from the problem's table (A.rec); without one
 // (the allocation-free residual) wave 0 evaluates the tile's.
-template <int N1, bool NS, int MODE, bool RG, bool REC>
-__global__ void __launch_bounds__(DgShape<N1>::NTH, MODE == 3 ? 2 : 3)
+template <int N1, bool NS, int MODE, bool RG, bool REC, bool LEAN = false>
+__global__ void __launch_bounds__(DgShape<N1>::NTH, MODE == 3 && !LEAN ? 2 : 3)
 dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict__ U, const double* __restrict__ Y,
           const double* __restrict__ Ubar, double* __restrict__ out, const double* __restrict__ yn2p,
           const double* __restrict__ ut2p, int eps_mode, double adt, Red red, long ms, ExStage rk, int ycount)
@@ -294,7 +304,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     double h[4][N1], hy[4][N1];
     int hslot = -1;
     bool hhigh = false;
-    if (wv >= 2) {
+    auto load_halo = [&]() {
+        if (wv < 2) return;
         const int l = t & 63, n = wv == 2 ? NZF : NXF;
         const bool up = l >= n;                           // top or right neighbours: their low end
         const int q = up ? l - n : l, g = q / N1, r = q - g * N1;
@@ -308,7 +319,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         const unsigned o = ok ? (unsigned)((ez * (long)nx + ex) * NP) + (wv == 2 ? r : r * N1) : 0u;
         dg_line<N1>(U, N, o, wv != 2, h);
         if constexpr (MODE == 3) dg_line<N1>(Y, N, o, wv != 2, hy);
-    }
+    };
+    if constexpr (!LEAN) load_halo();
     constexpr int NRL = (BRN * ROWS + NTH - 1) / NTH;   // loads per thread for the node rows
     double rr[NRL], rf = 0.0;
     if constexpr (REC) {
@@ -335,7 +347,7 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     double l0[FCN], urho[N1];
     if constexpr (MODE == 3) {
 #pragma unroll
-        for (int c = 0; c < FCN; ++c) l0[c] = ld(face0 + (long)c * NF, fo0);
+        for (int c = 0; c < FCN; ++c) l0[c] = LEAN ? 0.0 : ld(face0 + (long)c * NF, fo0);
     }
     double eps = 0.0;
     if constexpr (MODE == 3) {
@@ -350,14 +362,14 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         eps = uniform(eps_mode == 0 ? FdEps<double>::sqrt_eps / sqrt(yn2)
                                     : FdEps<double>::sqrt_eps * sqrt(ut2) / sqrt(yn2));
 #pragma unroll
-        for (int j = 0; j < N1; ++j) urho[j] = s[0][j];
+        for (int j = 0; j < N1; ++j) urho[j] = LEAN ? 0.0 : s[0][j];
         // the line of U' + eps y
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
             for (int j = 0; j < N1; ++j) {
                 s[c][j] = s[c][j] + eps * y[c][j];
-                if (wv >= 2) h[c][j] = h[c][j] + eps * hy[c][j];
+                if (!LEAN && wv >= 2) h[c][j] = h[c][j] + eps * hy[c][j];
             }
     }
 
@@ -379,6 +391,14 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         dlo[c] = da;
         sT[c * NSLOT + t] = b;
         if constexpr (NS) sT[(4 + c) * NSLOT + t] = db;
+    }
+    if constexpr (LEAN) {
+        load_halo();
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int j = 0; j < N1; ++j)
+                if (wv >= 2) h[c][j] = h[c][j] + eps * hy[c][j];
     }
     if (hslot >= 0) {
 #pragma unroll
@@ -402,7 +422,7 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     __syncthreads();
     // (JVP) the line's stored volume fluxes, read behind the face work
     double v0[4][N1];
-    if constexpr (MODE == 3) {
+    if constexpr (MODE == 3 && !LEAN) {
         const long vo = xd ? 0 : 4 * N;
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -453,6 +473,10 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
         const bool first = xd ? lx == 0 : lz == 0;   // the low neighbour is outside the tile
         const int slot = first ? NTH + (xd ? lz * N1 + ln : 2 * NXF + lx * N1 + ln) : t - (xd ? N1 : TEX * N1);
         double tl[4], nl[4], Phi[4], slo[3], shi[3];
+        if constexpr (LEAN) {
+#pragma unroll
+            for (int c = 0; c < FCN; ++c) l0[c] = ld(face0 + (long)c * NF, fo0);
+        }
         traces(slot, tl, nl);
         const bool wlo = first && (xd ? ex0 == 0 && !per : ez0 == 0);
         dg_face<NS, BGSUB>(A, tl, nl, tlo, dlo, sB[xd ? lz * N1 + ln : ROWS + lz], xd, wlo, false, Phi, slo, shi);
@@ -542,7 +566,8 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
             }
             if constexpr (MODE == 3) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) F[c] -= v0[c][q];
+                for (int c = 0; c < 4; ++c)
+                    F[c] -= LEAN ? ld(vol0 + (xd ? 0 : 4 * N) + c * N, n0 + q * (xd ? 1 : N1)) : v0[c][q];
             }
             if constexpr (MODE != 5) {
 #pragma unroll
@@ -555,7 +580,12 @@ dg_kernel(DgArgs Aa, const MemberArgs* __restrict__ mt, const double* __restrict
     if constexpr (MODE == 5) return;
     // (JVP) y again, for the output
     if constexpr (MODE == 3) {
-        if (xd) dg_line<N1>(opaque(Y), N, n0, true, y);
+        if (xd) {
+            dg_line<N1>(opaque(Y), N, n0, true, y);
+            if constexpr (LEAN)
+#pragma unroll
+                for (int j = 0; j < N1; ++j) urho[j] = ld(opaque(U), n0 + j);
+        }
     }
     __syncthreads();
     if (valid) {
@@ -651,7 +681,15 @@ static void launch_dg_n(int mode, const DgArgs& A0, const double* U, const doubl
         break;
     case 4: launch(dg_kernel<N1, NS, 4, RG, true>, 0); break;
     case 5: launch(dg_kernel<N1, NS, 5, RG, true>, 0); break;
-    default: launch(dg_kernel<N1, NS, 3, RG, true>, ycount); break;
+    default:
+        if constexpr (DG_LEAN<N1, NS>) {
+            if ((long)grid.x * mb.n > DG_LEAN_TILES) {
+                launch(dg_kernel<N1, NS, 3, RG, true, true>, ycount);
+                break;
+            }
+        }
+        launch(dg_kernel<N1, NS, 3, RG, true>, ycount);
+        break;
     }
 }
 

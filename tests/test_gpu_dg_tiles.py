@@ -92,3 +92,27 @@ def test_noalloc_more_tiles_than_partials():
     tol = 2 * EPS * 0.3 * np.linalg.norm(o.residual(U, 3) / np.tile(dg_mass(d), 4))
     assert np.linalg.norm(to_np(G) - to_np(Gs)) <= tol
     assert abs(float(np.sqrt(to_np(n2)[0])) - nrm) <= 1e-13 * nrm + tol
+
+
+@pytest.mark.parametrize("k", [1, 2])
+def test_jvp_beyond_one_round_of_tiles(k):
+    """The product's form for more tiles than run at once (its loads in another order) against
+    the form for fewer: a member's steps in a lock-step batch of more than 512 tiles have the
+    bits of the member alone."""
+    d = W.small(nx=26, nz=21, k=k, scheme=0, dt=0.6, mg_levels=1, rk_stages=1, newton_rtol=1e-8, newton_stall=1e-7,
+                gmres_m=30, x0=0.0, x1=40.0 * 26, z0=0.0, z1=40.0 * 21)
+    per = -(-26 // TILE[k][0]) * -(-21 // TILE[k][1])
+    members = 512 // per + 1
+    perts = [dict(shape=0, amp=1.0 + 0.01 * m, xc=500.0, zc=400.0, xr=200.0, zr=200.0) for m in range(members)]
+    print(f"case k={k} members={members}", flush=True)
+    q = jfmg.Problem(d, device=DEV)
+    U0 = [q.initial_state(p) for p in perts]
+    pb = jfmg.Problem(dict(d, batch=members), device=DEV)
+    U = torch.cat([u.reshape(-1) for u in U0])
+    assert pb.implicit_step(U)["status"] == 0
+    n = U0[0].numel()
+    for m in (0, members // 2, members - 1):
+        V = U0[m].clone()
+        assert q.implicit_step(V)["status"] == 0
+        assert not torch.equal(V, U0[m])
+        assert torch.equal(V.reshape(-1), U[m * n:(m + 1) * n]), m
