@@ -15,6 +15,7 @@
 // has to start at zero.
 #include "jfmg_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -41,6 +42,16 @@ struct Layout {
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// What a problem is measured by, whatever the kernels need of it: the tables with one more
+// value per node row, and one partial per 16, 14 or 8 elements (k = 1, 2, 3).
+size_t problem_bytes(const jfmg_config& c)
+{
+    const size_t rows = (size_t)c.nz * (c.k + 1), faces = (size_t)c.nz + 1, ne = (size_t)c.nx * c.nz;
+    const size_t per = c.k == 1 ? 16 : c.k == 2 ? 14 : 8;
+    return 2 * align256(rows * 4 * 8) + align256(rows * 8) + 2 * align256(faces * 4 * 8) + align256(rows * 2 * 8) +
+           align256(faces * 2 * 8) + align256((ne + per - 1) / per * 8);
+}
 
 // norm_pass: block partials of a separate norm kernel instead of the DG kernel's
 Layout layout_of(const jfmg_config& c, bool norm_pass)
@@ -132,8 +143,9 @@ extern "C" jfmg_status jfmg_stage_residual_noalloc(const jfmg_config* cfg, const
     Layout L = layout_of(*cfg, false);
     const bool norm_pass = L.end > SCRATCH_BYTES;
     if (norm_pass) L = layout_of(*cfg, true);
-    if (L.end > SCRATCH_BYTES)
-        return report(JFMG_ENOMEM, "problem needs " + std::to_string(L.end) + " bytes of the " +
+    const size_t need = std::max(problem_bytes(*cfg), L.end);
+    if (need > SCRATCH_BYTES)
+        return report(JFMG_ENOMEM, "problem needs " + std::to_string(need) + " bytes of the " +
                                        std::to_string(SCRATCH_BYTES) + "-byte static scratch");
     jfmg::RefTab R;
     if (!jfmg::build_reftab(cfg->k, cfg->transfer, R)) return report(JFMG_EINVAL, "singular subcell transfer");
