@@ -569,15 +569,21 @@ double* fvpart(jfmg_problem* p, int l, int bi) { return p->fvpart + (FVP_PER_LEV
 
 // read `count` device scalars starting at `slot` of every member into
 // out[member * count + i] (synchronizes the stream)
-jfmg_status read_scalars(jfmg_problem* p, int slot, int count, double* out)
+// the scalars that the queued work leaves in hscal, count per member
+jfmg_status wait_scalars(jfmg_problem* p, int count, double* out)
 {
-    if (count > HSCAL) return fail(p, JFMG_EINVAL, "too many scalars");
-    launch_gather(p->scal + slot, count, p->hscal, p->st, p->mb);
     HIPCHK(p, hipStreamSynchronize(p->st));
     std::memcpy(out, p->hscal, sizeof(double) * count * p->mb.n);
     p->syncs++;
     prof_flush(p);
     return JFMG_OK;
+}
+
+jfmg_status read_scalars(jfmg_problem* p, int slot, int count, double* out)
+{
+    if (count > HSCAL) return fail(p, JFMG_EINVAL, "too many scalars");
+    launch_gather(p->scal + slot, count, p->hscal, p->st, p->mb);
+    return wait_scalars(p, count, out);
 }
 
 // gas constants and the binomial coefficients C(gamma, k) of (1 + s)^gamma
@@ -1047,14 +1053,16 @@ jfmg_status stage_residual(jfmg_problem* p, const double* U, const double* Ubar,
 {
     {
         ProfScope ps(p, JFMG_K_DG_RESIDUAL, 3.0 * p->N * 8);
-        launch_dg(p->cfg.k, p->cfg.physics == 1, 2, p->A, U, nullptr, Ubar, G, nullptr, nullptr, 0, adt, red_at(p, S_G),
-                  p->st, p->mb);
+        launch_dg(p->cfg.k, p->cfg.physics == 1, 2, p->A, U, nullptr, Ubar, G, nullptr, nullptr, 0, adt,
+                  Red{p->partials, nullptr}, p->st, p->mb);
     }
+    launch_finalize(p->partials, dg_grid(p->cfg.k, p->A.nx, p->A.nz), 1, p->scal + S_G, p->st, Gate{}, p->mb,
+                    nrm ? p->hscal : nullptr);
     p->lh_count++;
     jfmg_status s = check_launch(p);
     if (s) return s;
     if (nrm) {   // one norm per member
-        s = read_scalars(p, S_G, 1, nrm);
+        s = wait_scalars(p, 1, nrm);
         if (s) return s;
         for (int b = 0; b < p->mb.n; ++b) nrm[b] = std::sqrt(nrm[b]);
     }

@@ -375,7 +375,7 @@ __device__ __forceinline__ double gate_after(const Gate& g)
 __device__ __forceinline__ bool gate_open(const Gate& g) { return !g.h || gate_after(g) < g.tau2 * g.h[g.nv]; }
 
 void launch_finalize(const double* partials, int nb, int nq, double* out, hipStream_t st, Gate gate = Gate{},
-                     const Mb& mb = Mb{});
+                     const Mb& mb = Mb{}, double* host = nullptr);
 void launch_norm2(const double* x, long n, Red red, hipStream_t st, const Mb& mb = Mb{});
 // device scalar slots <-> coherent pinned host memory (count values per member)
 void launch_gather(const double* src, int count, double* host, hipStream_t st, const Mb& mb);

@@ -18,9 +18,11 @@ int la_blocks(long n)
     return (int)((n + (long)LA_NTH * LA_EL - 1) / ((long)LA_NTH * LA_EL));
 }
 
-// out[q] = sum_b p[q * nb + b], one block per q, fixed order (0 where the gate is closed)
+// out[q] = sum_b p[q * nb + b], one block per q, fixed order (0 where the gate is closed); with
+// host (pinned) also host[m * entries + q], which saves the gather launch of a sum that only the
+// host waits for (stage residual and its norm at 1024x256 nodes 28.7 -> 27.5 us)
 __global__ void __launch_bounds__(256) finalize_kernel(const double* __restrict__ p, int nb, double* __restrict__ out,
-                                                       Gate gate, long ms)
+                                                       Gate gate, long ms, double* __restrict__ host)
 {
     p = mbr(p, ms);
     out = mbr(out, ms);
@@ -46,12 +48,16 @@ __global__ void __launch_bounds__(256) finalize_kernel(const double* __restrict_
         for (int k = 0; k < 8; ++k) a += v[k];
     }
     a = block_sum<256>(a, sh);
-    if (threadIdx.x == 0) out[q] = a;
+    if (threadIdx.x == 0) {
+        out[q] = a;
+        if (host) host[blockIdx.z * gridDim.x + q] = a;
+    }
 }
 
-void launch_finalize(const double* partials, int nb, int nq, double* out, hipStream_t st, Gate gate, const Mb& mb)
+void launch_finalize(const double* partials, int nb, int nq, double* out, hipStream_t st, Gate gate, const Mb& mb,
+                     double* host)
 {
-    finalize_kernel<<<dim3(nq, 1, mb.n), dim3(256), 0, st>>>(partials, nb, out, gate, mb.ms);
+    finalize_kernel<<<dim3(nq, 1, mb.n), dim3(256), 0, st>>>(partials, nb, out, gate, mb.ms, host);
 }
 
 // Scalars between the device slots of every member and coherent pinned host
