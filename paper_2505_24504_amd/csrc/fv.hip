@@ -47,7 +47,9 @@ enum { FVM_LIN = 0, FVM_STAGE = 1, FVM_MATVEC = 2, FVM_DEFECT = 3, FVM_STAGE_PC 
 // F_c = (U_c / rho)_K F_0, rho*_K = rho_K (S_K - q_K) / (S_K - S*),
 // p*_K = p_K + rho_K (S_K - q_K)(S* - q_K); S* = q_K in the supersonic cases turns the same
 // expressions into the physical flux.  18 operations fewer than the S*-factored form
-// (S*(S_K U_K - F_K) + S_K p*_K e_D) / (S_K - S*).
+// (S*(S_K U_K - F_K) + S_K p*_K e_D) / (S_K - S*).  In FP32, where the pressure can round to
+// zero and S_K - q_K = c with it, the supersonic rho*_K is rho_K itself instead of 0/0 (in
+// FP64 the root of a zero pressure is no number, which the wave speeds leave out).
 template <typename T, int D>
 __device__ __forceinline__ void fv_hllc(const Gas<T>& G, const T (&UL)[4], const T (&UR)[4], T pL, T pR, T dpL, T dpR,
                                         T irL, T irR, T (&F)[4])
@@ -63,8 +65,14 @@ __device__ __forceinline__ void fv_hllc(const Gas<T>& G, const T (&UL)[4], const
     const bool lk = supL | (!supR & (Ss >= T(0)));
     const T SK = lk ? SL : SR, mK = lk ? mL : mR, qK = lk ? qL : qR, dpK = lk ? dpL : dpR;
     const T uE = lk ? UL[E] * irL : UR[E] * irR, u3 = lk ? UL[3] * irL : UR[3] * irR;
-    const T S = (supL | supR) ? qK : Ss;
-    F[0] = mK * frcp<T>(SK - S) * S;
+    const bool sup = supL | supR;
+    const T S = sup ? qK : Ss;
+    if constexpr (std::is_same_v<T, float>) {
+        const T rK = lk ? UL[0] : UR[0];
+        F[0] = (sup ? rK : mK * frcp<T>(SK - Ss)) * S;
+    } else {
+        F[0] = mK * frcp<T>(SK - S) * S;
+    }
     F[D] = F[0] * S + (dpK + mK * (S - qK));
     F[E] = uE * F[0];
     F[3] = u3 * F[0];

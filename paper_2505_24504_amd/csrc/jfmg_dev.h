@@ -39,17 +39,20 @@ template <typename T> __device__ __forceinline__ T dsqrt(T a)
     if constexpr (std::is_same_v<T, float>) return sqrtf(a);
     else return sqrt(a);
 }
-// Square root of a positive normal number (sound speeds): hardware 1/sqrt
-// estimate; in FP64 one coupled Goldschmidt step for g ~ sqrt(a), h ~ 1/(2 sqrt(a)),
-// then two Newton corrections g += h (a - g^2); in FP32, where the estimate is good
-// to one ulp, one correction (5 operations instead of the library's 16).  Without the
-// rescaling of denormal, zero and infinite arguments that the library square root carries.
+// Square root of a normal number (sound speeds): hardware 1/sqrt estimate; in FP64 one
+// coupled Goldschmidt step for g ~ sqrt(a), h ~ 1/(2 sqrt(a)), then two Newton corrections
+// g += h (a - g^2), positive arguments only; in FP32, where the estimate is good to one
+// ulp, one correction (7 operations instead of the library's 16), and zero and infinity,
+// whose estimate is infinite or zero, are their own roots: an FP32 pressure pb + (p - pb)
+// rounds to zero where (1 + s)^gamma is below half an ulp of one.  Without the library's
+// rescaling of denormal arguments.
 template <typename T> __device__ __forceinline__ T psqrt(T a)
 {
     if constexpr (std::is_same_v<T, float>) {
         const float y = __builtin_amdgcn_rsqf(a);
         const float g = a * y;
-        return fmaf(fmaf(-g, g, a), 0.5f * y, g);
+        constexpr int ZERO_INF = 0x260;   // -0, +0, +inf
+        return __builtin_amdgcn_classf(a, ZERO_INF) ? a : fmaf(fmaf(-g, g, a), 0.5f * y, g);
     } else {
         const double y = __builtin_amdgcn_rsq(a);
         double g = a * y, h = 0.5 * y;
