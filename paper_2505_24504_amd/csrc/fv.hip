@@ -1128,9 +1128,10 @@ static int tile_launch_shape(const FvArgs<T>& A, const T* u, const T* F0, const 
     // Every work-group sums all partials of ||x||^2 by itself, which saves a launch (3 us)
     // while they are few; 4608 of them, read by as many work-groups, made the second stage of
     // 2.4 M cells take 82 us where the one after 1024 partials took 45: one launch before it.
+    // (Not a timed launch: the caller's kernel class is that of the tile kernel.)
     if (MODE != FVM_LIN && xcount > FV_SUM_MAX) {
-        timed_launch(fv_sum_kernel<NTH>, dim3(1, 1, (unsigned)mb.n), dim3(NTH), st, const_cast<double*>(xpart), xcount,
-                     mb.n > 1 ? mb.ms : 0L);
+        fv_sum_kernel<NTH><<<dim3(1, 1, (unsigned)mb.n), dim3(NTH), 0, st>>>(const_cast<double*>(xpart), xcount,
+                                                                             mb.n > 1 ? mb.ms : 0L);
         xpart += xcount;
         xcount = 1;
     }

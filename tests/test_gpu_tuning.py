@@ -1,0 +1,40 @@
+"""The instruments that a user tunes and measures with: the kernel-class timing and the tile
+autotuner, where a launch is preceded or replaced by another kernel."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2505_24504_amd import jfmg, workloads as W  # noqa: E402
+
+from gpu_common import DEV  # noqa: E402
+
+
+def setup_module(module):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    jfmg.load_library()
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+def test_stage_timing_behind_summed_partials(prec):
+    """1024 x 1024 cells in 256-cell tiles: 4096 partial sums of ||x||^2, which a kernel of a
+    few us adds up before each stage.  The class times the stage and not that kernel: its mean
+    launch is at least half of what the autotuner measures for the same shape, whose launches
+    have 1024 partials and no such kernel before them (a sum alone is below a tenth of it)."""
+    d = W.small(nx=256, nz=256, k=3, mg_levels=1, mg_key="mg008802V", rk_stages=1, mg_precision=prec,
+                x1=256 * 40.0, z1=256 * 40.0)
+    p = jfmg.Problem(d, device=DEV)
+    U = p.initial_state(dict(shape=0, amp=1.0, xc=5000.0, zc=5000.0, xr=2000.0, zr=2000.0))
+    p.linearize(U, 0.3)
+    _, times = p.autotune(reps=10)
+    p.set_tiles(["64x4_512"])
+    b = torch.randn(p.fv_size(0), device=DEV, generator=torch.Generator(device=DEV).manual_seed(3), dtype=p.fv_dtype)
+    p.mg_fv(b)
+    p.profile_enable(["fv_stage"])
+    p.mg_fv(b)
+    r = p.profile_read()["fv_stage"]
+    mean = 1e3 * r["ms"] / r["launches"]
+    print(f"fp{prec}: stage {mean:.1f} us, autotuner {times[0]['64x4_512']:.1f} us", flush=True)
+    assert r["launches"] == 15
+    assert mean >= 0.5 * times[0]["64x4_512"]
