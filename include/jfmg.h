@@ -284,6 +284,8 @@ jfmg_status jfmg_set_tiles(jfmg_problem* p, const int* shapes);
 /* Autotuner: on every level, time every shape with `reps` back-to-back launches
    (after one warm-up launch) of the smoother stage kernel at the current
    linearization state, with a fixed nonzero test vector, and keep the fastest.
+   Where the coarsest levels of a V-cycle in 8x4 tiles go in one launch, the time of
+   8x4 on such a level is its share of that launch.
    A lock-step batch times all its members in each launch.  shapes (mg_levels
    entries) receives the choice and times_us (mg_levels * JFMG_TILE_NSHAPE
    entries, level-major) the mean launch time in microseconds; either may be

@@ -702,6 +702,18 @@ double smoother_alpha(const jfmg_problem* p, int j)
     return p->cfg.rk_alpha[j] > 0 ? p->cfg.rk_alpha[j] : 1.0 / (p->cfg.rk_stages - j);
 }
 
+// whether the cycle is one whose levels l .. nlev - 1 may go in one launch, and the products
+// g'x of such a level in a cycle (its launches, otherwise)
+bool tail_key(const jfmg_problem* p, int l)
+{
+    const Key& k = p->key;
+    return l >= 1 && k.cycle == 1 && k.e >= 1 && k.f >= 1 && (l > 1 || k.c >= 1) && p->nlev - l <= TAIL_LEV;
+}
+int tail_products(const jfmg_problem* p, int l)
+{
+    return (p->key.e + p->key.f) * p->cfg.rk_stages - 1 + (l + 1 < p->nlev ? 1 : 0);
+}
+
 template <typename T> struct Mg {
     jfmg_problem* p;
     MgState s;
@@ -814,8 +826,7 @@ template <typename T> struct Mg {
     // entered with the first stage from x = 0 made by the producer of b)
     bool tail_fits(int l, int pc) const
     {
-        const Key& k = p->key;
-        if (l < 1 || pc != l - 1 || k.cycle != 1 || k.e < 1 || k.f < 1 || p->nlev - l > TAIL_LEV) return false;
+        if (pc != l - 1 || !tail_key(p, l)) return false;
         if (!s.xzero[l] || s.xzero[pc] || s.pre[l] < 1 || s.pre[l] > 256) return false;
         for (int m = l; m < p->nlev; ++m)
             if (!fv_tail_fits(p->lev[m].nx, p->lev[m].nz, p->lev[m].tile)) return false;
@@ -823,36 +834,43 @@ template <typename T> struct Mg {
     }
     void tail(int l, int pc)
     {
-        const Key& k = p->key;
-        const int S = p->cfg.rk_stages;
+        const TailArgs<T> a = tail_args(l, s.xi[pc], s.pre[l]);
+        double bytes = 0.0;
+        for (int m = 0; m < a.n; ++m) {
+            bytes += (m == 0 ? 11.0 : 2.0) * 4.0 * p->lev[l + m].nc * sizeof(T);   // u, F0; the top level's b, and x_f read and written
+            p->mv_count[l + m] += tail_products(p, l + m);
+        }
+        ProfScope ps(p, JFMG_K_FV_STAGE_SMALL, bytes);
+        p->xcnt[pc][s.xi[pc]] = FvLaunch<T>::tail(a, p->st, p->mb);
+        s.pre[l] = 0;
+    }
+    // the launch of levels l .. nlev - 1: xcount partials of the first stage from x = 0, the
+    // correction to buffer xi of level l - 1
+    TailArgs<T> tail_args(int l, int xi, int xcount) const
+    {
         TailArgs<T> a{};
         a.n = p->nlev - l;
         a.lev0 = l;
-        a.pre = k.e;
-        a.post = k.f;
-        a.S = S;
-        for (int j = 0; j < S; ++j) a.alpha[j] = alpha[j];
+        a.pre = p->key.e;
+        a.post = p->key.f;
+        a.S = p->cfg.rk_stages;
+        for (int j = 0; j < a.S; ++j) a.alpha[j] = alpha[j];
         a.adt = p->adt;
         a.A = fv_args<T>(p, l);
-        double bytes = 0.0;
         for (int m = 0; m < a.n; ++m) {
-            Level& L = p->lev[l + m];
+            const Level& L = p->lev[l + m];
             a.rc[m] = (const T*)L.rc;
             a.rf[m] = (const T*)L.rf;
             a.u[m] = (const T*)L.u;
             a.F0[m] = (const T*)L.F0;
-            bytes += (m == 0 ? 11.0 : 2.0) * 4.0 * L.nc * sizeof(T);   // u, F0; the top level's b, and x_f read and written
-            p->mv_count[l + m] += (k.e + k.f) * S - 1 + (m < a.n - 1 ? 1 : 0);
         }
         a.slots = p->scal + S_LEV + 4 * l;
         a.b = (const T*)p->lev[l].b;
         a.xpart = fvpart(p, l, 1);
-        a.xcount = s.pre[l];
-        a.xf = (T*)p->lev[pc].buf[s.xi[pc]];
-        a.red = Red{fvpart(p, pc, s.xi[pc]), nullptr};
-        ProfScope ps(p, JFMG_K_FV_STAGE_SMALL, bytes);
-        p->xcnt[pc][s.xi[pc]] = FvLaunch<T>::tail(a, p->st, p->mb);
-        s.pre[l] = 0;
+        a.xcount = xcount;
+        a.xf = (T*)p->lev[l - 1].buf[xi];
+        a.red = Red{fvpart(p, l - 1, xi), nullptr};
+        return a;
     }
 
     // MG_l; with pc >= 0 the final smoother stage applies the correction of level pc
@@ -1493,39 +1511,61 @@ template <typename T> jfmg_status autotune_t(jfmg_problem* p, int reps, int* sha
         return fail(p, JFMG_EDEVICE, "hipEventCreate failed");
     }
     jfmg_status res = JFMG_OK;
+    // mean milliseconds of a launch
+    auto time_launches = [&](auto launch) {
+        launch();
+        float ms = 0.0f;
+        if (hipEventRecord(e0, st) != hipSuccess) { res = fail(p, JFMG_EDEVICE, "hipEventRecord failed"); return ms; }
+        for (int r = 0; r < reps; ++r) launch();
+        if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+            hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+            res = fail(p, JFMG_EDEVICE, "event timing failed");
+        return ms / reps;
+    };
+    // test vector in buffer 0 (fixed pattern of O(1) values) and its norm partials
+    auto pattern = [&](int l, int bi) {
+        const long n = 4 * p->lev[l].nc;
+        launch_fill_pattern((T*)p->lev[l].buf[0], n, st, p->mb);
+        FvLaunch<T>::norm2((const T*)p->lev[l].buf[0], n, Red{fvpart(p, l, bi), nullptr}, st, p->mb);
+        return FvLaunch<T>::norm_blocks(n);
+    };
+    float t[MAXLEV][JFMG_TILE_NSHAPE] = {};
     for (int l = 0; l < p->nlev && res == JFMG_OK; ++l) {
         Level& L = p->lev[l];
-        const long n = 4 * L.nc;
-        // test vector in buffer 0 (fixed pattern of O(1) values) and its norm partials
-        launch_fill_pattern((T*)L.buf[0], n, st, p->mb);
-        FvLaunch<T>::norm2((const T*)L.buf[0], n, Red{fvpart(p, l, 0), nullptr}, st, p->mb);
-        const int xc = FvLaunch<T>::norm_blocks(n);
-        int best = L.tile;
-        float best_ms = 0.0f;
-        for (int sh = 0; sh < JFMG_TILE_NSHAPE; ++sh) {
+        const int xc = pattern(l, 0);
+        for (int sh = 0; sh < JFMG_TILE_NSHAPE && res == JFMG_OK; ++sh) {
             FvArgs<T> A = fv_args<T>(p, l);
             A.tile = sh;
-            auto launch = [&]() {
+            t[l][sh] = time_launches([&]() {
                 FvLaunch<T>::stage(A, (const T*)L.u, (const T*)L.F0, (const T*)L.buf[0], (const T*)L.buf[0],
                                    (const T*)L.buf[0], (T*)L.buf[1], fvpart(p, l, 0), xc, p->scal + S_LEV + 4 * l,
                                    1.0, p->adt, 0, Red{fvpart(p, l, 1), nullptr}, st, p->mb);
-            };
-            launch();
-            if (hipEventRecord(e0, st) != hipSuccess) { res = fail(p, JFMG_EDEVICE, "hipEventRecord failed"); break; }
-            for (int r = 0; r < reps; ++r) launch();
-            float ms = 0.0f;
-            if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
-                res = fail(p, JFMG_EDEVICE, "event timing failed");
-                break;
-            }
-            if (times_us) times_us[l * JFMG_TILE_NSHAPE + sh] = 1e3 * ms / reps;
-            if (sh == 0 || ms < best_ms) { best = sh; best_ms = ms; }
+            });
         }
-        if (res == JFMG_OK) {
-            L.tile = best;
-            if (shapes) shapes[l] = best;
-        }
+    }
+    // The coarsest levels that 8x4 tiles put in one launch (from l0 on; Mg::tail_fits): 8x4 stands
+    // there for that launch, each level's share of it in proportion to its launches in the fastest
+    // shapes.  The stage alone does not decide between 8x4 and 16x4 on such levels (3.7 and 3.8 us
+    // in FP32), but any other shape on one of them takes the others' single launch away too:
+    // implicit Euler step of 16x16 elements, k = 1, 8.7 ms with it and 12.6 without.
+    int l0 = p->nlev;
+    while (l0 > 1 && fv_tail_fits(p->lev[l0 - 1].nx, p->lev[l0 - 1].nz, JFMG_TILE_8x4) && tail_key(p, l0 - 1)) --l0;
+    if (l0 < p->nlev && res == JFMG_OK) {
+        Mg<T> mg{p};
+        mg.init();
+        const int xc = pattern(l0, 1);
+        launch_fill_pattern((T*)p->lev[l0].b, 4 * p->lev[l0].nc, st, p->mb);
+        const TailArgs<T> a = mg.tail_args(l0, 0, xc);
+        const float one = time_launches([&]() { FvLaunch<T>::tail(a, st, p->mb); });
+        float own = 0.0f;
+        for (int l = l0; l < p->nlev; ++l) own += tail_products(p, l) * *std::min_element(t[l], t[l] + JFMG_TILE_NSHAPE);
+        for (int l = l0; l < p->nlev && res == JFMG_OK; ++l)
+            t[l][JFMG_TILE_8x4] = *std::min_element(t[l], t[l] + JFMG_TILE_NSHAPE) * (one / own);
+    }
+    for (int l = 0; l < p->nlev && res == JFMG_OK; ++l) {
+        p->lev[l].tile = (int)(std::min_element(t[l], t[l] + JFMG_TILE_NSHAPE) - t[l]);
+        if (shapes) shapes[l] = p->lev[l].tile;
+        for (int sh = 0; sh < JFMG_TILE_NSHAPE && times_us; ++sh) times_us[l * JFMG_TILE_NSHAPE + sh] = 1e3 * t[l][sh];
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

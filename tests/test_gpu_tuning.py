@@ -38,3 +38,31 @@ def test_stage_timing_behind_summed_partials(prec):
     print(f"fp{prec}: stage {mean:.1f} us, autotuner {times[0]['64x4_512']:.1f} us", flush=True)
     assert r["launches"] == 15
     assert mean >= 0.5 * times[0]["64x4_512"]
+
+
+# (config, the levels that go in one launch in 8x4 tiles)
+def _tuned_cases():
+    d, _, _ = W.bubble_small()
+    out = []
+    for prec in (32, 64):
+        out.append((dict(d, mg_precision=prec), [1, 2]))                       # 16x16, 8x8
+        out.append((dict(d, mg_precision=prec, nx=12, nz=8, rk_stages=1), [1, 2]))   # 12x8, 6x4
+        out.append((dict(d, mg_precision=prec, nx=16, nz=8, mg_levels=4), [1, 2, 3]))   # 16x8, 8x4, 4x2
+    return out
+
+
+@pytest.mark.parametrize("case", _tuned_cases())
+def test_tuned_problem_keeps_the_one_launch_levels(case):
+    """The coarse levels that go in one launch in the default shapes do so after tuning: that
+    launch saves half of the time of the levels' own, so that no other shape is the fastest."""
+    d, levels = case
+    p = jfmg.Problem(d, device=DEV)
+    assert [l for l, t in enumerate(p.get_tiles()) if t == "8x4"][-len(levels):] == levels
+    U = p.initial_state(dict(shape=0, amp=0.5, xc=500.0, zc=350.0, xr=250.0, zr=250.0))
+    p.linearize(U, 0.5)
+    mv = p.implicit_step(U.clone())["fv_matvecs"]
+    for _ in range(3):
+        shapes, times = p.autotune(reps=20)
+        print([(l, {s: round(t, 2) for s, t in times[l].items()}) for l in levels], flush=True)
+        assert [shapes[l] for l in levels] == ["8x4"] * len(levels)
+    assert p.implicit_step(U.clone())["fv_matvecs"] == mv
