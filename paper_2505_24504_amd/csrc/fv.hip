@@ -366,7 +366,13 @@ fv_tile_kernel(FvArgs<T> Aa, const MemberArgs* __restrict__ mt, const T* __restr
     T eps = T(0), sc = T(0);
     bool xzero = false;   // uniform: g'x = 0 for x = 0
     if constexpr (PERT) {
-        const double xn2 = xsum.sum(xpart, xcount);   // ||x||^2, same order in every block
+        // ||x||^2, same order in every block.  The FP64 64x4 tile that transfers back exchanges it
+        // through the x-fluxes' array (the barrier behind the staged states comes before the first
+        // flux): with 2 KB of its own for it, three of its work-groups would fit a CU, not four.
+        constexpr bool LEND = TI && sizeof(T) == 8 && NTH == 256 && NCELL == NTH;
+        double xn2;
+        if constexpr (LEND) xn2 = xsum.sum(xpart, xcount, reinterpret_cast<double*>(&sFx[0][0][0]));
+        else xn2 = xsum.sum(xpart, xcount);
         if (!(xn2 > 0.0)) {
             xzero = true;
         } else {

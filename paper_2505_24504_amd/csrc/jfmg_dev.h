@@ -367,9 +367,14 @@ template <int NTH> struct PartialSum {
             v[k] = i < n ? x : 0.0;              // wait for the loads behind them)
         }
     }
+    // with sh: through these NTH doubles of the caller's LDS
     __device__ __forceinline__ double sum(const double* p, int n)
     {
-        __shared__ double sh[NW][64];
+        __shared__ double sh[NTH];
+        return sum(p, n, sh);
+    }
+    __device__ __forceinline__ double sum(const double* p, int n, double* sh)
+    {
         double s;
         if (n <= 64 * NV) {
             double w[NW < NV ? NW : NV];
@@ -395,11 +400,11 @@ template <int NTH> struct PartialSum {
                 for (int k = 0; k < 8; ++k) a += x[k];
             }
             const int lane = threadIdx.x & 63;
-            sh[threadIdx.x >> 6][lane] = a;
+            sh[threadIdx.x] = a;
             __syncthreads();
-            s = sh[0][lane];
+            s = sh[lane];
 #pragma unroll
-            for (int k = 1; k < NW; ++k) s += sh[k][lane];
+            for (int k = 1; k < NW; ++k) s += sh[64 * k + lane];
         }
         return wave_sum(s);
     }
