@@ -224,10 +224,10 @@ void launch_multidot(const double* w, const double* V, long ld, int nv, int self
 // replaced by pub.out's value, entry fidx by 1 where the second pass ran (else 0) and, where
 // the gate is closed, entries zoff .. zoff+zn (the skipped pass's coefficients) by 0, so the
 // host reads the Hessenberg column after the iteration's completion event without a separate
-// copy.
+// copy.  (h lies in that block and is not restrict.)
 __global__ void __launch_bounds__(LA_NTH)
 update_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int nv, long n,
-              double* __restrict__ h, long ms, const MemberArgs* __restrict__ mt, const double* __restrict__ hpart,
+              double* h, long ms, const MemberArgs* __restrict__ mt, const double* __restrict__ hpart,
               int hnb, Gate g2, double* __restrict__ dots, Publish pub)
 {
     constexpr int G = 4;
@@ -377,7 +377,7 @@ void launch_update(double* w, const double* V, long ld, int nv, long n, double* 
 __global__ void __launch_bounds__(LA_NTH)
 update2_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int nv, long n, Gate gate, Red red,
                long ms, const MemberArgs* __restrict__ mt, const double* __restrict__ hpart, int hnb,
-               double* __restrict__ hout, Publish pub)
+               double* hout, Publish pub)
 {
     constexpr int G = 4;
     __shared__ double hs[64], sh[LA_NTH / 64], total;
