@@ -538,14 +538,23 @@ def preconditioner_keys(steps=2):
     return out
 
 
+def jvp_bytes(nx, nz, k, viscous):
+    """Algorithmic bytes of a jfmg_jvp call: a pass over y for ||y||, then U' and y in and
+    the product out, and the stored terms of the linearization state: 8 volume fluxes per
+    node and, at every face point of the grid once, the flux's 4 components and in viscous
+    flow both sides' 3 jumps."""
+    nodes = nx * nz * (k + 1) ** 2
+    face_points = (k + 1) * ((nx + 1) * nz + nx * (nz + 1))
+    return 8 * (4 * 4 * nodes + 8 * nodes + (10 if viscous else 4) * face_points)
+
+
 def large_roofline(reps=20):
     """The FV operator and the DG JVP on vectors far above the 256 MB cache:
     a 1024x1024-quad, k = 3 problem (FV level 4096x4096 cells, DG vector 537 MB,
     density-current physics).  GB/s of algorithmic bytes of the whole call: an FV
     matvec call reads x for ||x|| (eps), then u, F0 and x (with halo) and writes
-    g'x (5 vectors); a JVP call reads y for ||y||, then U and y, and writes the
-    product (4 vectors).  Events on the launch stream bracket `reps` back-to-back
-    calls."""
+    g'x (5 vectors); a JVP call moves jvp_bytes.  Events on the launch stream bracket
+    `reps` back-to-back calls."""
     import ctypes
     import torch
     from paper_2505_24504_amd import jfmg, workloads as W
@@ -567,10 +576,8 @@ def large_roofline(reps=20):
         res = {}
         for name, call, nbytes in (
                 ("fv_matvec_4096x4096", lambda: p.L.jfmg_fv_matvec(p.h, 0, ptr(x), ptr(xo)), 5 * nfv * x.element_size()),
-                # ||y||^2 pass, then U', y in, G'y out, and the linearization state's volume
-                # fluxes and face terms (8 + 8 doubles per node at k = 3)
                 ("dg_jvp_1024x1024_k3", lambda: p.L.jfmg_jvp(p.h, ptr(y), ptr(yo)),
-                 4 * p.ndof * 8 + 8 * (8 * (p.ndof // 4) + 8 * (p.ndof // 64) * 16))):
+                 jvp_bytes(d["nx"], d["nz"], d["k"], True))):
             if prec == 32 and name.startswith("dg"):
                 continue
             assert call() == 0

@@ -66,3 +66,18 @@ def test_tuned_problem_keeps_the_one_launch_levels(case):
         print([(l, {s: round(t, 2) for s, t in times[l].items()}) for l in levels], flush=True)
         assert [shapes[l] for l in levels] == ["8x4"] * len(levels)
     assert p.implicit_step(U.clone())["fv_matvecs"] == mv
+
+
+@pytest.mark.parametrize("physics", [0, 1])
+def test_jvp_bytes_are_the_librarys(physics):
+    """bench.py's bytes of a JVP call are the library's of its kernel and a pass over y."""
+    import bench
+    d = W.small(nx=7, nz=5, k=3, physics=physics, mu=75.0 if physics else 0.0, mg_levels=1)
+    p = jfmg.Problem(d, device=DEV)
+    U = p.initial_state(dict(shape=0, amp=1.0, xc=500.0, zc=400.0, xr=200.0, zr=200.0))
+    p.linearize(U, 0.3)
+    p.profile_enable(["dg_jvp"])
+    p.jvp(U)
+    r = p.profile_read()["dg_jvp"]
+    assert r["launches"] == 1
+    assert bench.jvp_bytes(7, 5, 3, physics == 1) == r["bytes"] + 8 * p.ndof
