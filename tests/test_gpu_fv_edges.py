@@ -1,7 +1,8 @@
 """The FV operator's tile kernels at the edges of their tiles: levels narrower than a
 tile, one cell more or less than whole tiles, single rows, walls and x-periodic (the
-wrapped halo column), and more partial sums of ||x||^2 than a wave holds.  Bound: the
-matvec's parity bound."""
+wrapped halo column), in the FP64 matvec, whose ||x||^2 is one finished sum, against its
+parity bound; steps with more partial sums of ||x||^2 than a consumer adds up; and the
+coarsest levels in one launch."""
 import numpy as np
 import pytest
 import torch
@@ -74,7 +75,7 @@ def test_partials_summed_before_their_consumers(prec):
 
 # (k, nx, nz, levels, stages, bc, physics, precision): the coarser levels, small enough for one
 # launch of one work-group, are 16x16 and 8x8 cells; 18x6 (behind 36x12, which is too large);
-# 12x4 and 6x2, x-periodic; 36x8, 18x4 and 9x2; 2x2, less than a tile
+# 12x4 and 6x2, x-periodic; 18x12 and 9x6 (behind 36x24); 2x2, less than a tile
 TAILS = [(1, 16, 16, 3, 3, 0, 0, 64), (2, 24, 8, 3, 1, 0, 1, 32), (3, 6, 2, 3, 1, 1, 0, 64), (2, 24, 16, 4, 2, 1, 1, 32),
          (1, 2, 2, 2, 1, 0, 0, 64)]
 
