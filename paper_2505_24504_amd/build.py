@@ -26,8 +26,8 @@ def hipcc():
 def build(verbose: bool = False, jobs: int = 5, out: str = LIB, defines: tuple = ()) -> str:
     """Compile every HIP source to an object, then link the shared library.
 
-    `defines` (e.g. ("FV_COARSE_NTH=192",)) override the tile constants of the
-    kernels; `out` names the library file (objects go to a folder beside it)."""
+    `defines` go to the compiler as -D options; `out` names the library file (objects
+    go to a folder beside it)."""
     objdir = os.path.join(HERE, "_build") if out == LIB else out + ".objs"
     os.makedirs(objdir, exist_ok=True)
     procs = []

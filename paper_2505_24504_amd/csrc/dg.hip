@@ -92,7 +92,7 @@ __device__ __forceinline__ void dg_record(const DgArgs& A, bool zr, int i, int v
         if (v == 1 || (zr && i == 0)) UL[1] = -UL[1];
         if (v == 2 || (zr && i == A.nz)) UR[1] = -UR[1];
         const double ir = frcp(rho);
-        hllc_ax<double, 1>(A.gas, UL, UR, pb, pb, pb, pb, ir, ir, H);
+        hllc(A.gas, UL, UR, pb, pb, ir, ir, H);
 #pragma unroll
         for (int c = 0; c < 4; ++c) rec[(v == 0 ? BR_H : v == 1 ? BR_HLO : BR_HHI) + c] = H[c];
         if (v == 0) {
@@ -153,7 +153,7 @@ __device__ __forceinline__ void dg_face(const DgArgs& A, double (&tl)[4], const 
     pert_pressures<double, 2, false>(A.gas, rt, ir2, pb2, pp);
     const double pL = pp[0], pR = pp[1];
     const double irL = frcp(UL[0]), irR = frcp(UR[0]);
-    hllc_ax<double, 1>(A.gas, UL, UR, pL, pR, pL, pR, irL, irR, Phi);
+    hllc(A.gas, UL, UR, pL, pR, irL, irR, Phi);
     if constexpr (BGSUB) {
         const double* hb = row + (wlo && xf ? BR_HLO : whi && xf ? BR_HHI : BR_H);
 #pragma unroll
@@ -677,7 +677,7 @@ static void launch_dg_n(int mode, const DgArgs& A0, const double* U, const doubl
         } else {
             launch(dg_kernel<N1, NS, 2, true, true>, 0);
         }
-        if (red.out) launch_finalize(red.partials, (int)grid.x, 1, red.out, st, Gate{}, mb);
+        if (red.out) launch_finalize(red.partials, (int)grid.x, 1, red.out, st, mb);
         break;
     case 4: launch(dg_kernel<N1, NS, 4, RG, true>, 0); break;
     case 5: launch(dg_kernel<N1, NS, 5, RG, true>, 0); break;
@@ -809,7 +809,7 @@ void launch_norm2_total(int k, const DgArgs& A, const double* U, Red red, hipStr
     if (k == 1) launch_norm_total_k<2>(A, U, red, st, mb, grid);
     else if (k == 2) launch_norm_total_k<3>(A, U, red, st, mb, grid);
     else launch_norm_total_k<4>(A, U, red, st, mb, grid);
-    launch_finalize(red.partials, (int)grid.x, 1, red.out, st, Gate{}, mb);
+    launch_finalize(red.partials, (int)grid.x, 1, red.out, st, mb);
 }
 
 }  // namespace jfmg

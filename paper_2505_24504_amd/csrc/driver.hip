@@ -567,9 +567,7 @@ Red no_red() { return Red{nullptr, nullptr}; }
 int mass_fix_of(const jfmg_problem* p) { return p->cfg.transfer == 0 ? p->cfg.mass_fix : 0; }
 double* fvpart(jfmg_problem* p, int l, int bi) { return p->fvpart + (FVP_PER_LEVEL * l + bi) * p->fvp; }
 
-// read `count` device scalars starting at `slot` of every member into
-// out[member * count + i] (synchronizes the stream)
-// the scalars that the queued work leaves in hscal, count per member
+// the scalars that the queued work leaves in hscal, count per member (synchronizes the stream)
 jfmg_status wait_scalars(jfmg_problem* p, int count, double* out)
 {
     HIPCHK(p, hipStreamSynchronize(p->st));
@@ -579,6 +577,8 @@ jfmg_status wait_scalars(jfmg_problem* p, int count, double* out)
     return JFMG_OK;
 }
 
+// read `count` device scalars starting at `slot` of every member into
+// out[member * count + i]
 jfmg_status read_scalars(jfmg_problem* p, int slot, int count, double* out)
 {
     if (count > HSCAL) return fail(p, JFMG_EINVAL, "too many scalars");
@@ -627,7 +627,7 @@ template <typename T> FvArgs<T> fv_args(const jfmg_problem* p, int l)
     FvArgs<T> A;
     const Level& L = p->lev[l];
     A.nxl = L.nx; A.nzl = L.nz; A.bc = p->cfg.bc; A.physics = p->cfg.physics; A.nc = L.nc;
-    A.hx = (T)L.hx; A.hz = (T)L.hz; A.area = (T)(L.hx * L.hz); A.iarea = (T)(1.0 / (L.hx * L.hz)); A.g = (T)p->cfg.g; A.mu = (T)p->cfg.mu;
+    A.hx = (T)L.hx; A.hz = (T)L.hz; A.iarea = (T)(1.0 / (L.hx * L.hz)); A.g = (T)p->cfg.g; A.mu = (T)p->cfg.mu;
     A.gas = make_gas<T>(p->cfg);
     A.rc = (const T*)L.rc; A.rf = (const T*)L.rf;
     A.tile = L.tile;
@@ -796,7 +796,7 @@ template <typename T> struct Mg {
                                                      p->scal + S_LEV + 4 * l, alpha[j], p->adt, tinv_red, p->st,
                                                      p->mb);
                     }
-                    if (tinv_red.out) launch_finalize(tinv_red.partials, nb, 1, tinv_red.out, p->st, Gate{}, p->mb);
+                    if (tinv_red.out) launch_finalize(tinv_red.partials, nb, 1, tinv_red.out, p->st, p->mb);
                     p->mv_count[l]++;
                     tinv_done = true;
                     tinv_count = nb;
@@ -1074,7 +1074,7 @@ jfmg_status stage_residual(jfmg_problem* p, const double* U, const double* Ubar,
         launch_dg(p->cfg.k, p->cfg.physics == 1, 2, p->A, U, nullptr, Ubar, G, nullptr, nullptr, 0, adt,
                   Red{p->partials, nullptr}, p->st, p->mb);
     }
-    launch_finalize(p->partials, dg_grid(p->cfg.k, p->A.nx, p->A.nz), 1, p->scal + S_G, p->st, Gate{}, p->mb,
+    launch_finalize(p->partials, dg_grid(p->cfg.k, p->A.nx, p->A.nz), 1, p->scal + S_G, p->st, p->mb,
                     nrm ? p->hscal : nullptr);
     p->lh_count++;
     jfmg_status s = check_launch(p);
@@ -1747,7 +1747,7 @@ template <typename T> FvArgs<T> fv_args_of(const jfmg_problem* p, const jfmg_con
     A.nxl = (p->n1 * c.nx) >> l; A.nzl = (p->n1 * c.nz) >> l; A.bc = c.bc; A.physics = c.physics;
     A.nc = (long)A.nxl * A.nzl;
     const double hx = (c.x1 - c.x0) / A.nxl, hz = (c.z1 - c.z0) / A.nzl;
-    A.hx = (T)hx; A.hz = (T)hz; A.area = (T)(hx * hz); A.iarea = (T)(1.0 / (hx * hz)); A.g = (T)c.g; A.mu = (T)c.mu;
+    A.hx = (T)hx; A.hz = (T)hz; A.iarea = (T)(1.0 / (hx * hz)); A.g = (T)c.g; A.mu = (T)c.mu;
     A.gas = make_gas<T>(c);
     A.rc = at(L.rc); A.rf = at(L.rf);
     A.tile = L.tile;

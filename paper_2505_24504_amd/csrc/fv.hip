@@ -11,11 +11,12 @@
 // terms cancel, and the difference then loses digits only at the scale of
 // p - pb and of the other fluxes, not at that of pb (about 10^5 Pa).
 //
-// Layout: SoA [4][nzl][nxl].  A work-group is a 64 x 4 tile of cells (one
-// wave per row of 64 cells along x, so loads of a component are 256-byte
-// coalesced); neighbours come through the caches.  Every kernel that produces
-// a vector the next FD product needs also produces its squared norm through a
-// deterministic two-level reduction.
+// Layout: SoA [4][nzl][nxl].  A work-group of the operator kernels is a tile of
+// cells (six shapes, below) whose states go to LDS with a halo of one cell; each
+// face of the tile gets its flux once.  The streaming kernels take 64 x 4 tiles,
+// one wave per row of 64 cells.  Every kernel that produces a vector the next FD
+// product needs also produces its squared norm through a deterministic two-level
+// reduction.
 #include "jfmg_internal.h"
 
 namespace jfmg {
@@ -1278,7 +1279,7 @@ template <typename T>
 void FvLaunch<T>::norm2(const T* x, long n, Red red, hipStream_t st, const Mb& mb)
 {
     fv_norm2_kernel<T><<<dim3(norm_blocks(n), 1, mb.n), dim3(256), 0, st>>>(x, n, red, mb.ms);
-    if (red.out) launch_finalize(red.partials, norm_blocks(n), 1, red.out, st, Gate{}, mb);
+    if (red.out) launch_finalize(red.partials, norm_blocks(n), 1, red.out, st, mb);
 }
 // The default shape by the level's cells (in a ragged batch those of all members, which
 // share a launch).  Stage kernel, FP64 / FP32, us (viscous 256 x 64 and 768 x 192 elements

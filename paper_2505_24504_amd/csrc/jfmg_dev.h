@@ -1,5 +1,5 @@
-// Device helpers shared by the gfx950 kernels: gas physics, the HLLC flux,
-// the viscous flux and wave64 / block / multi-block reductions (fixed
+// Device helpers shared by the gfx950 kernels: gas physics, the HLLC flux
+// and wave64 / block / multi-block reductions (fixed
 // summation order everywhere, no float atomics).
 #pragma once
 
@@ -33,11 +33,6 @@ template <typename T> __device__ __forceinline__ T dpow(T a, T b)
 {
     if constexpr (std::is_same_v<T, float>) return powf(a, b);
     else return pow(a, b);
-}
-template <typename T> __device__ __forceinline__ T dsqrt(T a)
-{
-    if constexpr (std::is_same_v<T, float>) return sqrtf(a);
-    else return sqrt(a);
 }
 // Square root of a normal number (sound speeds): hardware 1/sqrt estimate; in FP64 one
 // coupled Goldschmidt step for g ~ sqrt(a), h ~ 1/(2 sqrt(a)), then two Newton corrections
@@ -186,45 +181,41 @@ __device__ __forceinline__ void pert_pressures(const Gas<T>& G, const T (&rt1)[n
     }
 }
 
-// HLLC flux (Toro) for the normal +e_D of a Cartesian face (D = 1: x, D = 2: z), Davis
-// wave speeds S_L = min(q_L - c_L, q_R - c_R), S_R = max(q_L + c_L, q_R + c_R); star flux
-// in the S*-factored form (S*(S_K U_K - F_K) + S_K p*_K e_D) / (S_K - S*),
-// p*_K = p_K + rho_K (S_K - q_K)(S* - q_K).  1/rho of both states is given (the callers
-// reuse it).  pL, pR set the sound speeds; dpL, dpR enter wherever the pressure is added
-// (the physical fluxes, the star pressure, p_R - p_L): the full pressures for the flux
-// F, or p - pb with a background pressure pb shared by both sides for F - pb e_D (the
-// star flux is affine in the pressure with weight one).
-// A face with normal -e_D is the mirror case, H(a, b; -e) = -H(b, a; +e), so every
+// HLLC flux (Toro) through a Cartesian face in its frame (component 1 the momentum along the
+// positive normal, 2 the tangential one), Davis wave speeds S_L = min(q_L - c_L, q_R - c_R),
+// S_R = max(q_L + c_L, q_R + c_R); star flux in the S*-factored form
+// (S*(S_K U_K - F_K) + S_K p*_K e_1) / (S_K - S*), p*_K = p_K + rho_K (S_K - q_K)(S* - q_K).
+// 1/rho of both states is given (the callers reuse it).
+// A face with the opposite normal is the mirror case, H(a, b; -e) = -H(b, a; +e), so every
 // Cartesian face (slip walls included, via a mirrored ghost state) needs only this form.
 // Without branches: the supersonic cases take the physical flux of the side that the
 // star flux is built on, so that one basic block holds the face and its long dependency
 // chain overlaps the work around it.
-template <typename T, int D>
-__device__ __forceinline__ void hllc_ax(const Gas<T>& G, const T* UL, const T* UR, T pL, T pR, T dpL, T dpR, T irL,
-                                        T irR, T* F)
+__device__ __forceinline__ void hllc(const Gas<double>& G, const double* UL, const double* UR, double pL, double pR,
+                                     double irL, double irR, double* F)
 {
-    constexpr int E = 3 - D;   // tangential momentum
-    const T rL = UL[0], rR = UR[0];
-    const T qL = UL[D] * irL, qR = UR[D] * irR;
-    const T cL = psqrt<T>(G.gamma * pL * irL), cR = psqrt<T>(G.gamma * pR * irR);
-    const T SL = fmin(qL - cL, qR - cR);
-    const T SR = fmax(qL + cL, qR + cR);
-    const T Ss = (dpR - dpL + rL * qL * (SL - qL) - rR * qR * (SR - qR)) * frcp<T>(rL * (SL - qL) - rR * (SR - qR));
-    const bool supL = SL >= T(0), supR = SR <= T(0);
-    const bool lk = supL | (!supR & (Ss >= T(0)));
-    const T SK = lk ? SL : SR, rK = lk ? rL : rR, qK = lk ? qL : qR, dpK = lk ? dpL : dpR;
-    const T uD = lk ? UL[D] : UR[D], uE = lk ? UL[E] : UR[E], u3 = lk ? UL[3] : UR[3];
-    const T FD = uD * qK + dpK, FE = uE * qK, F3 = u3 * qK;   // the physical flux (first component: uD)
-    const T pst = dpK + rK * (SK - qK) * (Ss - qK);
-    const T iden = frcp<T>(SK - Ss);
-    const T G0 = (Ss * (SK * rK - uD)) * iden;
-    const T GD = (Ss * (SK * uD - FD) + SK * pst) * iden;
-    const T GE = (Ss * (SK * uE - FE)) * iden;
-    const T G3 = (Ss * (SK * u3 - F3)) * iden;
+    const double rL = UL[0], rR = UR[0];
+    const double qL = UL[1] * irL, qR = UR[1] * irR;
+    const double cL = psqrt<double>(G.gamma * pL * irL), cR = psqrt<double>(G.gamma * pR * irR);
+    const double SL = fmin(qL - cL, qR - cR);
+    const double SR = fmax(qL + cL, qR + cR);
+    const double Ss =
+        (pR - pL + rL * qL * (SL - qL) - rR * qR * (SR - qR)) * frcp<double>(rL * (SL - qL) - rR * (SR - qR));
+    const bool supL = SL >= 0.0, supR = SR <= 0.0;
+    const bool lk = supL | (!supR & (Ss >= 0.0));
+    const double SK = lk ? SL : SR, rK = lk ? rL : rR, qK = lk ? qL : qR, pK = lk ? pL : pR;
+    const double u1 = lk ? UL[1] : UR[1], u2 = lk ? UL[2] : UR[2], u3 = lk ? UL[3] : UR[3];
+    const double F1 = u1 * qK + pK, F2 = u2 * qK, F3 = u3 * qK;   // the physical flux (first component: u1)
+    const double pst = pK + rK * (SK - qK) * (Ss - qK);
+    const double iden = frcp<double>(SK - Ss);
+    const double G0 = (Ss * (SK * rK - u1)) * iden;
+    const double G1 = (Ss * (SK * u1 - F1) + SK * pst) * iden;
+    const double G2 = (Ss * (SK * u2 - F2)) * iden;
+    const double G3 = (Ss * (SK * u3 - F3)) * iden;
     const bool sup = supL | supR;
-    F[0] = sup ? uD : G0;
-    F[D] = sup ? FD : GD;
-    F[E] = sup ? FE : GE;
+    F[0] = sup ? u1 : G0;
+    F[1] = sup ? F1 : G1;
+    F[2] = sup ? F2 : G2;
     F[3] = sup ? F3 : G3;
 }
 
@@ -292,7 +283,7 @@ template <int NTH> __device__ __forceinline__ double block_max(double v, double*
 // partial with a plain store; the partials are summed in a fixed order either
 // by a one-block finalize kernel launched right after the producer (scalars the
 // host or a later kernel reads) or by each block of the consuming kernel
-// itself (sum_partials).  Kernel boundaries make the partials visible; no
+// itself (PartialSum).  Kernel boundaries make the partials visible; no
 // agent-scope fence is executed per block.
 struct Red {
     double* partials;   // [nq][number of blocks]

@@ -18,21 +18,15 @@ int la_blocks(long n)
     return (int)((n + (long)LA_NTH * LA_EL - 1) / ((long)LA_NTH * LA_EL));
 }
 
-// out[q] = sum_b p[q * nb + b], one block per q, fixed order (0 where the gate is closed); with
-// host (pinned) also host[m * entries + q], which saves the gather launch of a sum that only the
+// out[q] = sum_b p[q * nb + b], one block per q, fixed order; with host (pinned) also host[m * entries + q], which saves the gather launch of a sum that only the
 // host waits for (stage residual and its norm at 1024x256 nodes 28.7 -> 27.5 us)
-__global__ void __launch_bounds__(256) finalize_kernel(const double* __restrict__ p, int nb, double* __restrict__ out,
-                                                       Gate gate, long ms, double* __restrict__ host)
+__global__ void __launch_bounds__(256)
+finalize_kernel(const double* __restrict__ p, int nb, double* __restrict__ out, long ms, double* __restrict__ host)
 {
     p = mbr(p, ms);
     out = mbr(out, ms);
-    gate.h = mbr(gate.h, ms);
     __shared__ double sh[4];
     const int q = blockIdx.x;
-    if (!gate_open(gate)) {
-        if (threadIdx.x == 0) out[q] = 0.0;
-        return;
-    }
     // eight loads in flight per thread
     const double* pq = p + (long)q * nb;
     double a = 0.0;
@@ -54,10 +48,9 @@ __global__ void __launch_bounds__(256) finalize_kernel(const double* __restrict_
     }
 }
 
-void launch_finalize(const double* partials, int nb, int nq, double* out, hipStream_t st, Gate gate, const Mb& mb,
-                     double* host)
+void launch_finalize(const double* partials, int nb, int nq, double* out, hipStream_t st, const Mb& mb, double* host)
 {
-    finalize_kernel<<<dim3(nq, 1, mb.n), dim3(256), 0, st>>>(partials, nb, out, gate, mb.ms, host);
+    finalize_kernel<<<dim3(nq, 1, mb.n), dim3(256), 0, st>>>(partials, nb, out, mb.ms, host);
 }
 
 // Scalars between the device slots of every member and coherent pinned host
@@ -106,7 +99,7 @@ void launch_norm2(const double* x, long n, Red red, hipStream_t st, const Mb& mb
     long b = (n + 255) / 256;
     const int nb = (int)(b < 1024 ? b : 1024);
     norm2_kernel<<<dim3(nb, 1, mb.n), dim3(256), 0, st>>>(x, n, red, mb.ms, mb.tab);
-    if (red.out) launch_finalize(red.partials, nb, 1, red.out, st, Gate{}, mb);
+    if (red.out) launch_finalize(red.partials, nb, 1, red.out, st, mb);
 }
 
 // Element k of the thread at base = block start + t (wave-wide loads of 512 contiguous bytes).
@@ -210,7 +203,7 @@ void launch_multidot(const double* w, const double* V, long ld, int nv, int self
     const int nb = la_blocks(n), ng = (nv + 3) / 4;
     const int gy = std::min(ng, std::max(1, LA_FILL / (nb * mb.n)));
     timed_launch(multidot_kernel, dim3(nb, gy, mb.n), dim3(LA_NTH), st, w, V, ld, nv, self, n, red, mb.ms, mb.tab);
-    if (red.out) launch_finalize(red.partials, nb, nv + self, red.out, st, Gate{}, mb);
+    if (red.out) launch_finalize(red.partials, nb, nv + self, red.out, st, mb);
 }
 
 // w -= sum_v h[v] V_v.
@@ -373,7 +366,7 @@ void launch_update(double* w, const double* V, long ld, int nv, long n, double* 
 // partials in a fixed order into pub.out, publishes, and clears the counter for the next
 // launch.  Where it is closed every work-group returns at once: there are at most
 // UPDATE2_GROUPS of them over all members, each taking blocks of w in turn (with one per
-// block, 9216 of them, the closed gate, the usual case, took 12 us; 1024 of them 4.1).
+// block, 9216 of them, the closed gate, the usual case, took 12 us; 1024 of them 5.7).
 __global__ void __launch_bounds__(LA_NTH)
 update2_kernel(double* __restrict__ w, const double* __restrict__ V, long ld, int nv, long n, Gate gate, Red red,
                long ms, const MemberArgs* __restrict__ mt, const double* __restrict__ hpart, int hnb,
@@ -593,7 +586,7 @@ void launch_dg_smooth(double* out, const double* x0, const double* r, const doub
     const int nb = (int)(b < 1024 ? b : 1024);
     if (!red.out) red.partials = nullptr;
     timed_launch(dg_smooth_kernel, dim3(nb, 1, mb.n), dim3(256), st, out, x0, r, t, alpha, dtau, n, red, mb.ms);
-    if (red.out) launch_finalize(red.partials, nb, 1, red.out, st, Gate{}, mb);
+    if (red.out) launch_finalize(red.partials, nb, 1, red.out, st, mb);
 }
 
 __global__ void __launch_bounds__(64) dg_dtau_kernel(const double* __restrict__ lam, double* __restrict__ out,

@@ -318,7 +318,7 @@ void launch_transfer_Tinv(int k, const DgArgs& A, int mass_fix, const T* u, doub
     if (k == 1) transfer_Tinv_k<2, T>(g, A, mass_fix, u, U, nxf, red, st, mb);
     else if (k == 2) transfer_Tinv_k<3, T>(g, A, mass_fix, u, U, nxf, red, st, mb);
     else transfer_Tinv_k<4, T>(g, A, mass_fix, u, U, nxf, red, st, mb);
-    if (red.out) launch_finalize(red.partials, (int)g.x, 1, red.out, st, Gate{}, mb);
+    if (red.out) launch_finalize(red.partials, (int)g.x, 1, red.out, st, mb);
 }
 
 template int launch_transfer_T<double>(int, const DgArgs&, int, const double*, double*, int, hipStream_t,
