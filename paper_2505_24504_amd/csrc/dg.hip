@@ -208,8 +208,8 @@ __device__ __forceinline__ void dg_line(const double* __restrict__ U, long N, un
 // time (two per CU, 512).  With more of them, LEAN: the halo's lines after the own, the stored
 // terms where they are used, three waves per SIMD; the same products and sums.  Inviscid
 // k = 2, 24 members: 34.3 -> 30.6 us per launch, the ensemble's step 71.5 -> 70.3 ms.  Not
-// for the viscous kernels and k = 3, whose registers would spill (k = 3 viscous, 9.4 M
-// unknowns: 169 us, 201 so).
+// for the viscous kernels and k = 3, whose registers spill (k = 3, viscous, 9.4 M unknowns:
+// 169 us, 201 so; inviscid, 16 registers: 46.0 and 50.3 us at 4.2 M, 207 and 237 at 16.8 M).
 constexpr long DG_LEAN_TILES = 512;
 template <int N1, bool NS> constexpr bool DG_LEAN = !NS && N1 <= 3;
 

@@ -1135,6 +1135,9 @@ static int tile_launch_shape(const FvArgs<T>& A, const T* u, const T* F0, const 
     // Every work-group sums all partials of ||x||^2 by itself, which saves a launch (3 us)
     // while they are few; 4608 of them, read by as many work-groups, made the second stage of
     // 2.4 M cells take 82 us where the one after 1024 partials took 45: one launch before it.
+    // (Eighteen sweeps with and without that launch, us, 64x4 tiles of a level 1024 cells wide:
+    // FP64 2048 partials 391 and 385, 3072 501 and 494, 3328 538 and 558, 5120 766 and 832;
+    // FP32 250 and 231, 320 and 314, 343 and 356, 460 and 496.)
     // (Not a timed launch: the caller's kernel class is that of the tile kernel.)
     if (MODE != FVM_LIN && xcount > FV_SUM_MAX) {
         fv_sum_kernel<NTH><<<dim3(1, 1, (unsigned)mb.n), dim3(NTH), 0, st>>>(const_cast<double*>(xpart), xcount,
@@ -1294,7 +1297,9 @@ void FvLaunch<T>::norm2(const T* x, long n, Red red, hipStream_t st, const Mb& m
 //   2359296    268 / 101   191 / 84.7  129 / 61.1 93.1 / 50.7  102 / 45.6
 // (by the level's width, the rule before, 192 x 96 cells took 8x4, the members 16x4 and a
 // level of 2400 x 80 cells 64x8, 11.7 / 8.7 against 10.5 / 7.8 with 64x4).  64x8 is the
-// fastest where its tiles fill the 512 places of one round, and in FP32 on large levels.
+// fastest in FP64 where its tiles fill the 512 places of one round (us, 64x8 and 64x4: 10.4 and
+// 10.7 at 448 tiles, 10.6 and 10.8 at 480; in FP32 7.6 and 7.5; below, 10.3 and 9.1 at 384; with
+// a second round 14.0 and 12.4 at 528), and in FP32 on large levels.
 // Rows that leave more than 30 % of the 64-cell rows empty take 16x4.
 int fv_default_tile(long cells, long padded64, bool f32)
 {

@@ -122,7 +122,9 @@ __device__ __forceinline__ double lane_value(double v, int l)
 // stays in registers: the basis vectors come in groups of G, the next group's loads in
 // flight while the current one is reduced (the wave's sums; one LDS exchange at the end
 // combines the waves); the block partials [v][block] are summed by the finalize kernel.
-// Grids too small to fill the chip split the groups over blockIdx.y.
+// Grids too small to fill the chip split the groups over blockIdx.y, into LA_FILL blocks at
+// most (mean launch of a step, us, unsplit and so: 6.8 and 5.5 with 128 blocks, 8.0 and 7.4
+// with 256, 11.9 and 11.6 with 512, 18.9 and 19.3 with 1024; twice as many: 19.9 with 1024).
 __global__ void __launch_bounds__(LA_NTH)
 multidot_kernel(const double* __restrict__ w, const double* __restrict__ V, long ld, int nv, int self, long n, Red red,
                 long ms, const MemberArgs* __restrict__ mt)
