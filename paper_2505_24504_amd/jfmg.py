@@ -418,7 +418,8 @@ class Problem:
 
     def autotune(self, reps: int = 10):
         """Time every tile shape on every level (needs linearize) and keep the
-        fastest; returns (shapes, {level: {shape: mean us per launch}})."""
+        fastest; returns (shapes, {level: {shape: mean us per launch}}), where the
+        time of "8x4" on levels that it puts in one launch is their share of it."""
         n = int(self.cfg.mg_levels)
         a = (C.c_int * n)()
         t = (C.c_double * (n * len(TILES)))()
